@@ -1388,7 +1388,8 @@ gs_status gs_feature_stats(const float *features, int64_t n, float *norm, void *
     gs_status s = begin_call(&dev, st);
     if (s != GS_OK) return s;
     DoneGuard done_guard{dev, st};
-    feature_stats(features, n, norm, st);
+    HIP_TRY(arena_reserve(g_work[dev], feature_stats_scratch_bytes(n)));
+    feature_stats(features, n, norm, g_work[dev].base, st);
     HIP_TRY(hipGetLastError());
     return GS_OK;
 }

@@ -342,7 +342,8 @@ size_t knn_scratch_bytes(int64_t n);
 // instead (nidx [n][16] indices, nd2 [n][16] float32 squared distances).
 hipError_t knn_features(const SceneDev &sc, float *feat, void *scratch, hipStream_t st, uint32_t *nidx = nullptr,
                         float *nd2 = nullptr);
-void feature_stats(const float *feat, int64_t n, float *norm, hipStream_t st);
+size_t feature_stats_scratch_bytes(int64_t n);
+void feature_stats(const float *feat, int64_t n, float *norm, void *scratch, hipStream_t st);
 size_t mixture_scratch_bytes(int64_t n);
 void proposal_mixture(const float *y, int64_t n, float floor, float *p, void *scratch, hipStream_t st);
 void log_targets(const float *s, int64_t n, float floor, float *out, hipStream_t st);

@@ -259,15 +259,59 @@ __global__ __launch_bounds__(256) void k_knn_features(SceneDev sc, Grid G, const
 }
 
 // Column means and 1/std (population) of an n x 64 float32 matrix, in FP64.
-__global__ __launch_bounds__(256) void k_feature_stats(const float *__restrict__ feat, int64_t n,
-                                                       float *__restrict__ norm) {
+// Bound by reading the matrix once.  A block takes kStatRows consecutive rows:
+// thread t reads the four columns 4 (t mod 16) .. + 3 of rows t / 16, t / 16 +
+// 16, ... as one float4, so a wave reads 1 KiB of consecutive memory per load,
+// and the block's sums go to its own slot; a second launch adds the slots in
+// block order (fixed, so the result is deterministic).  With one block per
+// column, every block read every 256-byte row for 4 bytes of it and only 64
+// of the 256 CUs worked: 2.17 ms for 10^6 rows (features and their statistics
+// together 7.58 -> 5.39 ms).
+// (The rows are only known to be 4-byte aligned: f32x4u says so.)
+constexpr int kStatRows = 1024;
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+static int64_t stat_blocks(int64_t n) { return (n + kStatRows - 1) / kStatRows; }
+size_t feature_stats_scratch_bytes(int64_t n) { return sizeof(double) * 2 * kMlpIn * (size_t)stat_blocks(n) + 256; }
+
+__global__ __launch_bounds__(256) void k_feature_sums(const float *__restrict__ feat, int64_t n,
+                                                      double *__restrict__ part) {
+    __shared__ double sh[16][2 * kMlpIn];
+    const int cg = threadIdx.x & 15, rg = threadIdx.x >> 4;
+    const int64_t lo = (int64_t)blockIdx.x * kStatRows, hi = min(lo + (int64_t)kStatRows, n);
+    double a[4] = {0, 0, 0, 0}, b[4] = {0, 0, 0, 0};
+#pragma unroll 4
+    for (int64_t r = lo + rg; r < hi; r += 16) {
+        const f32x4u v = *reinterpret_cast<const f32x4u *>(feat + r * kMlpIn + 4 * cg);
+        const double x[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            a[k] += x[k];
+            b[k] += x[k] * x[k];
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        sh[rg][4 * cg + k] = a[k];
+        sh[rg][kMlpIn + 4 * cg + k] = b[k];
+    }
+    __syncthreads();
+    if (threadIdx.x < 2 * kMlpIn) {
+        double s = 0.0;
+        for (int k = 0; k < 16; ++k) s += sh[k][threadIdx.x];
+        part[(int64_t)blockIdx.x * (2 * kMlpIn) + threadIdx.x] = s;
+    }
+}
+
+// One block per column: thread t adds the slots t, t + 256, ... in order, then
+// a fixed tree.
+__global__ __launch_bounds__(256) void k_feature_norm(const double *__restrict__ part, int64_t nblk, int64_t n,
+                                                      float *__restrict__ norm) {
     __shared__ double s1[256], s2[256];
     const int c = blockIdx.x;
     double a = 0.0, b = 0.0;
-    for (int64_t r = threadIdx.x; r < n; r += 256) {
-        const double x = feat[r * kMlpIn + c];
-        a += x;
-        b += x * x;
+    for (int64_t r = threadIdx.x; r < nblk; r += 256) {
+        a += part[r * (2 * kMlpIn) + c];
+        b += part[r * (2 * kMlpIn) + kMlpIn + c];
     }
     s1[threadIdx.x] = a;
     s2[threadIdx.x] = b;
@@ -287,8 +331,11 @@ __global__ __launch_bounds__(256) void k_feature_stats(const float *__restrict__
     }
 }
 
-void feature_stats(const float *feat, int64_t n, float *norm, hipStream_t st) {
-    hipLaunchKernelGGL(k_feature_stats, dim3(kMlpIn), dim3(256), 0, st, feat, n, norm);
+void feature_stats(const float *feat, int64_t n, float *norm, void *scratch, hipStream_t st) {
+    double *part = (double *)scratch;
+    const int64_t nblk = stat_blocks(n);
+    hipLaunchKernelGGL(k_feature_sums, dim3((unsigned)nblk), dim3(256), 0, st, feat, n, part);
+    hipLaunchKernelGGL(k_feature_norm, dim3(kMlpIn), dim3(256), 0, st, part, nblk, n, norm);
 }
 
 size_t knn_scratch_bytes(int64_t n) {
