@@ -410,14 +410,15 @@ gs_status gs_mlp_init(float *params, uint64_t seed, void *stream);
  * padded to 48, then over the 16 nearest other means (exact, ties by
  * index): log mean distance, log 16th distance, mean and max neighbour
  * alpha, log(sum of alphas / volume of the 16th-neighbour ball).
- * Synchronises the stream once (grid sizing). */
+ * Queued on the stream; no synchronisation. */
 gs_status gs_features(const gs_scene *scene, float *features, void *stream);
 
 /* The 16 nearest other means of every Gaussian, the neighbourhood the
  * features above are built from: neighbours device uint32[n][16] (indices;
  * 0xFFFFFFFF where fewer than 16 others exist), sq_dist device float[n][16]
  * (squared distances as float32 (dx dx + dy dy) + dz dz, +inf where missing),
- * ordered by (squared distance, index).  Synchronises the stream once. */
+ * ordered by (squared distance, index).  Queued on the stream; no
+ * synchronisation. */
 gs_status gs_knn(const gs_scene *scene, uint32_t *neighbours, float *sq_dist, void *stream);
 
 /* Column means and 1/std of device float[n][64] into device float[2][64]. */

@@ -10,18 +10,19 @@
 //   61 mean neighbour alpha, 62 max neighbour alpha,
 //   63 log(sum of neighbour alphas / volume of the 16th-neighbour ball).
 //
-// Grid: cell edge = cube root of (bounding-box volume / n), so one point per
-// cell on average; points are counting-sorted by cell.  A query visits rings
-// of cells at Chebyshev distance r = 0, 1, 2, ... and stops once it holds 16
-// neighbours and the 16th is closer than r cell edges (every unvisited point
-// is at least that far away).
+// Exact search: the points are sorted along a Hilbert curve, every 32 of them
+// are a leaf with its bounding box, and every 64 nodes of a level are the
+// children of one node of the next.  A wave answers the queries of 64
+// consecutive points of the curve: it descends from the top level, takes the
+// children nearest its queries' common box first and leaves out every subtree
+// that is farther than the worst 16th distance of its queries.  The curve only
+// decides what is visited when; which neighbours are found does not depend on
+// it.
 #include "gs_internal.hpp"
 
 #include <hip/hip_fp16.h>
 
 #include <algorithm>
-#include <cmath>
-#include <cstring>
 
 namespace gs {
 
@@ -39,223 +40,535 @@ __device__ __forceinline__ uint32_t ord_bits(float f) {
     return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
-// box[0..2] = min (ordered bits), box[3..5] = max
 // Bounding box of the means (order-preserving bits, so min / max are integer
-// operations): a fixed grid strides over the points, each block folds its
-// waves in LDS and adds one atomic per bound (atomics on one address
-// serialise, so one per wave would cost about a millisecond at 10^6 points).
+// operations) and the sums of the coordinates and of their squares, over the
+// points whose coordinates are all finite: a fixed grid strides over the
+// points, each block folds its waves in LDS and adds one atomic per value
+// (atomics on one address serialise, so one per wave would cost about a
+// millisecond at 10^6 points).
+struct CloudStats {
+    uint32_t lo[3], hi[3];        // ordered bits
+    unsigned long long finite;
+    double sum[3], sq[3];
+};
 constexpr int kBoxBlocks = 256;
-__global__ __launch_bounds__(256) void k_bbox(SceneDev sc, uint32_t *box) {
+
+__global__ void k_cloud_init(CloudStats *cs) {
+    for (int c = 0; c < 3; ++c) {
+        cs->lo[c] = 0xFFFFFFFFu;
+        cs->hi[c] = 0u;
+        cs->sum[c] = cs->sq[c] = 0.0;
+    }
+    cs->finite = 0ull;
+}
+
+__global__ __launch_bounds__(256) void k_cloud_stats(SceneDev sc, CloudStats *cs) {
     __shared__ uint32_t red[4][6];
+    __shared__ double sums[4][7];
     uint32_t lo[3] = {0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu}, hi[3] = {0u, 0u, 0u};
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < sc.n; i += (int64_t)gridDim.x * blockDim.x)
+    double sum[3] = {0, 0, 0}, sq[3] = {0, 0, 0}, cnt = 0;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < sc.n; i += (int64_t)gridDim.x * blockDim.x) {
+        float x[3];
+        for (int c = 0; c < 3; ++c) x[c] = kload(sc.mean, c * sc.n + i, sc.format, false);
+        if (!(isfinite(x[0]) && isfinite(x[1]) && isfinite(x[2]))) continue;
+        cnt += 1.0;
         for (int c = 0; c < 3; ++c) {
-            const uint32_t b = ord_bits(kload(sc.mean, c * sc.n + i, sc.format, false));
+            const uint32_t b = ord_bits(x[c]);
             lo[c] = min(lo[c], b);
             hi[c] = max(hi[c], b);
+            sum[c] += (double)x[c];
+            sq[c] += (double)x[c] * (double)x[c];
         }
-    for (int c = 0; c < 3; ++c)
-        for (int off = 32; off > 0; off >>= 1) {
+    }
+    for (int off = 32; off > 0; off >>= 1) {
+        for (int c = 0; c < 3; ++c) {
             lo[c] = min(lo[c], (uint32_t)__shfl_xor((int)lo[c], off));
             hi[c] = max(hi[c], (uint32_t)__shfl_xor((int)hi[c], off));
+            sum[c] += __shfl_xor(sum[c], off);
+            sq[c] += __shfl_xor(sq[c], off);
         }
+        cnt += __shfl_xor(cnt, off);
+    }
     const int w = threadIdx.x >> 6;
-    if ((threadIdx.x & 63) == 0)
+    if ((threadIdx.x & 63) == 0) {
         for (int c = 0; c < 3; ++c) {
             red[w][c] = lo[c];
             red[w][3 + c] = hi[c];
+            sums[w][c] = sum[c];
+            sums[w][3 + c] = sq[c];
         }
+        sums[w][6] = cnt;
+    }
     __syncthreads();
-    if (threadIdx.x < 3) {
-        const int c = threadIdx.x;
-        atomicMin(&box[c], min(min(red[0][c], red[1][c]), min(red[2][c], red[3][c])));
-        atomicMax(&box[3 + c], max(max(red[0][3 + c], red[1][3 + c]), max(red[2][3 + c], red[3][3 + c])));
+    const int t = threadIdx.x;
+    if (t < 3) {
+        atomicMin(&cs->lo[t], min(min(red[0][t], red[1][t]), min(red[2][t], red[3][t])));
+        atomicMax(&cs->hi[t], max(max(red[0][3 + t], red[1][3 + t]), max(red[2][3 + t], red[3][3 + t])));
+    }
+    if (t < 7) {
+        const double v = (sums[0][t] + sums[1][t]) + (sums[2][t] + sums[3][t]);
+        if (t < 3)
+            atomicAdd(&cs->sum[t], v);
+        else if (t < 6)
+            atomicAdd(&cs->sq[t - 3], v);
+        else
+            atomicAdd(&cs->finite, (unsigned long long)v);
     }
 }
 
-struct Grid {
-    float lo[3];
-    float cell, inv_cell;
-    int dim[3];
-};
-
-__device__ __forceinline__ int cell_coord(float x, float lo, float inv_cell, int dim) {
-    int c = (int)floorf((x - lo) * inv_cell);
-    return c < 0 ? 0 : (c >= dim ? dim - 1 : c);
+__device__ __forceinline__ float from_ord(uint32_t u) {
+    return __uint_as_float((u & 0x80000000u) ? (u & 0x7FFFFFFFu) : ~u);
 }
 
-__global__ void k_cell_count(SceneDev sc, Grid G, uint32_t *__restrict__ cell_of, uint32_t *__restrict__ count) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= sc.n) return;
-    int c3[3];
-    for (int c = 0; c < 3; ++c)
-        c3[c] = cell_coord(kload(sc.mean, c * sc.n + i, sc.format, false), G.lo[c], G.inv_cell, G.dim[c]);
-    const uint32_t id = (uint32_t)((c3[2] * G.dim[1] + c3[1]) * G.dim[0] + c3[0]);
-    cell_of[i] = id;
-    atomicAdd(&count[id], 1u);
+// Every third bit: 10 bits -> 30.
+__device__ __forceinline__ uint32_t spread3(uint32_t x) {
+    x = (x | (x << 16)) & 0x030000FFu;
+    x = (x | (x << 8)) & 0x0300F00Fu;
+    x = (x | (x << 4)) & 0x030C30C3u;
+    return (x | (x << 2)) & 0x09249249u;
 }
 
-__global__ void k_cell_scatter(int64_t n, const uint32_t *__restrict__ cell_of, const uint64_t *__restrict__ off,
-                               uint32_t *__restrict__ fill, uint32_t *__restrict__ order, float4 *__restrict__ pts,
-                               SceneDev sc) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const uint32_t c = cell_of[i];
-    const uint64_t p = off[c] + atomicAdd(&fill[c], 1u);
-    order[p] = (uint32_t)i;
-    const float x = kload(sc.mean, i, sc.format, false), y = kload(sc.mean, sc.n + i, sc.format, false);
-    const float z = kload(sc.mean, 2 * sc.n + i, sc.format, false);
-    const float a = kload(sc.opacity, i, sc.format, true);
-    pts[p] = make_float4(x, y, z, a);
-}
-
-__device__ __forceinline__ bool knn_less(float da, uint32_t ia, float db, uint32_t ib) {
-    return da < db || (da == db && ia < ib);
-}
-
-// kNeighbours: write the neighbour lists (indices and float32 squared
-// distances, ordered by (distance, index)) instead of the features.
-template <bool kNeighbours>
-__global__ __launch_bounds__(256) void k_knn_features(SceneDev sc, Grid G, const uint64_t *__restrict__ off,
-                                                      const uint32_t *__restrict__ order,
-                                                      const float4 *__restrict__ pts, float *__restrict__ feat,
-                                                      uint32_t *__restrict__ nidx, float *__restrict__ nd2) {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= sc.n) return;
-    const uint32_t q = order[t];     // queries in cell order: neighbouring lanes share cells
-    const float4 me = pts[t];
-    int c3[3];
-    c3[0] = cell_coord(me.x, G.lo[0], G.inv_cell, G.dim[0]);
-    c3[1] = cell_coord(me.y, G.lo[1], G.inv_cell, G.dim[1]);
-    c3[2] = cell_coord(me.z, G.lo[2], G.inv_cell, G.dim[2]);
-    float bd[kK];
-    uint32_t bi[kK];
-    float ba[kK];
+// Position of the cell (x[0], x[1], x[2]), 10 bits each, on a 3D Hilbert curve
+// (Skilling, "Programming the Hilbert curve", 2004): consecutive positions are
+// neighbouring cells, so 64 consecutive points of the curve stay together (on
+// a Morton curve they may lie on both sides of a jump).
+__device__ __forceinline__ uint32_t hilbert30(uint32_t (&x)[3]) {
 #pragma unroll
-    for (int k = 0; k < kK; ++k) {
-        bd[k] = INFINITY;
-        bi[k] = 0xFFFFFFFFu;
-        ba[k] = 0.0f;
-    }
-    const int rmax = max(G.dim[0], max(G.dim[1], G.dim[2]));
-    for (int r = 0; r <= rmax; ++r) {
-        for (int dz = -r; dz <= r; ++dz) {
-            const int z = c3[2] + dz;
-            if (z < 0 || z >= G.dim[2]) continue;
-            for (int dy = -r; dy <= r; ++dy) {
-                const int y = c3[1] + dy;
-                if (y < 0 || y >= G.dim[1]) continue;
-                const bool face = (dz == -r || dz == r || dy == -r || dy == r);
-                const int step = face ? 1 : 2 * r;
-                for (int dx = -r; dx <= r; dx += (step > 0 ? step : 1)) {
-                    const int x = c3[0] + dx;
-                    if (x < 0 || x >= G.dim[0]) continue;
-                    const uint32_t id = (uint32_t)((z * G.dim[1] + y) * G.dim[0] + x);
-                    const uint64_t lo = off[id], hi = off[id + 1];
-                    // candidates four at a time, their loads issued together
-                    // (slots past the cell's end repeat the query and are skipped)
-                    for (uint64_t p0 = lo; p0 < hi; p0 += 4) {
-                        uint32_t jj[4];
-                        float4 oo[4];
+    for (uint32_t q = 512u; q > 1u; q >>= 1) {
+        const uint32_t low = q - 1u;
 #pragma unroll
-                        for (int u = 0; u < 4; ++u) {
-                            const bool ok = p0 + u < hi;
-                            jj[u] = ok ? order[p0 + u] : q;
-                            oo[u] = ok ? pts[p0 + u] : me;
-                        }
-#pragma unroll
-                        for (int u = 0; u < 4; ++u) {
-                            const uint32_t j = jj[u];
-                            if (j == q) continue;
-                            const float4 o = oo[u];
-                            const float ex = o.x - me.x, ey = o.y - me.y, ez = o.z - me.z;
-                            const float d2 = ex * ex + ey * ey + ez * ez;
-                            if (!knn_less(d2, j, bd[kK - 1], bi[kK - 1])) continue;
-                            bool placed = false;
-#pragma unroll
-                            for (int k = kK - 1; k >= 0; --k) {
-                                if (placed) continue;
-                                const bool move = k > 0 && knn_less(d2, j, bd[k - 1], bi[k - 1]);
-                                if (move) {
-                                    bd[k] = bd[k - 1];
-                                    bi[k] = bi[k - 1];
-                                    ba[k] = ba[k - 1];
-                                } else {
-                                    bd[k] = d2;
-                                    bi[k] = j;
-                                    ba[k] = o.w;
-                                    placed = true;
-                                }
-                            }
-                        }
-                    }
-                }
+        for (int i = 0; i < 3; ++i) {
+            const uint32_t t = (x[0] ^ x[i]) & low;
+            if (x[i] & q) {
+                x[0] ^= low;
+            } else {
+                x[0] ^= t;
+                x[i] ^= t;
             }
         }
-        // every point outside the searched cube of cells is at least `reach`
-        // away: the distance to the cube's nearest face that has cells beyond
-        // it (less a margin for the rounding of the cell assignment)
-        float reach = INFINITY;
-        const float pc[3] = {me.x, me.y, me.z};
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            if (c3[a] - r > 0) reach = fminf(reach, pc[a] - (G.lo[a] + (float)(c3[a] - r) * G.cell));
-            if (c3[a] + r < G.dim[a] - 1) reach = fminf(reach, (G.lo[a] + (float)(c3[a] + r + 1) * G.cell) - pc[a]);
-        }
-        reach -= 1e-4f * G.cell;
-        if (bi[kK - 1] != 0xFFFFFFFFu && (reach == INFINITY || (reach > 0.0f && bd[kK - 1] < reach * reach))) break;
     }
+    x[1] ^= x[0];
+    x[2] ^= x[1];
+    uint32_t t = 0u;
+#pragma unroll
+    for (uint32_t q = 512u; q > 1u; q >>= 1) t ^= (x[2] & q) ? q - 1u : 0u;
+    return (spread3(x[0] ^ t) << 2) | (spread3(x[1] ^ t) << 1) | spread3(x[2] ^ t);
+}
+
+// 30-bit curve positions on a cubic grid of 1024 cells per side over the part of
+// the bounding box within three standard deviations of the centroid (a few
+// far points would otherwise leave most of the cloud in a handful of cells;
+// points outside go to the border cells, non-finite ones to cell 0).
+__global__ __launch_bounds__(256) void k_curve(SceneDev sc, const CloudStats *__restrict__ cs,
+                                                uint32_t *__restrict__ code) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= sc.n) return;
+    const double m = fmax((double)cs->finite, 1.0);
+    float lo[3], ext = 1e-30f;
+    for (int c = 0; c < 3; ++c) {
+        const double mean = cs->sum[c] / m, sd = sqrt(fmax(cs->sq[c] / m - mean * mean, 0.0));
+        lo[c] = fmaxf(from_ord(cs->lo[c]), (float)(mean - 3.0 * sd));
+        ext = fmaxf(ext, fminf(from_ord(cs->hi[c]), (float)(mean + 3.0 * sd)) - lo[c]);
+    }
+    const float inv = 1024.0f / ext;
+    uint32_t x[3];
+    for (int c = 0; c < 3; ++c) {
+        const float f = (kload(sc.mean, c * sc.n + i, sc.format, false) - lo[c]) * inv;
+        x[c] = f > 0.0f ? (uint32_t)fminf(f, 1023.0f) : 0u;   // (a NaN goes to 0)
+    }
+    code[i] = hilbert30(x);
+}
+
+// A node's bounding box, 32 bytes, so that a lane reads its child's box as two
+// 16-byte loads and a wave-uniform one is a single scalar load.
+struct __align__(32) NodeBox {
+    float lo[3], hi[3];
+    float pad[2];
+};
+
+constexpr int kLeaf = 32, kFan = 64, kMaxLevels = 5;
+struct Tree {
+    const float4 *pts;                  // points along the curve: x, y, z, index (bits); NaN past n
+    const NodeBox *box[kMaxLevels];     // level 0: leaves
+    int count[kMaxLevels];
+};
+
+__device__ __forceinline__ float half_min(float v) {   // over each 32 lanes
+    for (int off = 16; off > 0; off >>= 1) v = fminf(v, __shfl_xor(v, off));
+    return v;
+}
+__device__ __forceinline__ float half_max(float v) {
+    for (int off = 16; off > 0; off >>= 1) v = fmaxf(v, __shfl_xor(v, off));
+    return v;
+}
+
+// Points in curve order and the boxes of the leaves (fminf / fmaxf leave NaN
+// coordinates out; a point that holds one is nobody's neighbour).
+__global__ __launch_bounds__(256) void k_leaves(SceneDev sc, const uint32_t *__restrict__ sorted, int64_t padded,
+                                                float4 *__restrict__ pts, NodeBox *__restrict__ leaf) {
+    const int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (p >= padded) return;            // (padded: a multiple of 64, so whole waves stay)
+    float x[3] = {NAN, NAN, NAN};
+    uint32_t i = 0xFFFFFFFFu;
+    if (p < sc.n) {
+        i = sorted[p];
+        for (int c = 0; c < 3; ++c) x[c] = kload(sc.mean, c * sc.n + i, sc.format, false);
+    }
+    pts[p] = make_float4(x[0], x[1], x[2], __uint_as_float(i));
+    NodeBox b;
+    for (int c = 0; c < 3; ++c) {
+        b.lo[c] = half_min(fminf(x[c], INFINITY));
+        b.hi[c] = half_max(fmaxf(x[c], -INFINITY));
+    }
+    b.pad[0] = b.pad[1] = 0.0f;
+    if ((threadIdx.x & (kLeaf - 1)) == 0) leaf[p / kLeaf] = b;
+}
+
+// One wave per node: the box of its (up to) 64 children.
+__global__ __launch_bounds__(64) void k_nodes(const NodeBox *__restrict__ child, int nchild,
+                                              NodeBox *__restrict__ node) {
+    const int c = blockIdx.x * kFan + (int)threadIdx.x;
+    NodeBox b;
+    for (int k = 0; k < 3; ++k) {
+        b.lo[k] = c < nchild ? child[c].lo[k] : INFINITY;
+        b.hi[k] = c < nchild ? child[c].hi[k] : -INFINITY;
+        b.lo[k] = half_min(b.lo[k]);
+        b.hi[k] = half_max(b.hi[k]);
+        b.lo[k] = fminf(b.lo[k], __shfl_xor(b.lo[k], 32));
+        b.hi[k] = fmaxf(b.hi[k], __shfl_xor(b.hi[k], 32));
+    }
+    b.pad[0] = b.pad[1] = 0.0f;
+    if (threadIdx.x == 0) node[blockIdx.x] = b;
+}
+
+// Wave-wide minimum: a DPP scan (shifts by 1, 2, 4, 8 inside rows of 16 lanes,
+// then row_bcast:15 and row_bcast:31; lanes without a source keep their value)
+// leaves it in lane 63.
+template <int kCtrl, int kRowMask>
+__device__ __forceinline__ uint32_t dpp_min_step(uint32_t v) {
+    return min(v, (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)v, kCtrl, kRowMask, 0xF, false));
+}
+__device__ __forceinline__ uint32_t wave_min_bits(uint32_t v) {
+    v = dpp_min_step<0x111, 0xF>(v);
+    v = dpp_min_step<0x112, 0xF>(v);
+    v = dpp_min_step<0x114, 0xF>(v);
+    v = dpp_min_step<0x118, 0xF>(v);
+    v = dpp_min_step<0x142, 0xA>(v);
+    v = dpp_min_step<0x143, 0xC>(v);
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+
+// A neighbour is one 64-bit word, the bits of its float32 squared distance
+// above its index: words order as (distance, index).  Read as doubles they are
+// non-negative and never NaN (a float's bits up to infinity's, 0x7F800000, are
+// a finite double's upper half), so one v_min_f64 / v_max_f64 compares two of
+// them (denormal doubles are kept: FP64 denormals are on).
+// Inserting word w into the ascending list b: b[k] = min(b[k], max(b[k-1], w))
+// from the last to the first, in place (31 instructions, two temporaries; as
+// separate statements the compiler holds all sixteen maxima at once, and the
+// kernel spills).
+__device__ __forceinline__ void insert_word(double (&b)[16], double w) {
+    double t0, t1;
+    asm("v_max_f64 %8, %6, %11\n v_max_f64 %9, %5, %11\n v_min_f64 %7, %7, %8\n v_min_f64 %6, %6, %9\n"
+        "v_max_f64 %8, %4, %11\n v_max_f64 %9, %3, %11\n v_min_f64 %5, %5, %8\n v_min_f64 %4, %4, %9\n"
+        "v_max_f64 %8, %2, %11\n v_max_f64 %9, %1, %11\n v_min_f64 %3, %3, %8\n v_min_f64 %2, %2, %9\n"
+        "v_max_f64 %8, %0, %11\n v_max_f64 %9, %10, %11\n v_min_f64 %1, %1, %8\n v_min_f64 %0, %0, %9\n"
+        : "+v"(b[8]), "+v"(b[9]), "+v"(b[10]), "+v"(b[11]), "+v"(b[12]), "+v"(b[13]), "+v"(b[14]), "+v"(b[15]),
+          "=&v"(t0), "=&v"(t1)
+        : "v"(b[7]), "v"(w));
+    asm("v_max_f64 %8, %6, %10\n v_max_f64 %9, %5, %10\n v_min_f64 %7, %7, %8\n v_min_f64 %6, %6, %9\n"
+        "v_max_f64 %8, %4, %10\n v_max_f64 %9, %3, %10\n v_min_f64 %5, %5, %8\n v_min_f64 %4, %4, %9\n"
+        "v_max_f64 %8, %2, %10\n v_max_f64 %9, %1, %10\n v_min_f64 %3, %3, %8\n v_min_f64 %2, %2, %9\n"
+        "v_max_f64 %8, %0, %10\n v_min_f64 %0, %0, %10\n v_min_f64 %1, %1, %8\n"
+        : "+v"(b[0]), "+v"(b[1]), "+v"(b[2]), "+v"(b[3]), "+v"(b[4]), "+v"(b[5]), "+v"(b[6]), "+v"(b[7]), "=&v"(t0),
+          "=&v"(t1)
+        : "v"(w));
+}
+__device__ __forceinline__ double word_of(float d2, uint32_t i) {
+    return __hiloint2double((int)__float_as_uint(d2), (int)i);
+}
+
+struct Query {
+    float x, y, z;
+    uint32_t self;
+    float kth;                      // 16th distance so far (below 0: the lane asks for nothing)
+    double best[kK];                // ascending
+};
+
+// The 32 points of a leaf against every lane's query.  The points are wave
+// uniform (scalar loads); a lane takes a candidate when it is no farther than
+// its 16th so far, and the wave then shifts it into the lists with 31 FP64
+// minima and maxima and no branches.
+__device__ __forceinline__ bool search_leaf(const float4 *__restrict__ pts, int leaf, Query &q) {
+    const float4 *__restrict__ P = pts + (int64_t)leaf * kLeaf;
+    bool changed = false;
+    // (the next four points load while these are compared)
+    float4 o[4], nx[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) nx[u] = P[u];
+#pragma unroll 1
+    for (int u0 = 0; u0 < kLeaf; u0 += 4) {
+        const int un = min(u0 + 4, kLeaf - 4);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) o[u] = nx[u];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) nx[u] = P[un + u];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const float ex = o[u].x - q.x, ey = o[u].y - q.y, ez = o[u].z - q.z;
+            const float d2 = ex * ex + ey * ey + ez * ez;
+            const uint32_t i = __float_as_uint(o[u].w);
+            const bool take = d2 <= q.kth && i != q.self;     // (false for a NaN)
+            if (__ballot(take) == 0ull) continue;
+            changed = true;
+            insert_word(q.best, word_of(take ? d2 : INFINITY, take ? i : 0xFFFFFFFFu));
+            q.kth = q.kth < 0.0f ? q.kth : __uint_as_float((uint32_t)__double2hiint(q.best[kK - 1]));
+        }
+    }
+    return changed;
+}
+
+// Squared distance from a box to a box (or a point): every operation rounds
+// monotonically, in the order the candidates' squared distances are formed in,
+// so no point inside the first box is nearer in float32 than this.
+__device__ __forceinline__ float box_dist(const float *blo, const float *bhi, const float *qlo, const float *qhi) {
+    float g[3];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) g[c] = fmaxf(0.0f, fmaxf(blo[c] - qhi[c], qlo[c] - bhi[c]));
+    return g[0] * g[0] + g[1] * g[1] + g[2] * g[2];
+}
+
+struct Walk {
+    float qlo[3], qhi[3];     // box of the wave's queries
+    float R;                  // the worst 16th distance of its queries
+    int own;                  // its first own leaf (own and own + 1 are searched first)
+};
+
+// The lane's word for child c0 + lane of a level: the distance of its box with
+// the lane in the low 6 bits (which only lowers it), or all ones for a child
+// that is not there, too far or, among leaves, searched already.  One wave
+// minimum then picks the nearest child.
+// The common box of queries that lie on both sides of a jump of the curve, or
+// far out, may hold most of the cloud: when more than kWide children pass it,
+// each is held against every query by itself.  (Without this one wave in 15 625
+// opened 22 016 leaves at 10^6 points, of which 552 were near a query, and the
+// launch waited 11 ms for it.)
+constexpr int kWide = 16;
+__device__ __forceinline__ float lane_value(float v, int j) {
+    return __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(v), j));
+}
+__device__ __forceinline__ uint32_t child_words(const NodeBox *__restrict__ box, int c0, int cnt, const Walk &w,
+                                                const Query &q, bool leaves) {
+    const int lane = threadIdx.x;
+    NodeBox b = {};
+    float d = INFINITY;
+    bool near = false;
+    if (lane < cnt) {
+        b = box[c0 + lane];
+        d = box_dist(b.lo, b.hi, w.qlo, w.qhi);
+        near = !(d > w.R) && !(leaves && (unsigned)(c0 + lane - w.own) < 2u);
+    }
+    if (__popcll(__ballot(near)) > kWide) {
+        bool some = false;
+        d = INFINITY;
+#pragma unroll 4
+        for (int j = 0; j < 64; ++j) {
+            const float at[3] = {lane_value(q.x, j), lane_value(q.y, j), lane_value(q.z, j)};
+            const float dj = box_dist(b.lo, b.hi, at, at);
+            const bool hit = !(dj > lane_value(q.kth, j));
+            some = some || hit;
+            d = hit ? fminf(d, dj) : d;
+        }
+        near = near && some;
+    }
+    return near ? (__float_as_uint(d) & ~63u) | (uint32_t)lane : 0xFFFFFFFFu;
+}
+
+__device__ __forceinline__ float worst_kth(const Query &q) {
+    return __uint_as_float(~wave_min_bits(~__float_as_uint(fmaxf(q.kth, 0.0f))));
+}
+
+// One wave per 64 points of the curve.  What bounds it: VALU issue, about 10
+// instructions per (candidate, wave) and 40 per candidate that some lane takes;
+// at 10^6 clustered points a wave compares some 2 300 candidates, takes 330 and
+// opens 150 leaves.  1.05 ms there; on a Morton curve 2.0 ms.  (A uniform grid
+// with one lane per query, its list in registers behind branches, scanned
+// thousands of candidates per query where clusters are dense: 5 to 10 ms.)
+// kNeighbours: write the neighbour lists (indices and float32 squared
+// distances, ordered by (distance, index)); else the neighbourhood features
+// 59 .. 63 of each point, by index, for k_feature_rows.
+template <bool kNeighbours, int kTop>
+__global__ __launch_bounds__(64, 4) void k_knn(SceneDev sc, Tree T, float *__restrict__ nf, uint32_t *__restrict__ nidx,
+                                            float *__restrict__ nd2) {
+    const int lane = threadIdx.x;
+    // consecutive waves of the curve on one XCD: they visit the same leaves
+    const int nw = (int)((sc.n + 63) / 64), per = (nw + 7) >> 3;
+    const int wv = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
+    if (wv >= nw) return;
+    const int64_t p = (int64_t)wv * 64 + lane;
+    const float4 me = T.pts[p];
+    Query q;
+    q.x = me.x;
+    q.y = me.y;
+    q.z = me.z;
+    q.self = __float_as_uint(me.w);
+    const bool asks = p < sc.n && me.x == me.x && me.y == me.y && me.z == me.z;
+    q.kth = asks ? INFINITY : -1.0f;
+#pragma unroll
+    for (int k = 0; k < kK; ++k) q.best[k] = word_of(INFINITY, 0xFFFFFFFFu);
+    Walk w;
+    const float x[3] = {me.x, me.y, me.z};
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        float lo = half_min(asks ? x[c] : INFINITY), hi = half_max(asks ? x[c] : -INFINITY);
+        lo = fminf(lo, __shfl_xor(lo, 32));
+        hi = fmaxf(hi, __shfl_xor(hi, 32));
+        w.qlo[c] = __uint_as_float((uint32_t)__builtin_amdgcn_readfirstlane((int)__float_as_uint(lo)));
+        w.qhi[c] = __uint_as_float((uint32_t)__builtin_amdgcn_readfirstlane((int)__float_as_uint(hi)));
+    }
+    w.own = 2 * wv;
+    w.R = INFINITY;
+    if (__ballot(asks) != 0ull) {
+        // depth first, nearest child first: key[l] holds what is left of the
+        // open node of level l (its children), first[l] its first child
+        uint32_t key[kTop + 1];
+        int first[kTop + 1], l = kTop, own = 0;
+#pragma unroll
+        for (int k = 0; k <= kTop; ++k) {
+            key[k] = 0xFFFFFFFFu;
+            first[k] = 0;
+        }
+        for (;;) {
+            int leaf;
+            if (own < 2) {
+                leaf = w.own + own++;
+            } else {
+                if (own == 2) {
+                    key[kTop] = child_words(T.box[kTop], 0, T.count[kTop], w, q, kTop == 0);
+                    ++own;
+                }
+                leaf = -1;
+                while (leaf < 0 && l <= kTop) {
+#pragma unroll
+                    for (int k = 0; k <= kTop; ++k) {
+                        if (k != l) continue;
+                        const uint32_t m = wave_min_bits(key[k]);
+                        if (m == 0xFFFFFFFFu || __uint_as_float(m & ~63u) > w.R) {
+                            l = k + 1;                    // nothing near is left here
+                            break;
+                        }
+                        if (lane == (int)(m & 63u)) key[k] = 0xFFFFFFFFu;
+                        const int c = first[k] + (int)(m & 63u);
+                        if (k == 0) {
+                            leaf = c;
+                        } else {
+                            constexpr int kDown = 0;
+                            first[k > 0 ? k - 1 : kDown] = c * kFan;
+                            key[k > 0 ? k - 1 : kDown] =
+                                child_words(T.box[k > 0 ? k - 1 : kDown], c * kFan,
+                                            min(kFan, T.count[k > 0 ? k - 1 : kDown] - c * kFan), w, q, k == 1);
+                            l = k - 1;
+                        }
+                        break;
+                    }
+                }
+                if (leaf < 0) break;
+                const NodeBox b = T.box[0][leaf];
+                const float at[3] = {q.x, q.y, q.z};
+                if (__ballot(!(box_dist(b.lo, b.hi, at, at) > q.kth)) == 0ull) continue;
+            }
+            if (search_leaf(T.pts, leaf, q)) w.R = worst_kth(q);
+        }
+    }
+    if (p >= sc.n) return;
     if (kNeighbours) {
 #pragma unroll
         for (int k = 0; k < kK; ++k) {
-            nidx[(int64_t)q * kK + k] = bi[k];
-            nd2[(int64_t)q * kK + k] = bd[k];
+            nidx[(int64_t)q.self * kK + k] = (uint32_t)__double2loint(q.best[k]);
+            nd2[(int64_t)q.self * kK + k] = __uint_as_float((uint32_t)__double2hiint(q.best[k]));
         }
         return;
     }
-    // features, assembled in registers and stored as 16 float4 (one row of
-    // 256 bytes per point)
-    const int64_t n = sc.n;
-    float f[kMlpIn];
-    f[0] = kload(sc.mean, q, sc.format, false);
-    f[1] = kload(sc.mean, n + q, sc.format, false);
-    f[2] = kload(sc.mean, 2 * n + q, sc.format, false);
-#pragma unroll
-    for (int c = 0; c < 3; ++c) f[3 + c] = kload(sc.log_scale, c * n + q, sc.format, false);
-    float qq[4], qn = 0.0f;
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-        qq[c] = kload(sc.quat, c * n + q, sc.format, true);
-        qn += qq[c] * qq[c];
-    }
-    const float qs = (qq[0] < 0.0f ? -1.0f : 1.0f) * rsqrtf(fmaxf(qn, 1e-30f));
-#pragma unroll
-    for (int c = 0; c < 4; ++c) f[6 + c] = qq[c] * qs;
-    const float al = fminf(fmaxf(me.w, 1e-6f), 1.0f - 1e-6f);
-    f[10] = logf(al / (1.0f - al));
-    const int K = (sc.sh_degree + 1) * (sc.sh_degree + 1);
-#pragma unroll
-    for (int k = 0; k < 48; ++k) f[11 + k] = k < 3 * K ? kload(sc.sh, (int64_t)k * n + q, sc.format, false) : 0.0f;
     int cnt = 0;
-    float sd = 0.0f, sa = 0.0f, ma = 0.0f;
+    float sd = 0.0f, sa = 0.0f, ma = 0.0f, last = 0.0f;
 #pragma unroll
     for (int k = 0; k < kK; ++k) {
-        if (bi[k] == 0xFFFFFFFFu) continue;
+        const uint32_t i = (uint32_t)__double2loint(q.best[k]);
+        if (i == 0xFFFFFFFFu) continue;
+        const float d2 = __uint_as_float((uint32_t)__double2hiint(q.best[k]));
+        const float al = kload(sc.opacity, i, sc.format, true);
         ++cnt;
-        sd += sqrtf(bd[k]);
-        sa += ba[k];
-        ma = fmaxf(ma, ba[k]);
+        last = d2;
+        sd += sqrtf(d2);
+        sa += al;
+        ma = fmaxf(ma, al);
     }
-    const float d16 = cnt ? sqrtf(bd[cnt - 1]) : 1.0f;
+    const float d16 = cnt ? sqrtf(last) : 1.0f;
     const float tiny = 1e-12f;
-    f[59] = logf(fmaxf(cnt ? sd / cnt : 1.0f, tiny));
-    f[60] = logf(fmaxf(d16, tiny));
-    f[61] = cnt ? sa / cnt : 0.0f;
-    f[62] = ma;
-    f[63] = logf(fmaxf(sa, tiny) / fmaxf(4.18879020f * d16 * d16 * d16, tiny));
-    float4 *row = reinterpret_cast<float4 *>(feat + (int64_t)q * kMlpIn);
+    float4 f;
+    f.x = logf(fmaxf(cnt ? sd / cnt : 1.0f, tiny));
+    f.y = logf(fmaxf(d16, tiny));
+    f.z = cnt ? sa / cnt : 0.0f;
+    f.w = ma;
+    float *row = nf + (int64_t)q.self * 8;
+    *reinterpret_cast<float4 *>(row) = f;
+    row[4] = logf(fmaxf(sa, tiny) / fmaxf(4.18879020f * d16 * d16 * d16, tiny));
+}
+
+// The feature rows, 64 points per block: the attribute planes are read in
+// index order (a wave reads 64 consecutive values of a plane), transposed in
+// LDS (65 floats per row: no bank conflicts) and stored as whole rows: 0.12 ms
+// for 10^6 points, 4.1 TB/s.  (Assembled by the search itself, at scattered
+// indices, a row takes a whole line of every plane for each 4 bytes.)
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+__global__ __launch_bounds__(256) void k_feature_rows(SceneDev sc, const float *__restrict__ nf,
+                                                      float *__restrict__ feat) {
+    constexpr int kRows = 64, kPitch = kMlpIn + 1;
+    __shared__ float sh[kRows * kPitch];
+    const int64_t n = sc.n, r0 = (int64_t)blockIdx.x * kRows;
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int64_t i = r0 + lane;
+    const bool ok = i < n;
+    float *row = sh + lane * kPitch;
+    const int K = (sc.sh_degree + 1) * (sc.sh_degree + 1);
+#pragma unroll 4
+    for (int k = w; k < 48; k += 4)
+        row[11 + k] = (ok && k < 3 * K) ? kload(sc.sh, (int64_t)k * n + i, sc.format, false) : 0.0f;
+    if (ok) {
+        if (w == 0) {
+            for (int c = 0; c < 3; ++c) row[c] = kload(sc.mean, c * n + i, sc.format, false);
+            for (int c = 0; c < 3; ++c) row[3 + c] = kload(sc.log_scale, c * n + i, sc.format, false);
+        } else if (w == 1) {
+            float qq[4], qn = 0.0f;
 #pragma unroll
-    for (int k = 0; k < kMlpIn / 4; ++k) row[k] = make_float4(f[4 * k], f[4 * k + 1], f[4 * k + 2], f[4 * k + 3]);
+            for (int c = 0; c < 4; ++c) {
+                qq[c] = kload(sc.quat, c * n + i, sc.format, true);
+                qn += qq[c] * qq[c];
+            }
+            const float qs = (qq[0] < 0.0f ? -1.0f : 1.0f) * rsqrtf(fmaxf(qn, 1e-30f));
+#pragma unroll
+            for (int c = 0; c < 4; ++c) row[6 + c] = qq[c] * qs;
+        } else if (w == 2) {
+            const float al = fminf(fmaxf(kload(sc.opacity, i, sc.format, true), 1e-6f), 1.0f - 1e-6f);
+            row[10] = logf(al / (1.0f - al));
+        } else {
+            const float4 f = *reinterpret_cast<const float4 *>(nf + i * 8);
+            row[59] = f.x;
+            row[60] = f.y;
+            row[61] = f.z;
+            row[62] = f.w;
+            row[63] = nf[i * 8 + 4];
+        }
+    }
+    __syncthreads();
+    for (int t = threadIdx.x; t < kRows * (kMlpIn / 4); t += 256) {
+        const int r = t >> 4, c = 4 * (t & 15);
+        if (r0 + r < n) {
+            const float *v = sh + r * kPitch + c;
+            const f32x4u o = {v[0], v[1], v[2], v[3]};
+            *reinterpret_cast<f32x4u *>(feat + (r0 + r) * kMlpIn + c) = o;
+        }
+    }
 }
 
 // Column means and 1/std (population) of an n x 64 float32 matrix, in FP64.
@@ -269,7 +582,6 @@ __global__ __launch_bounds__(256) void k_knn_features(SceneDev sc, Grid G, const
 // together 7.58 -> 5.39 ms).
 // (The rows are only known to be 4-byte aligned: f32x4u says so.)
 constexpr int kStatRows = 1024;
-typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 static int64_t stat_blocks(int64_t n) { return (n + kStatRows - 1) / kStatRows; }
 size_t feature_stats_scratch_bytes(int64_t n) { return sizeof(double) * 2 * kMlpIn * (size_t)stat_blocks(n) + 256; }
 
@@ -338,11 +650,38 @@ void feature_stats(const float *feat, int64_t n, float *norm, void *scratch, hip
     hipLaunchKernelGGL(k_feature_norm, dim3(kMlpIn), dim3(256), 0, st, part, nblk, n, norm);
 }
 
+// Levels of the tree over n points: leaves, then 64 nodes per node until at
+// most 64 are left.
+static int tree_levels(int64_t n, int64_t (&count)[kMaxLevels]) {
+    int top = 0;
+    count[0] = (n + kLeaf - 1) / kLeaf;
+    while (count[top] > kFan) {
+        count[top + 1] = (count[top] + kFan - 1) / kFan;
+        ++top;
+    }
+    return top;
+}
+
 size_t knn_scratch_bytes(int64_t n) {
-    // cells <= 8n; per point: cell id, order, point record; per cell: count, fill, offset
-    const size_t cells = (size_t)8 * n + 8;
-    return (size_t)n * (4 + 4 + 16) + cells * (4 + 4 + 8) + sizeof(uint64_t) * ((cells + 2047) / 2048 + 8) +
-           64 * 256;
+    int64_t count[kMaxLevels];
+    const int top = tree_levels(n, count);
+    size_t b = (size_t)4 * 4 * n + sizeof(uint32_t) * (size_t)radix_sort_scratch_words(n, 1);   // codes and values, twice
+    b += (size_t)(n + 64) * 16 + (size_t)n * 32;                                                 // points, features 59-63
+    for (int l = 0; l <= top; ++l) b += sizeof(NodeBox) * (size_t)(count[l] + 2);
+    return b + 64 * 256;
+}
+
+template <bool kNeighbours>
+static void launch_knn(int top, const SceneDev &sc, const Tree &T, float *nf, uint32_t *nidx, float *nd2,
+                       hipStream_t st) {
+    const unsigned grid = (unsigned)(((sc.n + 63) / 64 + 7) / 8 * 8);
+    auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(grid), dim3(64), 0, st, sc, T, nf, nidx, nd2); };
+    switch (top) {
+        case 0: go(k_knn<kNeighbours, 0>); break;
+        case 1: go(k_knn<kNeighbours, 1>); break;
+        case 2: go(k_knn<kNeighbours, 2>); break;
+        default: go(k_knn<kNeighbours, 3>); break;      // n < 2^28: at most 2^23 leaves
+    }
 }
 
 hipError_t knn_features(const SceneDev &sc, float *feat, void *scratch, hipStream_t st, uint32_t *nidx,
@@ -356,65 +695,42 @@ hipError_t knn_features(const SceneDev &sc, float *feat, void *scratch, hipStrea
         o += bytes;
         return r;
     };
-    uint32_t *box = (uint32_t *)take(64);
-    uint32_t init[6] = {0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0u, 0u, 0u};
-    hipError_t e = hipMemcpyAsync(box, init, sizeof init, hipMemcpyHostToDevice, st);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_bbox, dim3(kBoxBlocks), dim3(256), 0, st, sc, box);
-    uint32_t hb[6];
-    e = hipMemcpyAsync(hb, box, sizeof hb, hipMemcpyDeviceToHost, st);
-    if (e != hipSuccess) return e;
-    e = hipStreamSynchronize(st);
-    if (e != hipSuccess) return e;
-    Grid G;
-    float ext[3];
-    double vol = 1.0;
-    auto unord = [](uint32_t u) {
-        const uint32_t b = (u & 0x80000000u) ? (u & 0x7FFFFFFFu) : ~u;
-        float f;
-        memcpy(&f, &b, sizeof f);
-        return f;
-    };
-    for (int c = 0; c < 3; ++c) {
-        G.lo[c] = unord(hb[c]);
-        const float h = unord(hb[3 + c]);
-        ext[c] = std::max(h - G.lo[c], 1e-6f);
-        vol *= ext[c];
+    CloudStats *cs = (CloudStats *)take(sizeof(CloudStats));
+    uint32_t *key0 = (uint32_t *)take((size_t)n * 4), *key1 = (uint32_t *)take((size_t)n * 4);
+    uint32_t *val0 = (uint32_t *)take((size_t)n * 4), *val1 = (uint32_t *)take((size_t)n * 4);
+    uint32_t *hist = (uint32_t *)take(sizeof(uint32_t) * (size_t)radix_sort_scratch_words(n, 1));
+    const int64_t padded = (n + 63) / 64 * 64;
+    float4 *pts = (float4 *)take((size_t)padded * 16);
+    float *nf = (float *)take((size_t)n * 32);
+    int64_t count[kMaxLevels];
+    const int top = tree_levels(n, count);
+    Tree T{};
+    T.pts = pts;
+    NodeBox *box[kMaxLevels] = {};
+    for (int l = 0; l <= top; ++l) {
+        T.box[l] = box[l] = (NodeBox *)take(sizeof(NodeBox) * (size_t)(count[l] + 2));
+        T.count[l] = (int)count[l];
     }
-    // about four points per cell of the bounding box (measured on clustered
-    // scenes: one per cell scans more cells, sixteen more candidates)
-    double cell = cbrt(4.0 * vol / (double)n);
-    int64_t cells = 0;
-    for (;;) {
-        cells = 1;
-        for (int c = 0; c < 3; ++c) {
-            G.dim[c] = (int)std::min<double>(1024.0, std::max(1.0, std::ceil(ext[c] / cell)));
-            cells *= G.dim[c];
-        }
-        if (cells <= 8 * n + 8) break;
-        cell *= 1.25;
+    const unsigned per256 = (unsigned)((n + 255) / 256);
+    hipLaunchKernelGGL(k_cloud_init, dim3(1), dim3(1), 0, st, cs);
+    hipLaunchKernelGGL(k_cloud_stats, dim3(std::min(per256, (unsigned)kBoxBlocks)), dim3(256), 0, st, sc, cs);
+    hipLaunchKernelGGL(k_curve, dim3(per256), dim3(256), 0, st, sc, (const CloudStats *)cs, key0);
+    uint32_t *ko = nullptr, *sorted = nullptr;
+    const hipError_t e =
+        radix_sort_segments(key0, val0, key1, val1, hist, n, 1, true, 4, nullptr, nullptr, &ko, &sorted, st);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_leaves, dim3((unsigned)((padded + 255) / 256)), dim3(256), 0, st, sc,
+                       (const uint32_t *)sorted, padded, pts, box[0]);
+    for (int l = 1; l <= top; ++l)
+        hipLaunchKernelGGL(k_nodes, dim3((unsigned)count[l]), dim3(64), 0, st, (const NodeBox *)box[l - 1],
+                           (int)count[l - 1], box[l]);
+    if (nidx) {
+        launch_knn<true>(top, sc, T, nullptr, nidx, nd2, st);
+    } else {
+        launch_knn<false>(top, sc, T, nf, nullptr, nullptr, st);
+        hipLaunchKernelGGL(k_feature_rows, dim3((unsigned)((n + 63) / 64)), dim3(256), 0, st, sc, (const float *)nf,
+                           feat);
     }
-    G.cell = (float)cell;
-    G.inv_cell = (float)(1.0 / cell);
-    uint32_t *cell_of = (uint32_t *)take((size_t)n * 4);
-    uint32_t *order = (uint32_t *)take((size_t)n * 4);
-    float4 *pts = (float4 *)take((size_t)n * 16);
-    uint32_t *count = (uint32_t *)take((size_t)cells * 4);
-    uint32_t *fill = (uint32_t *)take((size_t)cells * 4);
-    uint64_t *offs = (uint64_t *)take((size_t)(cells + 1) * 8);
-    uint64_t *tmp = (uint64_t *)take(sizeof(uint64_t) * scan_tmp_elems(cells + 1));
-    launch_fill_u32(count, 0u, cells, st);
-    launch_fill_u32(fill, 0u, cells, st);
-    hipLaunchKernelGGL(k_cell_count, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, sc, G, cell_of, count);
-    scan_u32_to_u64_exclusive(count, offs, cells, tmp, st);
-    hipLaunchKernelGGL(k_cell_scatter, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, n, cell_of, offs, fill,
-                       order, pts, sc);
-    if (nidx)
-        hipLaunchKernelGGL(k_knn_features<true>, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, sc, G, offs,
-                           order, pts, nullptr, nidx, nd2);
-    else
-        hipLaunchKernelGGL(k_knn_features<false>, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, sc, G, offs,
-                           order, pts, feat, nullptr, nullptr);
     return hipGetLastError();
 }
 

@@ -131,9 +131,12 @@ __global__ __launch_bounds__(kSortThreads) void k_radix_scatter(const uint32_t *
     __shared__ int tick;
     // blocks go to the XCDs in turn (block i to XCD i mod 8): block i works
     // on segment 8 (i / 8 / nb) + i mod 8, so each segment's scattered lines
-    // are written through one L2; its place in the segment is its ticket
-    const int64_t bi = blockIdx.x;
-    const int seg = (int)(((bi >> 3) / nb) * 8 + (bi & 7));
+    // are written through one L2; its place in the segment is its ticket.
+    // The last n_segs mod 8 segments are shared by every XCD instead (one XCD
+    // each would leave the others idle at the end: a sort of one segment ran
+    // on an eighth of the chip).
+    const int64_t bi = blockIdx.x, whole = (int64_t)nb * (n_segs & ~7);
+    const int seg = bi < whole ? (int)(((bi >> 3) / nb) * 8 + (bi & 7)) : (n_segs & ~7) + (int)((bi - whole) / nb);
     if (seg >= n_segs) return;
     int b;
     const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -263,7 +266,7 @@ hipError_t radix_sort_segments(uint32_t *key0, uint32_t *val0, uint32_t *key1, u
         const uint32_t *kb = pass == 0 ? kbase : nullptr;
         launch_fill_u32(hist, 0u, nstatus, st);
         // the last pass writes the values only (nothing reads the sorted keys)
-        const int64_t blocks = (int64_t)nb * ((n_segs + 7) / 8) * 8;
+        const int64_t blocks = (int64_t)nb * n_segs;
         hipLaunchKernelGGL(k_radix_scatter, dim3((unsigned)blocks), dim3(kSortThreads), 0, st, ki, vi,
                            pass + 1 < passes ? ko : nullptr, vo, n_per_seg, nb, shift,
                            (pass == 0 && vals_are_iota) ? 1 : 0, kb, seg_len, hist, extra, pass, n_segs);

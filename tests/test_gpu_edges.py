@@ -29,3 +29,94 @@ def test_feature_stats_block_edges(n, offset):
     inv = torch.where(std > 1e-9, 1 / std.clamp_min(1e-30), torch.ones_like(std))
     assert torch.all((norm[0] - mean).abs() <= 2.0 ** -24 * mean.abs() + 1e-12)
     assert torch.all((norm[1] - inv).abs() <= 1.0e-7 * inv)
+
+
+def _scene(gs, mean):
+    n = mean.shape[1]
+    one = lambda *s: torch.ones(*s, device="cuda")  # noqa: E731
+    return gs.DeviceScene(mean.contiguous(), -3.0 * one(3, n), one(4, n), 0.5 * one(n), 0.1 * one(1, 3, n), 0)
+
+
+def _brute_knn(mean, k=16):
+    """The k nearest other points by float32 (dx dx + dy dy) + dz dz, ties by
+    index; a NaN distance is no neighbour."""
+    x = mean.T.contiguous()
+    n = x.shape[0]
+    none = torch.iinfo(torch.int64).max
+    idx = torch.full((n, k), -1, dtype=torch.int32, device="cuda")
+    d2 = torch.full((n, k), float("inf"), device="cuda")
+    for i in range(0, n, 2048):
+        r = x[i:i + 2048]
+        e = [x[None, :, c] - r[:, None, c] for c in range(3)]
+        d = (e[0] * e[0] + e[1] * e[1]) + e[2] * e[2]
+        key = (d.view(torch.int32).long() << 32) | torch.arange(n, device="cuda")[None]
+        key[torch.isnan(d)] = none
+        key[torch.arange(r.shape[0]), torch.arange(i, i + r.shape[0])] = none
+        best = torch.sort(key, 1).values[:, :k]
+        m = best.shape[1]
+        there = best != none
+        idx[i:i + 2048, :m] = torch.where(there, (best & 0xFFFFFFFF).int(), torch.full_like(best, -1).int())
+        d2[i:i + 2048, :m] = torch.where(there, (best >> 32).int().view(torch.float32), torch.tensor(float("inf")).cuda())
+    return idx, d2
+
+
+@pytest.mark.parametrize("kind", ["normal", "lattice", "line", "copies", "far", "nonfinite"])
+@pytest.mark.parametrize("n", [1, 2, 16, 17, 31, 33, 64, 65, 2047, 2049, 4097, 20_000])
+def test_knn_tree_edges(kind, n):
+    """Neighbour sets and squared distances, bit for bit, around the tree's
+    leaves (32 points), waves (64) and nodes (2048 points; a third level from
+    131 073 on is test_knn_three_levels), for ties, a flat cloud, coincident
+    points, far outliers and non-finite means."""
+    import paper_2607_02721_amd as gs
+    from paper_2607_02721_amd import learned
+    g = torch.Generator(device="cuda").manual_seed(n)
+    m = torch.randn(3, n, generator=g, device="cuda")
+    if kind == "lattice":
+        m = (m * 4).round() / 8
+    elif kind == "line":
+        m[1:] = 0.25
+    elif kind == "copies":
+        m = m[:, torch.randint(0, max(1, n // 20), (n,), generator=g, device="cuda")]
+    elif kind == "far":
+        m[:, :3] *= 1e6
+    elif kind == "nonfinite":
+        m[0, n // 2] = float("nan")
+        m[1, n // 3] = float("inf")
+        m[2, n // 5] = -float("inf")
+    idx, d2 = learned.knn(_scene(gs, m))
+    ri, rd = _brute_knn(m)
+    assert torch.equal(idx, ri)
+    assert torch.equal(d2, rd)
+
+
+def test_knn_three_levels():
+    import paper_2607_02721_amd as gs
+    from paper_2607_02721_amd import learned
+    g = torch.Generator(device="cuda").manual_seed(3)
+    n = 140_000
+    m = torch.randn(3, n, generator=g, device="cuda")
+    m[:, ::2] *= 0.02       # half of the cloud in a dense core
+    idx, d2 = learned.knn(_scene(gs, m))
+    rows = torch.randint(0, n, (500,), generator=g, device="cuda")
+    e = [m[c][None, :] - m[c][rows][:, None] for c in range(3)]
+    d = (e[0] * e[0] + e[1] * e[1]) + e[2] * e[2]
+    key = (d.view(torch.int32).long() << 32) | torch.arange(n, device="cuda")[None]
+    key[torch.arange(500), rows] = torch.iinfo(torch.int64).max
+    best = torch.topk(key, 16, dim=1, largest=False).values.sort(1).values
+    assert torch.equal(idx[rows], (best & 0xFFFFFFFF).int())
+    assert torch.equal(d2[rows], (best >> 32).int().view(torch.float32))
+
+
+@pytest.mark.parametrize("views", [1, 7, 8, 9, 13])
+def test_depth_sort_segment_counts(views):
+    """Sensitivities of a call whose views fill whole groups of eight sort
+    segments, leave some over, or both, against one view per chunk."""
+    import synth
+    import paper_2607_02721_amd as gs
+    sc = synth.make_cluster_scene(10_000, 5, 1)     # three sort blocks per view
+    vw = synth.make_orbit_views(views, 6, 200, 136)
+    d = gs.DeviceScene.from_scene(sc)
+    one, _ = gs.sensitivity(d, vw)
+    two, _ = gs.sensitivity(d, vw, max_views_per_chunk=1)
+    assert float(one.max()) > 0
+    assert torch.equal(one, two)
