@@ -141,6 +141,7 @@ struct ChunkPlan {
 
 struct Setup {
     int64_t N;
+    int chunk_bits = kChunkBitsMax;   // log2 of the depth positions per binning chunk
     int nchunks;
     int agg = GS_AGG_RAY;       // query granularity of the sensitivity pass
     int nq = 1;                 // queries per ray (3 for per-channel queries)
@@ -150,6 +151,14 @@ struct Setup {
     std::vector<int> tiles_x, tiles_y;
     std::vector<int64_t> ray_base;
 };
+
+// The binning chunks of a call or plan scene, from its N and checked views.
+void setup_chunks(Setup &S) {
+    int64_t rows = 0;
+    for (int ty : S.tiles_y) rows += ty;
+    S.chunk_bits = chunk_bits_for(S.N, rows);
+    S.nchunks = chunk_count(S.N, S.chunk_bits);
+}
 
 // Compaction ranges are cut at every ceil(tiles / kRangeSamples)-th tile.
 constexpr int64_t kRangeSamples = 4096;
@@ -174,7 +183,7 @@ size_t chunk_scratch_bytes(const Setup &S, const ChunkPlan &c) {
     add(4 * sizeof(uint32_t) * (size_t)c.vc);
     add(4 * sizeof(uint32_t) * (size_t)c.vc * proj_blocks(N));
     add(sizeof(uint32_t) * nbins);
-    add(sizeof(uint64_t) * (size_t)rowbits_words(c.vc, chunk_max_rows(S, c), S.nchunks));
+    add(sizeof(uint64_t) * (size_t)rowbits_words(c.vc, chunk_max_rows(S, c), S.nchunks, S.chunk_bits));
     add(sizeof(uint32_t) * c.total_tiles);
     add(sizeof(uint64_t) * (c.total_tiles + 1));
     add(sizeof(uint64_t) * scan_tmp_elems(c.total_tiles + 1));
@@ -480,7 +489,8 @@ gs_status run_front(const gs_scene *scene, const gs_views *views, const gs_param
     b.proj_part = cv.take<uint32_t>(4 * (size_t)c.vc * proj_blocks(N));
     b.bin_count = cv.take<uint32_t>(nbins);
     b.rows_stride = chunk_max_rows(S, c);
-    b.rowbits = cv.take<uint64_t>((size_t)rowbits_words(c.vc, b.rows_stride, S.nchunks));
+    b.chunk_bits = S.chunk_bits;
+    b.rowbits = cv.take<uint64_t>((size_t)rowbits_words(c.vc, b.rows_stride, S.nchunks, S.chunk_bits));
     b.tile_tot = cv.take<uint32_t>(c.total_tiles);
     b.tile_off = cv.take<uint64_t>(c.total_tiles + 1);
     r.scan_tmp = cv.take<uint64_t>(scan_tmp_elems(c.total_tiles + 1));
@@ -855,7 +865,7 @@ gs_status gs_sensitivity(const gs_scene *scene, const gs_views *views, const gs_
     HIP_TRY(order_after_previous(dev, st));
     DoneGuard done_guard{dev, st};
     S.N = scene->n;
-    S.nchunks = (int)((S.N + (1 << kChunkBits) - 1) >> kChunkBits);
+    setup_chunks(S);
     S.agg = params->aggregate;
     S.nq = params->query_mode == GS_QUERY_CHANNEL ? 3 : 1;
     // every granularity composites on compacted lists (per-tile queries keep
@@ -889,7 +899,7 @@ gs_status gs_sensitivity(const gs_scene *scene, const gs_views *views, const gs_
             GS_OK)
             return s;
         entries += r.n_entries;
-        n_bins += (int64_t)c.total_tiles * S.nchunks;
+        n_bins += (int64_t)c.total_tiles * chunk_count(S.N, kChunkBitsMax);
         sort_passes = std::max(sort_passes, r.passes);
         CompositeArgs a = composite_args(r, c.total_tiles, params, params->share_floor, S);
         a.ccount = r.host_slot.clist ? r.ccount : nullptr;
@@ -1045,7 +1055,7 @@ gs_status gs_render_objective(const gs_scene *scene, const gs_views *views, cons
     HIP_TRY(order_after_previous(dev, st));
     DoneGuard done_guard{dev, st};
     S.N = scene->n;
-    S.nchunks = (int)((S.N + (1 << kChunkBits) - 1) >> kChunkBits);
+    setup_chunks(S);
     const auto chunks = plan_chunks(views, S, params, scratch_budget());
     Timer tm(false);
     double ms[6] = {0, 0, 0, 0, 0, 0};
@@ -1595,7 +1605,7 @@ size_t scene_buffer_bytes(const PlanScene &ps) {
     add(4 * sizeof(uint32_t) * (size_t)ps.c.vc);
     add(4 * sizeof(uint32_t) * (size_t)ps.c.vc * proj_blocks(N));
     add(sizeof(uint32_t) * ps.nbins);
-    add(sizeof(uint64_t) * (size_t)rowbits_words(ps.c.vc, chunk_max_rows(ps.S, ps.c), ps.S.nchunks));
+    add(sizeof(uint64_t) * (size_t)rowbits_words(ps.c.vc, chunk_max_rows(ps.S, ps.c), ps.S.nchunks, ps.S.chunk_bits));
     add(sizeof(uint32_t) * ps.c.total_tiles);
     add(sizeof(uint64_t) * (ps.c.total_tiles + 1));
     add(sizeof(uint64_t) * scan_tmp_elems(ps.c.total_tiles + 1));
@@ -1622,7 +1632,8 @@ void carve_scene(PlanScene &ps, Carve &cv) {
     b.proj_part = cv.take<uint32_t>(4 * (size_t)ps.c.vc * proj_blocks(N));
     b.bin_count = cv.take<uint32_t>(ps.nbins);
     b.rows_stride = chunk_max_rows(ps.S, ps.c);
-    b.rowbits = cv.take<uint64_t>((size_t)rowbits_words(ps.c.vc, b.rows_stride, ps.S.nchunks));
+    b.chunk_bits = ps.S.chunk_bits;
+    b.rowbits = cv.take<uint64_t>((size_t)rowbits_words(ps.c.vc, b.rows_stride, ps.S.nchunks, ps.S.chunk_bits));
     b.tile_tot = cv.take<uint32_t>(ps.c.total_tiles);
     b.tile_off = cv.take<uint64_t>(ps.c.total_tiles + 1);
     ps.scan_tmp = cv.take<uint64_t>(scan_tmp_elems(ps.c.total_tiles + 1));
@@ -1919,7 +1930,7 @@ gs_status gs_plan_create(const gs_scene *scenes, const gs_views *views, int32_t 
         }
         ps.sc = scenes[i];
         ps.S.N = scenes[i].n;
-        ps.S.nchunks = (int)((ps.S.N + (1 << kChunkBits) - 1) >> kChunkBits);
+        setup_chunks(ps.S);
         ps.c = ChunkPlan{0, views[i].n_views, ps.S.ray_base[views[i].n_views], 0};
         for (int v = 0; v < views[i].n_views; ++v) ps.c.total_tiles += ps.S.tiles_x[v] * ps.S.tiles_y[v];
         if (views[i].n_views > 65535) {

@@ -4,7 +4,7 @@
 // radix-sorted (depth key, index) sequence; ties by index because the sort is
 // stable and starts from index order).  A list entry is keyed by (tile, p)
 // and the lists are built by a counting sort on that key:
-//   1. count: one block per chunk of 2^14 consecutive positions counts its
+//   1. count: one block per chunk of 2^10 to 2^14 consecutive positions counts its
 //             entries per tile in LDS and stores them, one row per chunk;
 //   2. scan:  per tile, the exclusive prefix over chunks (in place) and the
 //             tile's total; a scan of the totals gives each tile's list start,
@@ -27,13 +27,10 @@
 namespace gs {
 
 constexpr int kBinThreads = 256;
-constexpr int kCountGroup = 32;        // chunks per XCD run (multiples of the 16 counts in a 64-byte line)
+constexpr int kCountGroup = 32;        // most chunks per XCD run (multiples of the 16 counts in a 64-byte line)
 constexpr int kEmitGroupChunks = 4;    // chunks (times the row groups) per XCD run
-constexpr int kSegBits = kChunkBits;
-constexpr int kSegSize = 1 << kSegBits;          // positions per chunk
 
-static_assert(kSegSize == kBinPositions, "one binning block per chunk");
-static_assert(kBinPositions <= 65536, "queued positions are 16-bit chunk offsets");
+static_assert(kChunkBitsMax <= 16, "queued positions are 16-bit chunk offsets");
 
 __device__ __forceinline__ void unpack_range(float f, int &lo, int &hi) {
     const uint32_t u = __float_as_uint(f);
@@ -70,31 +67,32 @@ __global__ __launch_bounds__(kBinThreads) void k_bin_count(const ViewDev *__rest
                                                            const uint32_t *__restrict__ yr_in,
                                                            uint32_t *__restrict__ bin_count,
                                                            const uint16_t *__restrict__ active,
-                                                           uint64_t *__restrict__ rowbits, int rows_stride) {
+                                                           uint64_t *__restrict__ rowbits, int rows_stride,
+                                                           int chunk_bits, int xcd_group) {
     // A position adds 1 to every tile of its tile rectangle: +1 / -1 at the
     // rectangle's corners of a 2D difference array, whose prefix sums along
     // x and then y are the counts (four LDS atomics per position, whatever
     // its size).
     extern __shared__ int32_t dif[];                  // [tiles_y + 1][tiles_x + 1]
     __shared__ uint64_t rowword[kBinThreads / 64][128];   // per wave: row words on their way to the lanes
-    const int64_t lb = xcd_block(blockIdx.x, kCountGroup);   // logical block: chunk + nchunks * view
+    const int64_t lb = xcd_block(blockIdx.x, xcd_group);   // logical block: chunk + nchunks * view
     const int v = (int)(lb / nchunks);
     if (v >= n_views) return;
     const ViewDev &V = views[v];
     const int64_t nv = nvis[v];
-    const int64_t lo = (lb - (int64_t)v * nchunks) * kBinPositions;
+    const int chunk = (int)(lb - (int64_t)v * nchunks);
+    const int64_t lo = (int64_t)chunk << chunk_bits;
     if (lo >= nv) return;
-    const int64_t hi = min(lo + (int64_t)kBinPositions, nv);
-    const int chunk = (int)(lo >> kSegBits);
+    const int64_t hi = min(lo + (1ll << chunk_bits), nv);
     const int tx_n = V.tiles_x, ty_n = V.tiles_y, ntiles = tx_n * ty_n;
     const int stride = tx_n + 1, cells = stride * (ty_n + 1);
     for (int i = threadIdx.x; i < cells; i += kBinThreads) dif[i] = 0;
     __syncthreads();
     // the view's row bitmaps for this chunk: word w of row r at
     // rb + r * row_pitch + w
-    constexpr int kWords = kBinPositions / 64;
-    const int64_t row_pitch = (int64_t)nchunks * kWords;
-    uint64_t *rb = rowbits + (int64_t)v * rows_stride * row_pitch + (int64_t)chunk * kWords;
+    const int words = 1 << (chunk_bits - 6);
+    const int64_t row_pitch = (int64_t)nchunks * words;
+    uint64_t *rb = rowbits + (int64_t)v * rows_stride * row_pitch + (int64_t)chunk * words;
     // every lane of a wave runs each step (positions past the chunk's end
     // are invalid), so the row words gathered into the lanes can be stored
     // by the whole wave
@@ -300,17 +298,17 @@ struct EmitLds {
     int32_t *head;      // [64] lane owning the item that starts a run
     uint32_t *rx, *ry, *rg;   // [64] the round's pixel ranges and indices
     uint32_t *ft, *fc;  // [64] lines to store: tile, and the entry in its last slot
-    uint16_t *queue;    // [kEmitBatch] chunk-local positions meeting the rows
+    uint16_t *queue;    // [batch] chunk-local positions meeting the rows
     uint32_t *act;      // [tiles / 32] (masked form only)
 };
 
-__host__ __device__ constexpr size_t emit_lds_bytes(int tiles, bool masked, int line_log) {
-    return sizeof(uint32_t) * ((size_t)tiles * ((1 << line_log) + 4) + 6 * kEmitWave) + sizeof(uint16_t) * kEmitBatch +
+__host__ __device__ constexpr size_t emit_lds_bytes(int tiles, bool masked, int line_log, int batch) {
+    return sizeof(uint32_t) * ((size_t)tiles * ((1 << line_log) + 4) + 6 * kEmitWave) + sizeof(uint16_t) * batch +
            (masked ? sizeof(uint32_t) * (((size_t)tiles + 31) / 32) : 0);
 }
 
 template <int kLine>
-__device__ __forceinline__ EmitLds emit_lds(uint32_t *base, int tiles) {
+__device__ __forceinline__ EmitLds emit_lds(uint32_t *base, int tiles, int batch) {
     EmitLds L;
     L.lanes = (uint64_t *)base;
     L.line = base + 2 * (size_t)tiles;
@@ -323,7 +321,7 @@ __device__ __forceinline__ EmitLds emit_lds(uint32_t *base, int tiles) {
     L.ft = L.rg + kEmitWave;
     L.fc = L.ft + kEmitWave;
     L.queue = (uint16_t *)(L.fc + kEmitWave);
-    L.act = (uint32_t *)(L.queue + kEmitBatch);
+    L.act = (uint32_t *)(L.queue + batch);
     return L;
 }
 
@@ -358,10 +356,10 @@ __global__ __launch_bounds__(kEmitWave) void k_bin_emit(const ViewDev *__restric
                                                         uint32_t *__restrict__ lists,
                                                         const uint16_t *__restrict__ active, uint64_t cap,
                                                         int group_tiles, const uint64_t *__restrict__ rowbits,
-                                                        int rows_stride) {
+                                                        int rows_stride, int chunk_bits, int batch) {
     extern __shared__ uint32_t lds[];
     constexpr int kLine = 1 << kLineLog;
-    const EmitLds L = emit_lds<kLine>(lds, group_tiles);
+    const EmitLds L = emit_lds<kLine>(lds, group_tiles, batch);
     // logical block: group + groups * (chunk + nchunks * view), with group =
     // row group + row_groups * column group
     const int groups = row_groups * col_groups;
@@ -375,12 +373,12 @@ __global__ __launch_bounds__(kEmitWave) void k_bin_emit(const ViewDev *__restric
     const ViewDev &V = views[v];
     const int sx = V.tsx, sy = V.tsy;
     const int64_t nv = nvis[v];
-    const int64_t lo = (int64_t)chunk * kBinPositions;
+    const int64_t lo = (int64_t)chunk << chunk_bits;
     const int r0 = (grp % row_groups) * kEmitRows, c0 = (grp / row_groups) * kEmitCols;
     if (lo >= nv || r0 >= V.tiles_y || c0 >= V.tiles_x) return;
     const int r1 = min(r0 + kEmitRows, V.tiles_y);    // rows [r0, r1)
     const int c1 = min(c0 + kEmitCols, V.tiles_x);    // columns [c0, c1)
-    const int hi = (int)(min(lo + (int64_t)kBinPositions, nv) - lo);
+    const int hi = (int)(min(lo + (1ll << chunk_bits), nv) - lo);
     const int tiles_x = V.tiles_x, ncols = c1 - c0;
     const int ntiles = (r1 - r0) * ncols;             // local tile (ty - r0) * ncols + (tx - c0)
     const uint64_t vlist = tile_off[V.tile_base];
@@ -422,12 +420,12 @@ __global__ __launch_bounds__(kEmitWave) void k_bin_emit(const ViewDev *__restric
     const int64_t o = (int64_t)v * N + lo;
     // this wave's row bitmap in the chunk (one word per 64 positions)
     static_assert(kEmitRows == 1, "the row bitmaps select one tile row");
-    constexpr int kWords = kBinPositions / 64;
+    const int words = 1 << (chunk_bits - 6);
     const uint64_t *rbits =
-        rowbits + ((int64_t)v * rows_stride + r0) * ((int64_t)nchunks * kWords) + (int64_t)chunk * kWords;
+        rowbits + ((int64_t)v * rows_stride + r0) * ((int64_t)nchunks * words) + (int64_t)chunk * words;
     static_assert(kEmitBatch % 64 == 0 && kEmitBatch <= 64 * kEmitWave, "one row-bitmap word per lane");
-    for (int b0 = 0; b0 < hi; b0 += kEmitBatch) {
-        const int b1 = min(b0 + kEmitBatch, hi);
+    for (int b0 = 0; b0 < hi; b0 += batch) {
+        const int b1 = min(b0 + batch, hi);
         // 1. positions of the batch that meet row r0, in order: lane l < 16
         // takes the bitmap word of positions b0 + 64 l ... + 63 (bits past the
         // chunk's visible positions are clear), a wave prefix sum of the
@@ -587,8 +585,12 @@ __global__ __launch_bounds__(kEmitWave) void k_bin_emit(const ViewDev *__restric
 
 void launch_bin_count(const ViewDev *views_dev, int Vc, int64_t N, int nchunks, const ChunkBufs &b,
                       const uint32_t *xr, const uint32_t *yr, int max_cells, hipStream_t st) {
-    const int64_t run = 8 * kCountGroup;
-    const int64_t blocks = ((int64_t)nchunks * Vc + run - 1) / run * run;
+    // runs of neighbouring chunks per XCD, short enough that every XCD gets one
+    // (runs of 32 left 96 blocks to three of the eight XCDs)
+    const int64_t all = (int64_t)nchunks * Vc;
+    const int group = (int)std::min<int64_t>(kCountGroup, std::max<int64_t>(1, all / 8));
+    const int64_t run = 8 * (int64_t)group;
+    const int64_t blocks = (all + run - 1) / run * run;
     static const bool lds_ok = [] {
         // views up to kMaxCellsPerView cells take more than 64 KiB of LDS
         const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_bin_count),
@@ -600,7 +602,7 @@ void launch_bin_count(const ViewDev *views_dev, int Vc, int64_t N, int nchunks, 
     (void)lds_ok;
     hipLaunchKernelGGL(k_bin_count, dim3((unsigned)blocks), dim3(kBinThreads), (size_t)max_cells * sizeof(int32_t),
                        st, views_dev, Vc, N, nchunks, b.nvis, xr, yr, b.bin_count, b.tile_active, b.rowbits,
-                       b.rows_stride);
+                       b.rows_stride, b.chunk_bits, group);
 }
 
 void launch_chunk_prefix(const ViewDev *views_dev, int Vc, int nchunks, const ChunkBufs &b, int max_tiles,
@@ -618,12 +620,13 @@ void launch_bin_emit(const ViewDev *views_dev, int Vc, int64_t N, int nchunks, c
     const int64_t blocks = ((int64_t)row_groups * col_groups * nchunks * Vc + run - 1) / run * run;
     const int group_tiles = kEmitRows * std::min(max_tiles_x, kEmitCols);
     const int line_log = tile_shift_x >= 5 ? 4 : 3;
-    const size_t lds = emit_lds_bytes(group_tiles, b.tile_active != nullptr, line_log);
+    const int batch = std::min(kEmitBatch, 1 << b.chunk_bits);
+    const size_t lds = emit_lds_bytes(group_tiles, b.tile_active != nullptr, line_log, batch);
     const dim3 grid((unsigned)blocks);
     auto go = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, grid, dim3(kEmitWave), lds, st, views_dev, Vc, N, nchunks, row_groups, col_groups,
                            b.nvis, xr, yr, sorted_g, b.bin_count, b.tile_off, b.lists, b.tile_active, cap,
-                           group_tiles, b.rowbits, b.rows_stride);
+                           group_tiles, b.rowbits, b.rows_stride, b.chunk_bits, batch);
     };
     if (b.tile_active)
         line_log == 4 ? go(k_bin_emit<true, 4>) : go(k_bin_emit<true, 3>);

@@ -11,13 +11,14 @@ namespace gs {
 // or 32); 16 x 16 unless the caller or the tuner picks another shape.
 constexpr int kTileShiftDefault = 4;
 constexpr int kQuad = 8;           // compositing quadrant edge: one wave per 8x8 quadrant
-constexpr int kChunkBits = 14;     // depth ranks are binned in chunks of 2^14 (one list segment per tile)
+// Depth positions are binned in chunks of 2^bits (one list segment per tile
+// and chunk), 10 <= bits <= 14: see chunk_bits_for.
+constexpr int kChunkBitsMin = 10, kChunkBitsMax = 14;
 // The counting kernel keeps a view's 2D difference array of
 // (tiles_x + 1)(tiles_y + 1) int32 cells in LDS beside its 4 KiB of row
 // words: 38 912 cells (152 KiB) fit the 160 KiB a workgroup may take on CDNA4.
 constexpr int kMaxCellsPerView = 38912;
 constexpr int kSortTile = 4096;    // radix sort: keys per block (4 waves x 16 rounds x 64 lanes)
-constexpr int kBinPositions = 1 << kChunkBits;  // binning: depth-sorted positions per chunk (count block)
 constexpr int kEmitBatch = 2048;   // emission: positions a wave queues at a time (2048 measured best of 512-4096)
 constexpr uint32_t kInvisibleKey = 0xFFFFFFFFu;
 constexpr uint32_t kIndexMask = 0x0FFFFFFFu; // list entry = gaussian | quadrant mask << 28
@@ -99,9 +100,11 @@ struct ChunkBufs {
     // each tile's exclusive prefix over chunks
     uint32_t *bin_count;
     // Per (view, tile row, chunk): bit i of word w is set when depth position
-    // chunk * 2^14 + 64 w + i meets the tile row ([Vc][rows_stride][nchunks][256]
-    // u64, written by the counting kernel, read by the emission).
+    // chunk * 2^chunk_bits + 64 w + i meets the tile row ([Vc][rows_stride]
+    // [nchunks][2^chunk_bits / 64] u64, written by the counting kernel, read by
+    // the emission).
     uint64_t *rowbits;
+    int32_t chunk_bits;  // log2 of the depth positions per chunk
     int32_t rows_stride; // largest tile-row count of the chunk's views
     uint32_t *tile_tot;  // [tiles in chunk] entries per tile
     uint64_t *tile_off;  // exclusive scan of tile_tot (+1 trailing total): the tile's list
@@ -184,9 +187,26 @@ void launch_quad_list(const uint16_t *active, int total_tiles, int quad_log, uin
 // column).  max_tx / max_ty: the largest tile grid of the chunk's views.
 void launch_tile_sat(const ViewDev *views_dev, int Vc, int max_tx, int max_ty, const uint16_t *active, uint32_t *sat,
                      hipStream_t st);
+inline int chunk_count(int64_t n, int chunk_bits) { return (int)((n + (1ll << chunk_bits) - 1) >> chunk_bits); }
+// Chunk length for n Gaussians over `rows` tile rows (of all views).  The
+// counting kernel runs a block per (view, chunk) and the emission a wave per
+// (tile row, chunk), whose work follows how many Gaussians a row meets: long
+// chunks keep a tile's list segments at whole lines, short ones give the chip
+// enough waves, and even ones.  The largest length that leaves kEmitWaves waves
+// or more.  Calls with 2^14 always and with this rule: 50k Gaussians x 24 views
+// at 640x360 1396 -> 1150 us, 437k x 13 at 1237x823 2999 -> 2601 us; 1M x 100
+// views at 1280x720 has 142 600 waves at 2^14 and keeps it.  With 16 384 as the
+// bound the second took 3250 us where 65 536 gave 2860, and twice as many or
+// more measured the same within 3%.
+constexpr int64_t kEmitWaves = 65536;
+inline int chunk_bits_for(int64_t n, int64_t rows) {
+    int bits = kChunkBitsMax;
+    while (bits > kChunkBitsMin && rows * chunk_count(n, bits) < kEmitWaves) --bits;
+    return bits;
+}
 // u64 words of the row bitmaps of Vc views with at most max_ty tile rows.
-inline int64_t rowbits_words(int Vc, int max_ty, int nchunks) {
-    return (int64_t)Vc * max_ty * nchunks * (kBinPositions / 64);
+inline int64_t rowbits_words(int Vc, int max_ty, int nchunks, int chunk_bits) {
+    return ((int64_t)Vc * max_ty * nchunks << chunk_bits) / 64;
 }
 // max_cells: the largest (tiles_x + 1) (tiles_y + 1) of the views.
 void launch_bin_count(const ViewDev *views_dev, int Vc, int64_t N, int nchunks, const ChunkBufs &b,

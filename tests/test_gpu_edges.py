@@ -120,3 +120,23 @@ def test_depth_sort_segment_counts(views):
     two, _ = gs.sensitivity(d, vw, max_views_per_chunk=1)
     assert float(one.max()) > 0
     assert torch.equal(one, two)
+
+
+@pytest.mark.parametrize("n", [1023, 1025, 30_000, 60_000])
+@pytest.mark.parametrize("tile", [(16, 16), (32, 32), (8, 8)])
+def test_binning_chunk_lengths(n, tile):
+    """The binning chunk follows the waves a call has: 200 views in one call
+    take longer chunks than single views (2^11 against 2^10 positions at
+    60 000 Gaussians and 8-pixel rows).  The lists, and so the sensitivities,
+    do not depend on it: one call of all views is the maximum of their own."""
+    import synth
+    import paper_2607_02721_amd as gs
+    sc = synth.make_cluster_scene(n, 8, 0)
+    vw = synth.make_orbit_views(200, 9, 64, 136)
+    d = gs.DeviceScene.from_scene(sc)
+    every, _ = gs.sensitivity(d, vw, tile=tile)
+    each = torch.zeros_like(every)
+    for v in range(200):
+        each = torch.maximum(each, gs.sensitivity(d, vw.subset([v]), tile=tile)[0])
+    assert float(every.max()) > 0
+    assert torch.equal(every, each)
