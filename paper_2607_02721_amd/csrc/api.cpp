@@ -201,6 +201,7 @@ size_t chunk_scratch_bytes(const Setup &S, const ChunkPlan &c) {
     add(sizeof(uint64_t) * (kRangeSamples + 2));            // sampled tile offsets (compaction ranges)
     add(sizeof(int32_t) * c.total_tiles);                   // tile -> scene slot
     add(sizeof(SceneSlot) + 256);                           // slot + work counter
+    add(sizeof(int32_t) * (size_t)c.total_tiles + 2 * kOrderClasses * sizeof(uint32_t));   // tile order
     add(sizeof(double) * ((N + 4095) / 4096 + 2));
     add(sizeof(double) * 3 * quads);                        // objective partials
     add(sizeof(double) * (3 * (size_t)c.vc + 1));
@@ -439,6 +440,8 @@ struct ChunkRun {
     SceneSlot *slot_dev = nullptr;
     int32_t *tile_scene = nullptr;
     uint32_t *work = nullptr;
+    int32_t *tile_order = nullptr;
+    uint32_t *order_classes = nullptr;
     ViewDev *views_dev = nullptr;
     int32_t *tile_view = nullptr;
     uint32_t *sorted_g = nullptr;
@@ -515,6 +518,8 @@ gs_status run_front(const gs_scene *scene, const gs_views *views, const gs_param
     r.tile_scene = cv.take<int32_t>(c.total_tiles);
     r.slot_dev = cv.take<SceneSlot>(1);
     r.work = cv.take<uint32_t>(64);
+    r.tile_order = cv.take<int32_t>(c.total_tiles);
+    r.order_classes = cv.take<uint32_t>(2 * kOrderClasses);
     r.sum_tmp = cv.take<double>((N + 4095) / 4096 + 2);
     r.tile_sums = cv.take<double>(3 * ((size_t)c.total_tiles << S.quad_log));
     r.view_sums = cv.take<double>(3 * (size_t)c.vc + 1);
@@ -962,6 +967,10 @@ gs_status gs_sensitivity(const gs_scene *scene, const gs_views *views, const gs_
             continue;
         }
         tm.mark(3, st);
+        if (!a.quad_list && order_pays((int64_t)a.total_tiles << a.region_log)) {
+            launch_tile_order(a, r.tile_order, r.order_classes, st);
+            a.tile_order = r.tile_order;
+        }
         launch_composite_pass1(a, st);
         HIP_TRY(hipGetLastError());
         tm.mark(4, st);
@@ -1563,6 +1572,8 @@ struct PlanGroup {
     int32_t *tile_view = nullptr, *tile_scene = nullptr;
     SceneSlot *slots = nullptr;
     uint32_t *work = nullptr;
+    int32_t *tile_order = nullptr;
+    uint32_t *order_classes = nullptr;
     uint32_t *ccount = nullptr;   // [total_tiles << quad_log] entries pass 1 compacted per quadrant
     std::vector<CompositeBatch> batches;
     int total_tiles = 0, total_views = 0;
@@ -1697,6 +1708,10 @@ void enqueue_plan(gs_plan *P, hipStream_t st, float *const *sens) {
             a.region_log = P->region_log;
             a.ccount = cb.compact ? G.ccount + ((size_t)cb.t0 << P->quad_log) : nullptr;
             a.report_floor = P->p.share_floor > 0.0f ? std::nextafter(P->p.share_floor, 0.0f) : 0.0f;
+            if (!a.work && order_pays((int64_t)a.total_tiles << a.region_log)) {
+                launch_tile_order(a, G.tile_order, G.order_classes, st);
+                a.tile_order = G.tile_order;
+            }
             launch_composite_pass1(a, st);
             launch_composite_pass2(a, false, nullptr, st);
         }
@@ -1804,7 +1819,7 @@ gs_status plan_allocate(gs_plan *P, hipStream_t st) {
             G.total_views += ps.c.vc;
             G.total_tiles += ps.c.total_tiles;
         }
-        const size_t table_bytes = sizeof(ViewDev) * G.total_views + 2 * sizeof(int32_t) * G.total_tiles +
+        const size_t table_bytes = sizeof(ViewDev) * G.total_views + 3 * sizeof(int32_t) * G.total_tiles +
                                    (sizeof(uint32_t) << P->quad_log) * G.total_tiles + sizeof(SceneSlot) * G.scenes.size() +
                                    8192;
         if (dev_alloc(P->from, &G.buf, G.bytes + table_bytes + 65536, nullptr) != hipSuccess) {
@@ -1818,6 +1833,8 @@ gs_status plan_allocate(gs_plan *P, hipStream_t st) {
         G.tile_scene = cv.take<int32_t>(G.total_tiles);
         G.slots = cv.take<SceneSlot>(G.scenes.size());
         G.work = cv.take<uint32_t>(64);
+        G.tile_order = cv.take<int32_t>(G.total_tiles);
+        G.order_classes = cv.take<uint32_t>(2 * kOrderClasses);
         G.ccount = cv.take<uint32_t>((size_t)G.total_tiles << P->quad_log);
         auto &gv = group_views[gi];
         auto &gtv = group_tv[gi];

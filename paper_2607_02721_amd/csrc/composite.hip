@@ -463,6 +463,27 @@ __device__ __forceinline__ bool setup_region(const CompositeArgs &a, int logical
     return r.valid != 0u;
 }
 
+// The region this block composites, or a number past the launch's regions.
+// With a tile order the longest lists start first: a wave's time follows its
+// list, and a launch in tile order, its dense tiles anywhere, ended in a tail
+// (437k Gaussians x 13 views: the two passes 954 + 934 us in tile order, 688 +
+// 699 so; 1M x 100 views, whose tail is short, 0 to 1%).  The order is dealt
+// over the XCDs in runs of kOrderRun tiles, which are mostly neighbours and
+// gather the same records (runs of 1 lost 2% at 1M x 100 views on some scenes,
+// 4 to 64 measured alike), and a tile's regions stay on its XCD.
+constexpr int kOrderRun = 16;
+__device__ __forceinline__ int region_of_block(const CompositeArgs &a) {
+    const int nreg = a.total_tiles << a.region_log;
+    const int b = (int)blockIdx.x;
+    if (a.tile_order) {
+        const int slot = b >> 3, k = slot >> a.region_log;
+        const int t = ((k / kOrderRun) * 8 + (b & 7)) * kOrderRun + k % kOrderRun;
+        if (t >= a.total_tiles) return nreg;
+        return (a.tile_order[t] << a.region_log) + (slot & ((1 << a.region_log) - 1));
+    }
+    return a.xcd_remap ? xcd_remap(b, (nreg + 7) & ~7) : b;
+}
+
 // Pass 1 over regions of up to 2 x 2 quadrants (one wave per region, region
 // r of a tile covering quadrant columns 2 rx + kx and rows 2 ry + ky, k =
 // kx + 2 ky): the wave reads the tile list once for its quadrants, gathers
@@ -487,7 +508,7 @@ __global__ __launch_bounds__(kWave) void k_pass1_region(CompositeArgs a) {
     __shared__ RegionRec rec[kWave];
     const int lane = threadIdx.x;
     const int nreg = a.total_tiles << a.region_log;
-    const int logical = a.xcd_remap ? xcd_remap(blockIdx.x, (nreg + 7) & ~7) : (int)blockIdx.x;
+    const int logical = region_of_block(a);
     if (logical >= nreg) return;
     RegionSetup R;
     if (!setup_region(a, logical, R)) return;
@@ -918,7 +939,7 @@ __global__ __launch_bounds__(kWave, kStats ? 5 : 7) void k_pass2_region(Composit
     __shared__ RegionRec rec[kWave];
     const int lane = threadIdx.x;
     const int nreg = a.total_tiles << a.region_log;
-    const int logical = a.xcd_remap ? xcd_remap(blockIdx.x, (nreg + 7) & ~7) : (int)blockIdx.x;
+    const int logical = region_of_block(a);
     if (logical >= nreg) return;
     RegionSetup R;
     if (!setup_region(a, logical, R)) return;
@@ -1204,6 +1225,71 @@ static unsigned resident_waves(K kernel) {
     return (unsigned)std::max(1, cus) * (unsigned)std::max(1, per_cu);
 }
 
+static inline unsigned region_grid(const CompositeArgs &a) {
+    return a.tile_order ? (unsigned)((a.total_tiles + 8 * kOrderRun - 1) / (8 * kOrderRun) * (8 * kOrderRun) << a.region_log)
+                        : (unsigned)(((a.total_tiles << a.region_log) + 7) & ~7);
+}
+
+// Half-octave class of a tile's list length, the longest lists in class 0.
+__device__ __forceinline__ int length_class(const CompositeArgs &a, int t) {
+    const int gt = a.tile_first + t;
+    const SceneSlot &S = a.slots[a.tile_scene[gt]];
+    const uint64_t len = S.tile_off[gt - S.tile0 + 1] - S.tile_off[gt - S.tile0];
+    if (len == 0) return kOrderClasses - 1;
+    const int half = (int)(__float_as_uint((float)len) >> 22) - 2 * 127;      // 2 log2(len), rounded down
+    return max(0, kOrderClasses - 2 - half);
+}
+
+constexpr int kOrderThreads = 256, kOrderTiles = 4;     // tiles per block: 1024
+__global__ __launch_bounds__(kOrderThreads) void k_tile_classes(CompositeArgs a, uint32_t *__restrict__ classes) {
+    __shared__ uint32_t cnt[kOrderClasses];
+    if (threadIdx.x < kOrderClasses) cnt[threadIdx.x] = 0u;
+    __syncthreads();
+    for (int k = 0; k < kOrderTiles; ++k) {
+        const int t = ((int)blockIdx.x * kOrderTiles + k) * kOrderThreads + (int)threadIdx.x;
+        if (t < a.total_tiles) atomicAdd(&cnt[length_class(a, t)], 1u);
+    }
+    __syncthreads();
+    if (threadIdx.x < kOrderClasses && cnt[threadIdx.x]) atomicAdd(&classes[threadIdx.x], cnt[threadIdx.x]);
+}
+
+// classes: the totals, then a cursor per class.  A block takes a run of each
+// class for its tiles.  (The order inside a class is open: it changes when a
+// tile is composited, never what.)
+__global__ __launch_bounds__(kOrderThreads) void k_tile_order(CompositeArgs a, uint32_t *__restrict__ classes,
+                                                              int32_t *__restrict__ order) {
+    __shared__ uint32_t cnt[kOrderClasses], base[kOrderClasses];
+    const int tid = (int)threadIdx.x;
+    if (tid < kOrderClasses) cnt[tid] = 0u;
+    __syncthreads();
+    int cls[kOrderTiles];
+    uint32_t rank[kOrderTiles];
+    for (int k = 0; k < kOrderTiles; ++k) {
+        const int t = ((int)blockIdx.x * kOrderTiles + k) * kOrderThreads + tid;
+        cls[k] = t < a.total_tiles ? length_class(a, t) : -1;
+        rank[k] = cls[k] >= 0 ? atomicAdd(&cnt[cls[k]], 1u) : 0u;
+    }
+    __syncthreads();
+    if (tid < kOrderClasses) {
+        uint32_t before = 0u;
+        for (int c = 0; c < tid; ++c) before += classes[c];
+        base[tid] = before + (cnt[tid] ? atomicAdd(&classes[kOrderClasses + tid], cnt[tid]) : 0u);
+    }
+    __syncthreads();
+    for (int k = 0; k < kOrderTiles; ++k) {
+        const int t = ((int)blockIdx.x * kOrderTiles + k) * kOrderThreads + tid;
+        if (cls[k] >= 0) order[base[cls[k]] + rank[k]] = t;
+    }
+}
+
+void launch_tile_order(const CompositeArgs &a, int32_t *order, uint32_t *classes, hipStream_t st) {
+    const int per = kOrderThreads * kOrderTiles;
+    const unsigned blocks = (unsigned)((a.total_tiles + per - 1) / per);
+    launch_fill_u32(classes, 0u, 2 * kOrderClasses, st);
+    hipLaunchKernelGGL(k_tile_classes, dim3(blocks), dim3(kOrderThreads), 0, st, a, classes);
+    hipLaunchKernelGGL(k_tile_order, dim3(blocks), dim3(kOrderThreads), 0, st, a, classes, order);
+}
+
 static inline unsigned flat_grid(const CompositeArgs &a) {
     if (a.quad_list) return (unsigned)std::max(a.n_listed, 1);
     return (unsigned)(((a.total_tiles << a.quad_log) + 7) & ~7);
@@ -1223,7 +1309,7 @@ static void pass1_mode(const CompositeArgs &a, hipStream_t st) {
         }
     }
     if (!a.quad_list) {
-        const unsigned grid = (unsigned)(((a.total_tiles << a.region_log) + 7) & ~7);
+        const unsigned grid = region_grid(a);
         hipLaunchKernelGGL((k_pass1_region<kMode>), dim3(grid), dim3(kWave), 0, st, a);
         return;
     }
@@ -1285,7 +1371,7 @@ static void pass2_ray(const CompositeArgs &a, bool stats, uint64_t *counters, hi
 template <int kMode, bool kPersistentForm>
 static void pass2_ray_any(const CompositeArgs &a, bool stats, uint64_t *counters, hipStream_t st) {
     if (a.ccount && !a.work && !a.quad_list) {
-        const unsigned grid = (unsigned)(((a.total_tiles << a.region_log) + 7) & ~7);
+        const unsigned grid = region_grid(a);
         if (stats)
             hipLaunchKernelGGL((k_pass2_region<true, kMode>), dim3(grid), dim3(kWave), 0, st, a, counters);
         else
@@ -1305,7 +1391,7 @@ static void pass2_ray_any(const CompositeArgs &a, bool stats, uint64_t *counters
 template <int kMode>
 static bool pass2_agg_region(const CompositeArgs &a, hipStream_t st) {
     if (!(a.ccount && !a.work && !a.quad_list && a.agg >= 1 && a.agg <= 3)) return false;
-    const unsigned grid = (unsigned)(((a.total_tiles << a.region_log) + 7) & ~7);
+    const unsigned grid = region_grid(a);
     if (a.agg == 1)
         hipLaunchKernelGGL((k_pass2_region<false, kMode, 1>), dim3(grid), dim3(kWave), 0, st, a, nullptr);
     else if (a.agg == 2)

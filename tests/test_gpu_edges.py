@@ -140,3 +140,24 @@ def test_binning_chunk_lengths(n, tile):
         each = torch.maximum(each, gs.sensitivity(d, vw.subset([v]), tile=tile)[0])
     assert float(every.max()) > 0
     assert torch.equal(every, each)
+
+
+@pytest.mark.parametrize("aggregate", ["ray", "tile", "image"])
+@pytest.mark.parametrize("tile", [(16, 16), (32, 32), (32, 16)])
+def test_tile_order_matches_tile_by_tile(aggregate, tile):
+    """A call of more than 8 192 regions composites its tiles longest list
+    first, one of fewer in tile order; the sensitivities are the same: 41 views
+    in one call against each view by itself (the tile count is no multiple of
+    the runs the order is dealt in)."""
+    import synth
+    import paper_2607_02721_amd as gs
+    sc = synth.make_cluster_scene(20_000, 10, 1)
+    vw = synth.make_orbit_views(41, 11, 330, 207)
+    d = gs.DeviceScene.from_scene(sc)
+    agg = {"ray": gs.AGG_RAY, "tile": gs.AGG_TILE, "image": gs.AGG_IMAGE}[aggregate]
+    every, _ = gs.sensitivity(d, vw, tile=tile, aggregate=agg)
+    each = torch.zeros_like(every)
+    for v in range(41):
+        each = torch.maximum(each, gs.sensitivity(d, vw.subset([v]), tile=tile, aggregate=agg)[0])
+    assert float(every.max()) > 0
+    assert torch.equal(every, each)
