@@ -718,7 +718,6 @@ CompositeArgs composite_args(const ChunkRun &r, int total_tiles, const gs_params
                              const Setup &S) {
     CompositeArgs a{};
     a.quad_log = S.quad_log;
-    a.clist_pos = S.agg == GS_AGG_TILE ? 1 : 0;
     a.region_log = region_log_of(S.tsx, S.tsy);
     a.views = r.views_dev;
     a.tile_view = r.tile_view;
@@ -873,8 +872,7 @@ gs_status gs_sensitivity(const gs_scene *scene, const gs_views *views, const gs_
     setup_chunks(S);
     S.agg = params->aggregate;
     S.nq = params->query_mode == GS_QUERY_CHANNEL ? 3 : 1;
-    // every granularity composites on compacted lists (per-tile queries keep
-    // list positions in them: their accumulators are indexed by position)
+    // every granularity composites on compacted lists
     S.compact = true;
     const auto chunks = plan_chunks(views, S, params, scratch_budget());
     launch_fill_u32((uint32_t *)sens, 0u, S.N, st);
@@ -924,7 +922,6 @@ gs_status gs_sensitivity(const gs_scene *scene, const gs_views *views, const gs_
         // 16x16 query): the region lists hold Gaussians and pass 2 takes each
         // share's maximum itself, with no per-entry accumulators
         const bool tile_direct = S.agg == GS_AGG_TILE && a.ccount && !a.quad_list && !a.work;
-        if (tile_direct) a.clist_pos = 0;
         if (S.agg == GS_AGG_TILE && !tile_direct && region_log_of(S.tsx, S.tsy) > 0)
             return fail(GS_ERR_UNSUPPORTED, "tile queries on binning tiles above 16x16 need the region form");
         if (r.ranges.size() > 1) {
@@ -971,6 +968,10 @@ gs_status gs_sensitivity(const gs_scene *scene, const gs_views *views, const gs_
             launch_tile_order(a, r.tile_order, r.order_classes, st);
             a.tile_order = r.tile_order;
         }
+        // (counting calls keep the region form: their pair counters say what
+        // its 64-entry slices walk)
+        a.by_quads = !a.quad_list && S.agg != GS_AGG_TILE && !(params->flags & GS_FLAG_COUNT_PAIRS) &&
+                     quads_pay((int64_t)a.total_tiles << a.region_log);
         launch_composite_pass1(a, st);
         HIP_TRY(hipGetLastError());
         tm.mark(4, st);
@@ -1712,6 +1713,7 @@ void enqueue_plan(gs_plan *P, hipStream_t st, float *const *sens) {
                 launch_tile_order(a, G.tile_order, G.order_classes, st);
                 a.tile_order = G.tile_order;
             }
+            a.by_quads = !a.work && quads_pay((int64_t)a.total_tiles << a.region_log);
             launch_composite_pass1(a, st);
             launch_composite_pass2(a, false, nullptr, st);
         }

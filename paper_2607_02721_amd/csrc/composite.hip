@@ -112,6 +112,22 @@ __device__ __forceinline__ bool setup_quad(const CompositeArgs &a, int logical, 
     return true;
 }
 
+// With a tile order the longest lists start first: a wave's time follows its
+// list, and a launch in tile order, its dense tiles anywhere, ended in a tail
+// (437k Gaussians x 13 views: the two passes 954 + 934 us in tile order, 688 +
+// 699 so; 1M x 100 views, whose tail is short, 0 to 1%).  The order is dealt
+// over the XCDs in runs of kOrderRun tiles, which are mostly neighbours and
+// gather the same records (runs of 1 lost 2% at 1M x 100 views on some scenes,
+// 4 to 64 measured alike), and the 2^per_log regions or quadrants of a tile stay
+// on its XCD.  Returns the block's unit, or `past` if it has none.
+constexpr int kOrderRun = 16;
+__device__ __forceinline__ int unit_in_order(const CompositeArgs &a, int per_log, int past) {
+    const int slot = (int)blockIdx.x >> 3, k = slot >> per_log;
+    const int t = ((k / kOrderRun) * 8 + ((int)blockIdx.x & 7)) * kOrderRun + k % kOrderRun;
+    if (t >= a.total_tiles) return past;
+    return (a.tile_order[t] << per_log) + (slot & ((1 << per_log) - 1));
+}
+
 // Next quadrant for this wave: the block's own (remapped) index in the flat
 // form, or the next item of the work counter in the persistent form.  The
 // form is a template parameter so that the flat kernels keep every
@@ -122,6 +138,7 @@ __device__ __forceinline__ int next_quad(const CompositeArgs &a, int &iter) {
     if (!kPersistent) {
         if (iter++) return nq;
         if (a.quad_list) return (int)blockIdx.x < a.n_listed ? (int)a.quad_list[blockIdx.x] : nq;
+        if (a.tile_order) return unit_in_order(a, a.quad_log, nq);
         if (!a.xcd_remap) return blockIdx.x;
         const int padded = (nq + 7) & ~7;
         return xcd_remap(blockIdx.x, padded);
@@ -366,28 +383,38 @@ __global__ __launch_bounds__(kWave) void k_pass1(CompositeArgs a) {
         uint32_t ccnt = 0;
         for (uint64_t e0 = w.start; e0 < w.end; e0 += kWave) {
             if (__all(done)) break;
-            const int n = stage_slice<0, 1, kCh, !kCh>(w, e0, a.r2_log2, geo, col, nullptr, nullptr, nullptr, cblue,
-                                                 cl ? cl + ccnt : nullptr);
+            const int n = stage_slice<0, kBlock, kCh, !kCh>(w, e0, a.r2_log2, geo, col, nullptr, nullptr, nullptr,
+                                                            cblue, cl ? cl + ccnt : nullptr);
             ccnt += (uint32_t)n;
             wave_sync();
-            for (int j = 0; j < n; ++j) {
-                const float4 G = geo[j], Cc = col[j];
-                bool in_fp;
-                const float rho = kCh ? pair_rho(G, Cc, w.xl, w.yl, a.r2_log2, in_fp)
-                                      : pair_rho_log2(G, Cc, w.xl, w.yl, in_fp);
-                if (kMode == kModeL1) {
-                    const float cr = Cc.z * rho;
-                    A = fmaf(cr, T, A);
-                } else if (kMode == kModeL2) {
-                    const float rt = rho * T;
-                    A = fmaf(Cc.z * rt, rt, A);
-                } else {
-                    const float rt = rho * T;
-                    A = fmaf(Cc.z, rt, A);
-                    AG = fmaf(Cc.w, rt, AG);
-                    AB = fmaf(cblue[j], rt, AB);
+            // blocks of kBlock entries without branches (null entries fill the
+            // last one): their attenuations are independent of each other, only
+            // the short chain through A and T is not
+            for (int j0 = 0; j0 < n; j0 += kBlock) {
+                float rho[kBlock];
+#pragma unroll
+                for (int q = 0; q < kBlock; ++q) {
+                    bool in_fp;
+                    rho[q] = kCh ? pair_rho(geo[j0 + q], col[j0 + q], w.xl, w.yl, a.r2_log2, in_fp)
+                                 : pair_rho_log2(geo[j0 + q], col[j0 + q], w.xl, w.yl, in_fp);
                 }
-                T = fmaf(-rho, T, T);
+#pragma unroll
+                for (int q = 0; q < kBlock; ++q) {
+                    const float4 Cc = col[j0 + q];
+                    if (kMode == kModeL1) {
+                        const float cr = Cc.z * rho[q];
+                        A = fmaf(cr, T, A);
+                    } else if (kMode == kModeL2) {
+                        const float rt = rho[q] * T;
+                        A = fmaf(Cc.z * rt, rt, A);
+                    } else {
+                        const float rt = rho[q] * T;
+                        A = fmaf(Cc.z, rt, A);
+                        AG = fmaf(Cc.w, rt, AG);
+                        AB = fmaf(cblue[j0 + q], rt, AB);
+                    }
+                    T = fmaf(-rho[q], T, T);
+                }
             }
             if (kMode == kModeL1) done = done || (T * cmax < a.share_floor * A);
             if (kMode == kModeL2) done = done || ((T * T) * cmax < a.share_floor * A);
@@ -404,6 +431,17 @@ __global__ __launch_bounds__(kWave) void k_pass1(CompositeArgs a) {
         if (cl && threadIdx.x == 0) a.ccount[qi] = ccnt;
     }
 }
+
+// Pointers known to be global memory: read from a scene slot, a pointer is
+// generic to the compiler, whose loads then also count as LDS accesses and wait
+// for each other.
+template <typename T>
+using GlobalPtr = const __attribute__((address_space(1))) T *;
+template <typename T>
+__device__ __forceinline__ GlobalPtr<T> as_global(const T *p) {
+    return (GlobalPtr<T>)p;
+}
+typedef float GeoHalf __attribute__((ext_vector_type(4)));   // half of a GeoRec
 
 // An entry staged for a region: g = (mean x, y relative to the region's
 // first quadrant, beta, a'), c = (g', log2 alpha, colour sum, cut + log2
@@ -423,16 +461,16 @@ struct __align__(16) RegionRec {
 };
 
 // Region `logical` of the launch: its tile, view, scene slot, origin and, per
-// quadrant k (column k & 1, row k >> 1), the quadrant's index in the tile,
+// quadrant k (column k & 1, row k >> 1),
 // its sub-rectangle bit and whether it exists (inside the view and the tile).
 struct RegionSetup {
     int gt, v;
     const SceneSlot *S;
     const ViewDev *V;
     int ox, oy;
-    int quad[4];
     uint32_t qbit[4];
     uint32_t valid;
+    int list_quad;      // the region's first quadrant, whose slots hold its compacted list
 };
 
 __device__ __forceinline__ bool setup_region(const CompositeArgs &a, int logical, RegionSetup &r) {
@@ -454,34 +492,20 @@ __device__ __forceinline__ bool setup_region(const CompositeArgs &a, int logical
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
         const int kx = k & 1, ky = k >> 1;
-        r.quad[k] = (qxb + kx) + ((qyb + ky) << qlx);
         const bool ok = kx < kxn && ky < kyn && r.ox + kQuad * kx < V.W && r.oy + kQuad * ky < V.H;
-        r.qbit[k] = ok ? quad_subrect_bits(r.quad[k], V.tsx, V.tsy) << 28 : 0u;
+        r.qbit[k] = ok ? quad_subrect_bits((qxb + kx) + ((qyb + ky) << qlx), V.tsx, V.tsy) << 28 : 0u;
         r.valid |= ok ? (1u << k) : 0u;
     }
+    r.list_quad = qxb + (qyb << qlx);
     // quadrant 0 exists whenever any does (it holds the region's origin)
     return r.valid != 0u;
 }
 
 // The region this block composites, or a number past the launch's regions.
-// With a tile order the longest lists start first: a wave's time follows its
-// list, and a launch in tile order, its dense tiles anywhere, ended in a tail
-// (437k Gaussians x 13 views: the two passes 954 + 934 us in tile order, 688 +
-// 699 so; 1M x 100 views, whose tail is short, 0 to 1%).  The order is dealt
-// over the XCDs in runs of kOrderRun tiles, which are mostly neighbours and
-// gather the same records (runs of 1 lost 2% at 1M x 100 views on some scenes,
-// 4 to 64 measured alike), and a tile's regions stay on its XCD.
-constexpr int kOrderRun = 16;
 __device__ __forceinline__ int region_of_block(const CompositeArgs &a) {
     const int nreg = a.total_tiles << a.region_log;
-    const int b = (int)blockIdx.x;
-    if (a.tile_order) {
-        const int slot = b >> 3, k = slot >> a.region_log;
-        const int t = ((k / kOrderRun) * 8 + (b & 7)) * kOrderRun + k % kOrderRun;
-        if (t >= a.total_tiles) return nreg;
-        return (a.tile_order[t] << a.region_log) + (slot & ((1 << a.region_log) - 1));
-    }
-    return a.xcd_remap ? xcd_remap(b, (nreg + 7) & ~7) : b;
+    if (a.tile_order) return unit_in_order(a, a.region_log, nreg);
+    return a.xcd_remap ? xcd_remap(blockIdx.x, (nreg + 7) & ~7) : (int)blockIdx.x;
 }
 
 // Pass 1 over regions of up to 2 x 2 quadrants (one wave per region, region
@@ -542,24 +566,39 @@ __global__ __launch_bounds__(kWave) void k_pass1_region(CompositeArgs a) {
     const float cut = a.r2_log2;
     // the region's list: entries that reach one of its quadrants, each with
     // its quadrant bits (in the slots of quadrant 0's compacted list)
-    uint32_t *cl = S.clist ? S.clist + ((start << a.quad_log) + (uint64_t)R.quad[0] * (end - start) - a.clist_shift)
+    uint32_t *cl = S.clist ? S.clist + ((start << a.quad_log) + (uint64_t)R.list_quad * (end - start) - a.clist_shift)
                            : nullptr;
     uint32_t ccnt = 0u;
     const uint64_t lt = lanemask_lt64();
-    for (uint64_t e0 = start; e0 < end && alive; e0 += kWave) {
-        const uint64_t e = e0 + lane;
-        const uint32_t raw = e < end ? S.lists[e] : 0u;
-        uint32_t want = 0u;
+    // Two slices ahead their list words and one slice ahead their records are
+    // on the way while a slice composites: a launch of few waves, or its last
+    // long lists, would otherwise wait for memory four times per 64 entries.
+    const GlobalPtr<GeoHalf> Rv = as_global((const GeoHalf *)(S.R + vbase));
+    const GlobalPtr<float> CBv = as_global(S.CB + vbase);
+    const GlobalPtr<uint32_t> lists = as_global(S.lists + start);
+    const uint64_t len = end - start;
+    uint32_t want = 0u;
 #pragma unroll
-        for (int k = 0; k < 4; ++k) want |= ((alive >> k) & 1u) ? R.qbit[k] : 0u;
+    for (int k = 0; k < 4; ++k) want |= ((alive >> k) & 1u) ? R.qbit[k] : 0u;
+    uint32_t raw = lane < len ? lists[lane] : 0u, raw1 = lane + kWave < len ? lists[lane + kWave] : 0u;
+    for (uint64_t e0 = 0; e0 < len && alive; e0 += kWave) {
         uint32_t h = 0u;
         const uint32_t g = raw & kIndexMask;
-        const int64_t o = vbase + g;
-        float4 r1 = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-        float mx0 = 0.0f, my0 = 0.0f, mx1 = 0.0f, my1 = 0.0f;
+        want = 0u;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) want |= ((alive >> k) & 1u) ? R.qbit[k] : 0u;
+        GeoHalf pm = {0.0f, 0.0f, 0.0f, 0.0f}, pq = {0.0f, 0.0f, 0.0f, 0.0f};
         if (raw & want) {
-            const float4 r0 = S.R[o].m;
-            r1 = S.R[o].q;
+            pm = Rv[2 * (uint64_t)(raw & kIndexMask)];
+            pq = Rv[2 * (uint64_t)(raw & kIndexMask) + 1];
+        }
+        const float4 r0 = make_float4(pm.x, pm.y, pm.z, pm.w), r1 = make_float4(pq.x, pq.y, pq.z, pq.w);
+        float mx0 = 0.0f, my0 = 0.0f, mx1 = 0.0f, my1 = 0.0f, cb = 0.0f;
+        want = 0u;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) want |= ((alive >> k) & 1u) ? R.qbit[k] : 0u;
+        if (raw & want) {
+            if (!kCh) cb = CBv[g];
             mx0 = (r0.x - fx0) + r0.z;
             my0 = (r0.y - fy0) + r0.w;
             mx1 = (r0.x - fx1) + r0.z;
@@ -580,22 +619,22 @@ __global__ __launch_bounds__(kWave) void k_pass1_region(CompositeArgs a) {
             q.m1 = make_float2(-sg.w * mx1, my1);
             if (kCh) {
                 // as stage_raw with kChannel: (g', alpha, c_R, c_G), c_B
-                const float4 c3 = S.R3[o];
+                const float4 c3 = S.R3[vbase + g];
                 q.c = make_float4(r1.z, r1.w, c3.x, c3.y);
                 q.cblue = c3.z;
             } else {
-                const float cb = S.CB[o];
                 const float la = __builtin_amdgcn_logf(r1.w);
                 q.c = make_float4(r1.z, la, cb, cut + la);
             }
         }
         if (cl && h)
-            __builtin_nontemporal_store((a.clist_pos ? (uint32_t)(e - start) : g) | (h << 28),
-                                        &cl[ccnt + (uint32_t)__popcll(bal & lt)]);
+            __builtin_nontemporal_store(g | (h << 28), &cl[ccnt + (uint32_t)__popcll(bal & lt)]);
         ccnt += (uint32_t)n;
         uint64_t bq[4];
 #pragma unroll
         for (int k = 0; k < 4; ++k) bq[k] = __ballot((h >> k) & 1u);
+        raw = raw1;
+        raw1 = e0 + 2 * kWave + lane < len ? lists[e0 + 2 * kWave + lane] : 0u;
         wave_sync();
         // Slot j holds the entry of the j-th lane of bal in lane order; its
         // quadrant bits are that lane's bits of bq[k] (scalar work only).  Two
@@ -661,7 +700,7 @@ __global__ __launch_bounds__(kWave) void k_pass1_region(CompositeArgs a) {
             }
         }
     }
-    if (cl && lane == 0) a.ccount[((gt - a.tile_first) << a.quad_log) + R.quad[0]] = ccnt;
+    if (cl && lane == 0) a.ccount[((gt - a.tile_first) << a.quad_log) + R.list_quad] = ccnt;
 }
 
 // Transposed butterfly over 64 lanes for 16 values: afterwards lane L holds
@@ -746,7 +785,7 @@ template <bool kStats, bool kPersistent, int kAgg, int kMode, bool kCompact>
 __global__ __launch_bounds__(kWave, kPersistent ? 5 : ((kAgg != 0 || kMode == kModeChannel) ? 6 : 7))
 void k_pass2(CompositeArgs a, uint64_t *__restrict__ counters) {
     static_assert(!(kAgg != 0 && kMode == kModeChannel), "per-channel queries have no aggregated form");
-    static_assert(!(kAgg != 0 && kCompact), "aggregated queries walk the tile lists");
+    static_assert(!(kAgg == 1 && kCompact), "per-tile queries index their accumulators by list position");
     constexpr bool kCh = kMode == kModeChannel;
     __shared__ float4 geo[kWave], col[kWave];
     __shared__ uint32_t sid[kWave];
@@ -925,12 +964,10 @@ void k_pass2(CompositeArgs a, uint64_t *__restrict__ counters) {
 // shares go through the transposed sum of k_pass2 (the same per-pixel shares
 // and the same sums over each quadrant's 64 pixels), each sum becomes u64
 // fixed point as there, and the quadrants' integers are added before one
-// atomic per entry.  Per-tile queries (16x16 binning tiles: one region per
-// tile, so a region is one whole query) take the share's maximum at once when
-// the region lists hold Gaussians; with list positions
-// (CompositeArgs::clist_pos) they accumulate per list entry instead.
+// atomic per entry.  For per-tile queries a region is one whole query: they
+// take the share's maximum at once.
 template <bool kStats, int kMode, int kAgg = 0>
-__global__ __launch_bounds__(kWave, kStats ? 5 : 7) void k_pass2_region(CompositeArgs a,
+__global__ __launch_bounds__(kWave, kStats ? 5 : (kMode == kModeChannel ? 6 : 7)) void k_pass2_region(CompositeArgs a,
                                                                          uint64_t *__restrict__ counters) {
     constexpr bool kCh = kMode == kModeChannel;
     static_assert(!(kCh && kAgg != 0), "per-channel queries have no aggregated form");
@@ -994,9 +1031,9 @@ __global__ __launch_bounds__(kWave, kStats ? 5 : 7) void k_pass2_region(Composit
         alive |= (((R.valid >> k) & 1u) && !__all(done[k])) ? (1u << k) : 0u;
     }
     const uint64_t start = S.tile_off[gt - S.tile0], end = S.tile_off[gt - S.tile0 + 1];
-    const uint32_t *__restrict__ cl =
-        S.clist + ((start << a.quad_log) + (uint64_t)R.quad[0] * (end - start) - a.clist_shift);
-    const uint32_t count = a.ccount[((gt - a.tile_first) << a.quad_log) + R.quad[0]];
+    const GlobalPtr<uint32_t> cl = as_global(
+        (const uint32_t *)S.clist + ((start << a.quad_log) + (uint64_t)R.list_quad * (end - start) - a.clist_shift));
+    const uint32_t count = a.ccount[((gt - a.tile_first) << a.quad_log) + R.list_quad];
     const int64_t vbase = (int64_t)(v - S.view0) * S.N;
     const float cmax = __uint_as_float(S.cmax[v - S.view0]);
     const float cut = a.r2_log2;
@@ -1005,39 +1042,52 @@ __global__ __launch_bounds__(kWave, kStats ? 5 : 7) void k_pass2_region(Composit
     uint32_t n_in = 0, n_live = 0, n_amb = 0, amb = 0u;   // amb: quadrants whose ray saw an ambiguous pair
     uint64_t n_eval = 0;
     const uint64_t lt = lanemask_lt64();
+    // (list words two slices ahead, records and sensitivities one slice ahead,
+    // as in k_pass1_region; a sensitivity read early is only lower, and one that
+    // a share beats is raised by an atomic maximum anyway)
+    const GlobalPtr<GeoHalf> Rv = as_global((const GeoHalf *)(S.R + vbase));
+    const GlobalPtr<float> CBv = as_global(S.CB + vbase);
+    const GlobalPtr<uint32_t> sens = as_global((const uint32_t *)sens_bits);
+    uint32_t raw = lane < count ? cl[lane] : 0u, raw1 = lane + kWave < count ? cl[lane + kWave] : 0u;
+    GeoHalf pm = {0.0f, 0.0f, 0.0f, 0.0f}, pq = {0.0f, 0.0f, 0.0f, 0.0f};
+    float pcb = 0.0f;
+    uint32_t psens = 0u;
+    auto fetch = [&]() {
+        if ((raw >> 28) & alive) {
+            const uint64_t g = raw & kIndexMask;
+            pm = Rv[2 * g];
+            pq = Rv[2 * g + 1];
+            if (!kCh) pcb = CBv[g];
+            if (kAgg == 0) psens = sens[g];
+        }
+    };
     for (uint32_t e0 = 0; e0 < count && alive; e0 += kWave) {
-        const uint32_t e = e0 + lane;
-        const uint32_t raw = e < count ? cl[e] : 0u;
         const uint32_t h = (raw >> 28) & alive;
         const uint64_t bal = __ballot(h != 0u);
         const int n = __popcll(bal);
+        fetch();
         if (h) {
-            // (per-tile queries: the list holds the entry's position in the
-            // tile's list, whose entry gives the Gaussian)
-            const uint32_t pos = raw & kIndexMask;
-            const uint32_t g = (kAgg == 1 && a.clist_pos) ? S.lists[start + pos] & kIndexMask : pos;
-            const int64_t o = vbase + g;
-            const float4 r0 = S.R[o].m;
-            const float4 r1 = S.R[o].q;
+            const uint32_t g = raw & kIndexMask;
+            const float4 r0 = make_float4(pm.x, pm.y, pm.z, pm.w), r1 = make_float4(pq.x, pq.y, pq.z, pq.w);
             float cb;
             RegionRec &q = rec[__popcll(bal & lt)];
             const float4 sg = scaled_geo((r0.x - fx0) + r0.z, (r0.y - fy0) + r0.w, r1.x, r1.y);
             q.g = sg;
             if (kCh) {
-                const float4 c3 = S.R3[o];
+                const float4 c3 = S.R3[vbase + g];
                 cb = c3.x;
                 q.c = make_float4(r1.z, r1.w, c3.x, c3.y);
                 q.cblue = c3.z;
             } else {
-                cb = S.CB[o];
+                cb = pcb;
                 const float la = __builtin_amdgcn_logf(r1.w);
                 q.c = make_float4(r1.z, la, cb, cut + la);
             }
             q.m1 = make_float2(-sg.w * ((r0.x - fx1) + r0.z), (r0.y - fy1) + r0.w);
-            q.sid = (kAgg == 1 && a.clist_pos) ? pos : g;
+            q.sid = g;
             q.hq = h;
             if (kAgg == 0) {
-                const float sold = fmaxf(__uint_as_float(sens_bits[g]), a.report_floor);
+                const float sold = fmaxf(__uint_as_float(psens), a.report_floor);
                 q.sold = sold;
                 // c x > sold implies x > sold / (c (1 + 2^-24)); the bar sits
                 // below that by more than the rounding of v_rcp_f32 and the
@@ -1051,6 +1101,8 @@ __global__ __launch_bounds__(kWave, kStats ? 5 : 7) void k_pass2_region(Composit
 #pragma unroll
         for (int k = 0; k < 4; ++k) bq[k] = __ballot((h >> k) & 1u);
         if (kStats) n_eval += (uint64_t)(__popcll(bq[0]) + __popcll(bq[1]) + __popcll(bq[2]) + __popcll(bq[3]));
+        raw = raw1;
+        raw1 = e0 + 2 * kWave + lane < count ? cl[e0 + 2 * kWave + lane] : 0u;
         wave_sync();
         if constexpr (kAgg != 0) {
             // per quadrant, its entries as bits in slot order (slot j is the
@@ -1086,7 +1138,7 @@ __global__ __launch_bounds__(kWave, kStats ? 5 : 7) void k_pass2_region(Composit
                 }
                 const int j = jb + (lane >> 2);
                 if ((lane & 3) == 0 && j < n && acc) {
-                    if (kAgg == 1 && !a.clist_pos) {
+                    if (kAgg == 1) {
                         // the region is the whole 16x16 query and the list
                         // holds the Gaussian: the sum is complete, so its share
                         // raises the sensitivity here (the value k_agg_tile_max
@@ -1094,8 +1146,7 @@ __global__ __launch_bounds__(kWave, kStats ? 5 : 7) void k_pass2_region(Composit
                         const float sq_share = (float)((double)acc * (1.0 / kAggScale));
                         if (sq_share > 0.0f) atomicMax(&sens_bits[rec[j].sid], __float_as_uint(sq_share));
                     } else {
-                        const int64_t idx = kAgg == 1 ? (int64_t)(start + rec[j].sid)
-                                                      : (kAgg == 2 ? vbase + rec[j].sid : (int64_t)rec[j].sid);
+                        const int64_t idx = kAgg == 2 ? vbase + rec[j].sid : (int64_t)rec[j].sid;
                         atomicAdd((unsigned long long *)&a.acc[idx], (unsigned long long)acc);
                     }
                 }
@@ -1225,10 +1276,13 @@ static unsigned resident_waves(K kernel) {
     return (unsigned)std::max(1, cus) * (unsigned)std::max(1, per_cu);
 }
 
-static inline unsigned region_grid(const CompositeArgs &a) {
-    return a.tile_order ? (unsigned)((a.total_tiles + 8 * kOrderRun - 1) / (8 * kOrderRun) * (8 * kOrderRun) << a.region_log)
-                        : (unsigned)(((a.total_tiles << a.region_log) + 7) & ~7);
+// Blocks of a flat launch of 2^per_log units per tile.
+static inline unsigned unit_grid(const CompositeArgs &a, int per_log) {
+    const int deal = 8 * kOrderRun;
+    return a.tile_order ? (unsigned)((a.total_tiles + deal - 1) / deal * deal << per_log)
+                        : (unsigned)(((a.total_tiles << per_log) + 7) & ~7);
 }
+static inline unsigned region_grid(const CompositeArgs &a) { return unit_grid(a, a.region_log); }
 
 // Half-octave class of a tile's list length, the longest lists in class 0.
 __device__ __forceinline__ int length_class(const CompositeArgs &a, int t) {
@@ -1292,12 +1346,13 @@ void launch_tile_order(const CompositeArgs &a, int32_t *order, uint32_t *classes
 
 static inline unsigned flat_grid(const CompositeArgs &a) {
     if (a.quad_list) return (unsigned)std::max(a.n_listed, 1);
-    return (unsigned)(((a.total_tiles << a.quad_log) + 7) & ~7);
+    return unit_grid(a, a.quad_log);
 }
 
 // The flat form over every quadrant runs by regions (k_pass1_region,
-// bit-identical, every query mode); runs over a quadrant list (sparse ray
-// masks) and the persistent form run by quadrants.
+// bit-identical, every query mode) or, when few, by quadrants (quads_pay); runs
+// over a quadrant list (sparse ray masks) and the persistent form run by
+// quadrants.
 template <int kMode>
 static void pass1_mode(const CompositeArgs &a, hipStream_t st) {
     if constexpr (kMode != kModeChannel) {
@@ -1308,7 +1363,7 @@ static void pass1_mode(const CompositeArgs &a, hipStream_t st) {
             return;
         }
     }
-    if (!a.quad_list) {
+    if (!a.quad_list && !a.by_quads) {
         const unsigned grid = region_grid(a);
         hipLaunchKernelGGL((k_pass1_region<kMode>), dim3(grid), dim3(kWave), 0, st, a);
         return;
@@ -1326,17 +1381,19 @@ void launch_composite_pass1(const CompositeArgs &a, hipStream_t st) {
     }
 }
 
+template <int kMode, int kAgg, bool kCompact>
+static void pass2_agg_quads(const CompositeArgs &a, uint64_t *counters, hipStream_t st) {
+    hipLaunchKernelGGL((k_pass2<false, false, kAgg, kMode, kCompact>), dim3(flat_grid(a)), dim3(kWave), 0, st, a,
+                       counters);
+}
 template <int kMode>
 static void pass2_agg(const CompositeArgs &a, uint64_t *counters, hipStream_t st) {
     if (a.agg == 1)
-        hipLaunchKernelGGL((k_pass2<false, false, 1, kMode, false>), dim3(flat_grid(a)), dim3(kWave), 0, st, a,
-                           counters);
+        pass2_agg_quads<kMode, 1, false>(a, counters, st);
     else if (a.agg == 2)
-        hipLaunchKernelGGL((k_pass2<false, false, 2, kMode, false>), dim3(flat_grid(a)), dim3(kWave), 0, st, a,
-                           counters);
+        a.ccount ? pass2_agg_quads<kMode, 2, true>(a, counters, st) : pass2_agg_quads<kMode, 2, false>(a, counters, st);
     else
-        hipLaunchKernelGGL((k_pass2<false, false, 3, kMode, false>), dim3(flat_grid(a)), dim3(kWave), 0, st, a,
-                           counters);
+        a.ccount ? pass2_agg_quads<kMode, 3, true>(a, counters, st) : pass2_agg_quads<kMode, 3, false>(a, counters, st);
 }
 
 template <int kMode, bool kPersistentForm, bool kCompact>
@@ -1370,7 +1427,7 @@ static void pass2_ray(const CompositeArgs &a, bool stats, uint64_t *counters, hi
 // quadrant lists.
 template <int kMode, bool kPersistentForm>
 static void pass2_ray_any(const CompositeArgs &a, bool stats, uint64_t *counters, hipStream_t st) {
-    if (a.ccount && !a.work && !a.quad_list) {
+    if (a.ccount && !a.work && !a.quad_list && !a.by_quads) {
         const unsigned grid = region_grid(a);
         if (stats)
             hipLaunchKernelGGL((k_pass2_region<true, kMode>), dim3(grid), dim3(kWave), 0, st, a, counters);
@@ -1390,7 +1447,7 @@ static void pass2_ray_any(const CompositeArgs &a, bool stats, uint64_t *counters
 // rejects the first).
 template <int kMode>
 static bool pass2_agg_region(const CompositeArgs &a, hipStream_t st) {
-    if (!(a.ccount && !a.work && !a.quad_list && a.agg >= 1 && a.agg <= 3)) return false;
+    if (!(a.ccount && !a.work && !a.quad_list && !a.by_quads && a.agg >= 1 && a.agg <= 3)) return false;
     const unsigned grid = region_grid(a);
     if (a.agg == 1)
         hipLaunchKernelGGL((k_pass2_region<false, kMode, 1>), dim3(grid), dim3(kWave), 0, st, a, nullptr);

@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 namespace gs {
 
 // Binning tiles are 2^tsx x 2^tsy pixels with tsx, tsy in {3, 4, 5} (8, 16
@@ -292,11 +294,10 @@ struct CompositeArgs {
                                  // the region form: per region, at the region's first quadrant)
     uint64_t clist_shift;        // subtracted from every compacted-list offset (launches over a tile range
                                  // whose compacted lists fill a pool from its start)
-    int32_t clist_pos;           // 1: the region lists hold each entry's position in its tile's list instead
-                                 // of its Gaussian index (per-tile queries index their accumulators by it)
     const uint32_t *quad_list;   // ray-masked runs: the quadrants ((tile << quad_log) + q) holding a selected ray,
     int32_t n_listed;            // in order; only these are composited (null: every quadrant)
     const int32_t *tile_order;   // region launches: the launch's tiles, longest lists first (null: in tile order)
+    int32_t by_quads;            // 1: one wave per quadrant instead of per region (quads_pay)
     float report_floor;          // pass 2 reports no share below the share floor: the float just below it, or 0
     uint32_t *amb_rays;          // pass 2 with counters: bit of every ray (ViewDev::ray_base numbering) with an
                                  // ambiguous pair is OR-ed in (null: none)
@@ -314,6 +315,18 @@ void launch_tile_order(const CompositeArgs &a, int32_t *order, uint32_t *classes
 // lost 3%, 7 280 2%), and from 12 500 on the tail of a launch in tile order,
 // with the dense tiles anywhere, is worth more than the ordering's 20 us.
 inline bool order_pays(int64_t regions) { return regions > 8192; }
+// Whether a launch of this many regions runs one wave per quadrant instead.  A
+// region's wave takes its entries one after the other through up to four
+// quadrants behind branches, some 400 cycles each when nothing else shares its
+// SIMD; a quadrant's wave takes four entries at a time without branches, about a
+// tenth, at a quarter more instructions in all.  So few regions, whose longest
+// list is what the launch waits for, run by quadrants, and launches that fill
+// the chip with regions by regions.  (Calls by regions and by quadrants: 100k
+// Gaussians x 2 views at 400x300, 950 regions, 1590 and 660 us; 20k x 24, 11 400
+// regions, per image 990 and 590; 50k x 24 at 640x360, 22 080 regions, 1135 and
+// 1109; 250k x 20 at 960x540, 40 800 regions, 2460 and 2990.)
+constexpr int64_t kByQuads = 32768;
+inline bool quads_pay(int64_t regions) { return regions <= kByQuads; }
 void launch_composite_pass1(const CompositeArgs &a, hipStream_t st);
 void launch_composite_pass2(const CompositeArgs &a, bool stats, uint64_t *counters, hipStream_t st);
 // Query objectives of the aggregated granularities from pass 1's per-ray A:

@@ -161,3 +161,42 @@ def test_tile_order_matches_tile_by_tile(aggregate, tile):
         each = torch.maximum(each, gs.sensitivity(d, vw.subset([v]), tile=tile, aggregate=agg)[0])
     assert float(every.max()) > 0
     assert torch.equal(every, each)
+
+
+@pytest.mark.parametrize("mode", ["rgbsum", "nocolor", "l2", "channel"])
+@pytest.mark.parametrize("tile", [(16, 16), (32, 32), (8, 16)])
+def test_quadrant_and_region_forms_agree(mode, tile):
+    """Small calls composite one wave per quadrant, except counting calls, which
+    run by regions: the same bits."""
+    import synth
+    import paper_2607_02721_amd as gs
+    sc = synth.make_cluster_scene(20_000, 12, 2)
+    vw = synth.make_orbit_views(3, 13, 333, 205)
+    d = gs.DeviceScene.from_scene(sc)
+    qm = {"rgbsum": gs.QUERY_RGBSUM, "nocolor": gs.QUERY_NOCOLOR, "l2": gs.QUERY_L2, "channel": gs.QUERY_CHANNEL}[mode]
+    quads, _ = gs.sensitivity(d, vw, query_mode=qm, tile=tile)
+    regions, st = gs.sensitivity(d, vw, query_mode=qm, tile=tile, stats=True, count_pairs=True)
+    assert st["n_live_pairs"] > 0 and float(quads.max()) > 0
+    assert torch.equal(quads, regions)
+
+
+@pytest.mark.parametrize("mode", ["rgbsum", "l2"])
+def test_aggregates_by_regions_and_by_quadrants(mode):
+    """42 640 regions in one call composite by regions, a view at a time by
+    quadrants.  Per-image results are the maximum over the views, bit for bit;
+    the per-scene result is a sum of exact integers of each launch, whose unit
+    (2^-60 of the launch's A) and division are all that differ."""
+    import synth
+    import paper_2607_02721_amd as gs
+    sc = synth.make_cluster_scene(20_000, 14, 1)
+    vw = synth.make_orbit_views(41, 15, 640, 414)
+    d = gs.DeviceScene.from_scene(sc)
+    qm = {"rgbsum": gs.QUERY_RGBSUM, "l2": gs.QUERY_L2}[mode]
+    every, _ = gs.sensitivity(d, vw, query_mode=qm, aggregate=gs.AGG_IMAGE)
+    each, _ = gs.sensitivity(d, vw, query_mode=qm, aggregate=gs.AGG_IMAGE, max_views_per_chunk=1)
+    assert float(every.max()) > 0
+    assert torch.equal(every, each)
+    every, _ = gs.sensitivity(d, vw, query_mode=qm, aggregate=gs.AGG_SCENE)
+    each, _ = gs.sensitivity(d, vw, query_mode=qm, aggregate=gs.AGG_SCENE, max_views_per_chunk=1)
+    # (float32 sums of up to 64 shares per quadrant, against A in float32)
+    assert torch.all((every - each).abs() <= 2e-6 * each + 1e-15)
