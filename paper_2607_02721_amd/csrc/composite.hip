@@ -1181,22 +1181,8 @@ __global__ __launch_bounds__(kWave, kStats ? 5 : (kMode == kModeChannel ? 6 : 7)
                             if ((mq[k] >> i) & 1u) {
                                 const float uu = fmaf(G.z, dyq[k >> 1], dxq[k & 1]);
                                 const float P = fmaf(-uu, uu, tq[k >> 1]);
-                                const float E = __builtin_amdgcn_exp2f(P);
                                 const float bar = kCh ? cut : C.w;
                                 const bool in_fp = P >= bar;
-                                const float rho = in_fp ? (kCh ? C.y * E : E) : 0.0f;
-                                const float rt = rho * T[k];
-                                float x;
-                                if (kCh) {
-                                    // the share itself, as k_pass2 forms it
-                                    x = rt * fmaxf(C.z * invR[k], fmaxf(C.w * invG[k], q.cblue * invB[k]));
-                                } else {
-                                    // the share is c x, and c x is monotone in
-                                    // x: the entry's largest share is c times
-                                    // its largest x (rounding is monotone too)
-                                    x = kMode == kModeL1 ? rt : rt * rt;
-                                }
-                                m = umax32(m, __float_as_uint(x));
                                 if (kStats) {
                                     const float later = kMode == kModeL2 ? (T[k] * T[k]) * cmax : T[k] * cmax;
                                     n_in += (positive[k] && in_fp) ? 1u : 0u;
@@ -1205,7 +1191,28 @@ __global__ __launch_bounds__(kWave, kStats ? 5 : (kMode == kModeChannel ? 6 : 7)
                                     n_amb += am ? 1u : 0u;
                                     amb |= am ? (1u << k) : 0u;
                                 }
-                                T[k] = fmaf(-rho, T[k], T[k]);
+                                // (a branch, not selects: lanes outside the
+                                // footprint are masked off by scalar
+                                // instructions, which the vector unit does not
+                                // wait for: calls 1% faster at 1M x 100 views.
+                                // In pass 1 the same lost 1 to 2% at mid sizes.)
+                                if (in_fp) {
+                                    const float E = __builtin_amdgcn_exp2f(P);
+                                    const float rho = kCh ? C.y * E : E;
+                                    const float rt = rho * T[k];
+                                    float x;
+                                    if (kCh) {
+                                        // the share itself, as k_pass2 forms it
+                                        x = rt * fmaxf(C.z * invR[k], fmaxf(C.w * invG[k], q.cblue * invB[k]));
+                                    } else {
+                                        // the share is c x, and c x is monotone in
+                                        // x: the entry's largest share is c times
+                                        // its largest x (rounding is monotone too)
+                                        x = kMode == kModeL1 ? rt : rt * rt;
+                                    }
+                                    m = umax32(m, __float_as_uint(x));
+                                    T[k] = fmaf(-rho, T[k], T[k]);
+                                }
                             }
                         }
                     }
