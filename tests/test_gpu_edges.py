@@ -200,3 +200,26 @@ def test_aggregates_by_regions_and_by_quadrants(mode):
     each, _ = gs.sensitivity(d, vw, query_mode=qm, aggregate=gs.AGG_SCENE, max_views_per_chunk=1)
     # (float32 sums of up to 64 shares per quadrant, against A in float32)
     assert torch.all((every - each).abs() <= 2e-6 * each + 1e-15)
+
+
+@pytest.mark.parametrize("log_scale", [-20.0, -6.0, 0.0, 8.0, 30.0])
+def test_projection_scale_range(log_scale):
+    """Gaussians from far below a pixel (the dilation alone) to scales whose
+    conic products leave the range of the shared reciprocal, at the parity bar
+    of 1e-5 against the FP64 oracle on the rays neither side calls ambiguous."""
+    import synth
+    import paper_2607_02721_amd as gs
+    from oracle import oracle as ora
+    ora.build(force=False)
+    sc = synth.make_cluster_scene(400, 16, 3)
+    sc.log_scale[:, ::2] = np.float32(log_scale)
+    sc.opacity[::2] *= np.float32(0.2)
+    vw = synth.make_orbit_views(3, 17, 97, 61)
+    ref = ora.sensitivity(sc, vw)
+    mask_np = synth.pack_bits(~ref["flag"])
+    ref = ora.sensitivity(sc, vw, None, mask_np)
+    mask = torch.as_tensor(mask_np.view(np.int32)).cuda()
+    s, st = gs.sensitivity(gs.DeviceScene.from_scene(sc), vw, ray_mask=mask, stats=True)
+    assert st["n_projected"] > 0
+    err = np.abs(s.cpu().numpy().astype(np.float64) - ref["s"]) - (1e-5 * ref["s"] + 1e-12)
+    assert err.max() <= 0
