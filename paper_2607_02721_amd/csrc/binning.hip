@@ -224,6 +224,7 @@ __global__ __launch_bounds__(kBinThreads) void k_chunk_prefix(const ViewDev *__r
 constexpr int kEmitWave = 64;
 constexpr int kEmitRows = 1;
 constexpr int kEmitCols = 128;     // tile columns per wave (2048 pixels)
+constexpr int kDirectTiles = 16;   // active tiles of a masked wave up to which it takes them one by one
 
 __device__ __forceinline__ uint64_t lanemask_lt64_bin() {
     const unsigned lane = threadIdx.x & 63;
@@ -265,16 +266,19 @@ __device__ __forceinline__ uint64_t bits_from(int s) {
     return s >= 64 ? 0ull : (s <= 0 ? ~0ull : (~0ull << s));
 }
 
-// Whether the 128-bit set (lo, hi) holds any of the bits a..b (0 <= a <= b < 128).
-__device__ __forceinline__ bool range_hits(uint64_t lo, uint64_t hi, int a, int b) {
-    const uint64_t mlo = bits_from(a) & ~bits_from(b + 1);
-    const uint64_t mhi = bits_from(a - 64) & ~bits_from(b + 1 - 64);
-    return ((lo & mlo) | (hi & mhi)) != 0ull;
+// The bits a..b (0 <= a <= b < 128) of the 128-bit set (lo, hi).
+__device__ __forceinline__ void clip_range(uint64_t &lo, uint64_t &hi, int a, int b) {
+    lo &= bits_from(a) & ~bits_from(b + 1);
+    hi &= bits_from(a - 64) & ~bits_from(b + 1 - 64);
 }
 
-template <bool kMasked>
-__device__ __forceinline__ bool tile_on(const uint32_t *act, int t) {
-    return !kMasked || ((act[t >> 5] >> (t & 31)) & 1u);
+// Position of the j-th set bit (from 0) of a 128-bit set that has more than j.
+__device__ __forceinline__ int nth_bit(uint64_t lo, uint64_t hi, int j) {
+    const int c = __popcll(lo);
+    const int base = j < c ? 0 : 64;
+    uint64_t m = j < c ? lo : hi;
+    for (int k = j < c ? j : j - c; k > 0; --k) m &= m - 1ull;
+    return base + __ffsll((long long)m) - 1;
 }
 
 // A list entry's store: 64-byte lines bypass the L2 (they are whole write
@@ -299,7 +303,7 @@ struct EmitLds {
     uint32_t *rx, *ry, *rg;   // [64] the round's pixel ranges and indices
     uint32_t *ft, *fc;  // [64] lines to store: tile, and the entry in its last slot
     uint16_t *queue;    // [batch] chunk-local positions meeting the rows
-    uint32_t *act;      // [tiles / 32] (masked form only)
+    uint32_t *act;      // [tiles / 32] active tiles (masked form only)
 };
 
 __host__ __device__ constexpr size_t emit_lds_bytes(int tiles, bool masked, int line_log, int batch) {
@@ -414,6 +418,17 @@ __global__ __launch_bounds__(kEmitWave) void k_bin_emit(const ViewDev *__restric
         act_hi = (nw > 2 ? (uint64_t)L.act[2] : 0ull) | (nw > 3 ? (uint64_t)L.act[3] << 32 : 0ull);
         if ((act_lo | act_hi) == 0ull) return;
     }
+    // few active tiles (sparse masks): the queued positions are held against
+    // each of them, 64 at a time, and the hits of a ballot go out in order at
+    // the tile's cursor (lane a holds that of the a-th active tile).  The general
+    // form's owner search, ranks and lines in LDS are a chain of some twenty LDS
+    // accesses per round, which the 16 waves a CU has room for do not hide: 2.43
+    // -> 1.32 ms at 1M Gaussians x 100 views, 1% of the 8x8 blocks (three active
+    // tiles of 80 per row; bounds of 16 and of 64 tiles measured alike).
+    const int n_act = kMasked ? __popcll(act_lo) + __popcll(act_hi) : 0;
+    const bool direct = kMasked && n_act <= kDirectTiles;
+    uint32_t cursor = 0u;
+    if (direct && lane < n_act) cursor = L.seg0[nth_bit(act_lo, act_hi, lane)];
     // entries at or past `room` would fall outside the list buffer
     const uint64_t room = cap > vlist ? cap - vlist : 0ull;
     uint32_t *__restrict__ vl = lists + vlist;
@@ -460,18 +475,46 @@ __global__ __launch_bounds__(kEmitWave) void k_bin_emit(const ViewDev *__restric
                 ny_ = yr_in[o + p];
                 ng_ = sorted_g[o + p];
             }
+            if (kMasked && direct) {
+                // the positions against each active tile in turn
+                int xl, xh, yl, yh;
+                unpack_range(__uint_as_float(ux), xl, xh);
+                unpack_range(__uint_as_float(uy), yl, yh);
+                const int xa = qi < nq ? xl >> sx : 0x7FFFFFFF, xb = xh >> sx;
+                uint64_t lo64 = act_lo, hi64 = act_hi;
+                for (int a = 0; a < n_act; ++a) {
+                    const bool low = lo64 != 0ull;
+                    const int tx = c0 + (low ? __ffsll((long long)lo64) - 1 : 63 + __ffsll((long long)hi64));
+                    lo64 &= lo64 - (low ? 1ull : 0ull);
+                    hi64 &= hi64 - (low ? 0ull : 1ull);
+                    const bool hit = xa <= tx && tx <= xb;
+                    const uint64_t bal = __ballot(hit);
+                    if (bal == 0ull) continue;
+                    const uint32_t at = (uint32_t)__builtin_amdgcn_readlane((int)cursor, a);
+                    const uint64_t e = (uint64_t)at + (uint32_t)__popcll(bal & lanemask_lt64_bin());
+                    if (hit && e < room)
+                        store_entry<kLine>(ug | (quad_mask(tx, r0, xl, xh, yl, yh, sx, sy) << 28), &vl[e]);
+                    if (lane == a) cursor = at + (uint32_t)__popcll(bal);
+                }
+                continue;
+            }
             int k = 0;
             if (qi < nq) {
                 int xl, xh, yl, yh;
                 unpack_range(__uint_as_float(ux), xl, xh);
                 unpack_range(__uint_as_float(uy), yl, yh);
-                // the tiles of its rectangle inside this wave's rows and columns
-                // (masked form: none unless one of them is active)
-                const int kx = min(xh >> sx, c1 - 1) - max(xl >> sx, c0) + 1;
-                k = kx > 0 ? kx * (min(yh >> sy, r1 - 1) - max(yl >> sy, r0) + 1) : 0;
-                if (kMasked && k > 0 &&
-                    !range_hits(act_lo, act_hi, max(xl >> sx, c0) - c0, min(xh >> sx, c1 - 1) - c0))
-                    k = 0;
+                // the tiles of its rectangle inside this wave's row and columns
+                // (masked form: the active ones among them)
+                const int xa = max(xl >> sx, c0) - c0, xb = min(xh >> sx, c1 - 1) - c0;
+                if (kMasked) {
+                    if (xa <= xb) {
+                        uint64_t lo64 = act_lo, hi64 = act_hi;
+                        clip_range(lo64, hi64, xa, xb);
+                        k = __popcll(lo64) + __popcll(hi64);
+                    }
+                } else {
+                    k = max(xb - xa + 1, 0);
+                }
             }
             const int incl = wave_scan_add(k);
             const int K = __builtin_amdgcn_readlane(incl, kEmitWave - 1);
@@ -498,17 +541,16 @@ __global__ __launch_bounds__(kEmitWave) void k_bin_emit(const ViewDev *__restric
                 unpack_range(__uint_as_float(L.rx[own]), xl, xh);
                 unpack_range(__uint_as_float(L.ry[own]), yl, yh);
                 const uint32_t g = L.rg[own];
-                const int tx0 = max(xl >> sx, c0), ty0 = max(yl >> sy, r0);
-                const int nx = min(xh >> sx, c1 - 1) - tx0 + 1;
-                // j / nx as floor((j + 1/2) r) with r within one ulp of 1/nx:
-                // exact for nx * ny <= 8160 (checked exhaustively on the host;
-                // only groups of several tile rows divide)
-                const int dy = kEmitRows == 1 ? 0 : (int)(((float)j + 0.5f) * __builtin_amdgcn_rcpf((float)nx));
-                const int tx = tx0 + (j - dy * nx), ty = kEmitRows == 1 ? r0 : ty0 + dy;
-                const int tc = kEmitRows == 1 ? tx - c0 : (ty - r0) * ncols + (tx - c0);
-                const bool in = item && (unsigned)tc < (unsigned)ntiles;
-                const int t = in ? tc : 0;
-                const bool on = in && tile_on<kMasked>(L.act, t);
+                const int tx0 = max(xl >> sx, c0), ty = r0;
+                int tc = tx0 - c0 + j;                 // tile column within the wave
+                if (kMasked) {
+                    uint64_t lo64 = act_lo, hi64 = act_hi;
+                    clip_range(lo64, hi64, tx0 - c0, min(xh >> sx, c1 - 1) - c0);
+                    tc = item ? nth_bit(lo64, hi64, j) : 0;
+                }
+                const int tx = c0 + tc;
+                const bool on = item && (unsigned)tc < (unsigned)ntiles;
+                const int t = on ? tc : 0;
                 const uint32_t val = g | (quad_mask(tx, ty, xl, xh, yl, yh, sx, sy) << 28);
                 // Lanes on the same tile: each lane ORs its bit into its tile's
                 // 64-bit LDS mask (cleared just before), then reads it back.
@@ -552,6 +594,7 @@ __global__ __launch_bounds__(kEmitWave) void k_bin_emit(const ViewDev *__restric
         }
         wave_sync();   // the queue is refilled by the next batch
     }
+    if (direct) return;
     // 3. the last, partly filled line of every tile whose segment ends inside one
     for (int t4 = 0; t4 < ntiles; t4 += kEmitWave) {
         const int t = t4 + lane;

@@ -223,3 +223,30 @@ def test_projection_scale_range(log_scale):
     assert st["n_projected"] > 0
     err = np.abs(s.cpu().numpy().astype(np.float64) - ref["s"]) - (1e-5 * ref["s"] + 1e-12)
     assert err.max() <= 0
+
+
+@pytest.mark.parametrize("per_row", [1, 15, 16, 17, 40, 80])
+def test_masked_emission_tiles_per_row(per_row):
+    """Ray masks with few active tiles per tile row (emitted tile by tile, up to
+    16) and with more (the general form): the selected rays' objectives equal the
+    unmasked render's bit for bit, the others read 0."""
+    import synth
+    import paper_2607_02721_amd as gs
+    W, H = 1280, 96
+    sc = synth.make_cluster_scene(30_000, 18, 1)
+    vw = synth.make_orbit_views(2, 19, W, H)
+    rng = np.random.default_rng(per_row)
+    keep = np.zeros((2, H, W), bool)
+    for v in range(2):
+        for ty in range(H // 16):
+            for tx in rng.choice(W // 16, per_row, replace=False):
+                y, x = 16 * ty + 8 * rng.integers(2), 16 * tx + 8 * rng.integers(2)
+                keep[v, y:y + 8, x:x + 8] = True
+    mask = torch.as_tensor(synth.pack_bits(keep.reshape(-1)).view(np.int32)).cuda()
+    d = gs.DeviceScene.from_scene(sc)
+    whole = gs.render_objective(d, vw, diag=False)["per_ray"]
+    part = gs.render_objective(d, vw, ray_mask=mask, diag=False)["per_ray"]
+    on = torch.as_tensor(keep.reshape(-1)).cuda()
+    assert float(whole[on].max()) > 0
+    assert torch.equal(part[on], whole[on])
+    assert float(part[~on].abs().max()) == 0
