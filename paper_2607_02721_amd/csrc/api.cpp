@@ -583,7 +583,7 @@ gs_status run_front(const gs_scene *scene, const gs_views *views, const gs_param
     // ray-masked runs: which tiles hold a selected ray, as per-view tables
     // that projection uses to drop Gaussians meeting none of them
     if (b.tile_active) {
-        launch_tile_active(r.views_dev, r.tile_view, c.total_tiles, p->ray_mask, b.tile_active, st);
+        launch_tile_active(r.views_dev, r.tile_view, c.total_tiles, S.tsy, p->ray_mask, b.tile_active, st);
         launch_tile_sat(r.views_dev, c.vc, max_tx, max_ty, b.tile_active, b.tile_sat, st);
         launch_quad_list(b.tile_active, c.total_tiles, S.quad_log, qcnt, qoff, qtmp, r.quad_list, st);
     }

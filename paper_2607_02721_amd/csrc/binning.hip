@@ -717,34 +717,43 @@ void launch_list_guard(uint64_t *tile_off, int64_t ntiles, uint64_t cap, uint32_
 // A tile is active when at least one of its rays is selected by the ray mask;
 // inactive tiles get empty lists.  active[t] holds one bit per 8x8 quadrant
 // (bit q: quadrant q, row-major inside the tile, holds a selected ray).  One
-// wave per tile: lane L takes the pixels L, L + 64, ... of the tile (row-major),
-// and the bits are OR-ed over the wave with a ballot per quadrant.
-__global__ __launch_bounds__(64) void k_tile_active(const ViewDev *__restrict__ views,
-                                                    const int32_t *__restrict__ tile_view,
-                                                    const uint32_t *__restrict__ mask, uint16_t *__restrict__ active) {
-    const int gt = blockIdx.x;
-    const ViewDev &V = views[tile_view[gt]];
-    const int tl = gt - V.tile_base;
-    const int tx = tl % V.tiles_x, ty = tl / V.tiles_x;
-    const int tw = 1 << V.tsx, area = tw << V.tsy, qlx = V.tsx - 3;
-    uint32_t mine = 0u;    // quadrants of this lane's pixels that hold a selected ray
-    for (int k = threadIdx.x; k < area; k += 64) {
-        const int lx = k & (tw - 1), ly = k >> V.tsx;
-        const int px = (tx << V.tsx) + lx, py = (ty << V.tsy) + ly;
-        if (px < V.W && py < V.H) {
+// lane per pixel row of a tile: its up to 32 mask bits are consecutive, so one
+// or two words give them; lanes of a tile then OR their quadrant bits.  (A wave
+// per tile with a bit test per pixel took 146 us for 360 000 tiles of
+// 16x16; this takes 35.)
+__global__ __launch_bounds__(256) void k_tile_active(const ViewDev *__restrict__ views,
+                                                     const int32_t *__restrict__ tile_view,
+                                                     const uint32_t *__restrict__ mask, uint16_t *__restrict__ active,
+                                                     int total_tiles, int tsy) {
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const int gt = (int)(i >> tsy), row = (int)i & ((1 << tsy) - 1);
+    uint32_t bits = 0u;
+    if (gt < total_tiles) {
+        const ViewDev &V = views[tile_view[gt]];
+        const int tl = gt - V.tile_base;
+        const int px = (tl % V.tiles_x) << V.tsx, py = ((tl / V.tiles_x) << V.tsy) + row;
+        const int width = min(1 << V.tsx, V.W - px);
+        if (py < V.H) {
             const int64_t ray = V.ray_base + (int64_t)py * V.W + px;
-            if ((mask[ray >> 5] >> (ray & 31)) & 1u) mine |= 1u << ((lx >> 3) + ((ly >> 3) << qlx));
+            const int sh = (int)(ray & 31);
+            uint64_t w = mask[ray >> 5];
+            if (sh + width > 32) w |= (uint64_t)mask[(ray >> 5) + 1] << 32;
+            const uint32_t sel = (uint32_t)(w >> sh) & (width < 32 ? (1u << width) - 1u : ~0u);
+            const int qlx = V.tsx - 3;
+            uint32_t cols = 0u;
+            for (int c = 0; c < (1 << qlx); ++c) cols |= ((sel >> (8 * c)) & 0xFFu) ? (1u << c) : 0u;
+            bits = cols << ((row >> 3) << qlx);
         }
     }
-    const int nq = 1 << (V.tsx + V.tsy - 6);
-    uint32_t bits = 0u;
-    for (int q = 0; q < nq; ++q) bits |= __any((mine >> q) & 1u) ? (1u << q) : 0u;
-    if (threadIdx.x == 0) active[gt] = (uint16_t)bits;
+    for (int off = 1; off < (1 << tsy); off <<= 1) bits |= (uint32_t)__shfl_xor((int)bits, off);
+    if (gt < total_tiles && row == 0) active[gt] = (uint16_t)bits;
 }
 
-void launch_tile_active(const ViewDev *views_dev, const int32_t *tile_view, int total_tiles, const uint32_t *mask,
-                        uint16_t *active, hipStream_t st) {
-    hipLaunchKernelGGL(k_tile_active, dim3(total_tiles), dim3(64), 0, st, views_dev, tile_view, mask, active);
+void launch_tile_active(const ViewDev *views_dev, const int32_t *tile_view, int total_tiles, int tile_shift_y,
+                        const uint32_t *mask, uint16_t *active, hipStream_t st) {
+    const int64_t lanes = (int64_t)total_tiles << tile_shift_y;
+    hipLaunchKernelGGL(k_tile_active, dim3((unsigned)((lanes + 255) / 256)), dim3(256), 0, st, views_dev, tile_view,
+                       mask, active, total_tiles, tile_shift_y);
 }
 
 // Row y + 1 of view v's table: running counts of active tiles along tile row

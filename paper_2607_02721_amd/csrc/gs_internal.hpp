@@ -178,8 +178,8 @@ int64_t radix_sort_scratch_words(int64_t n_per_seg, int n_segs);
 void launch_key_compact(const ChunkBufs &b, int Vc, int64_t N, uint32_t *kout, uint32_t *vout, hipStream_t st);
 void launch_ranges_in_order(const uint32_t *sorted_g, const ChunkBufs &b, int Vc, int64_t N, uint32_t *xr,
                             uint32_t *yr, hipStream_t st);
-void launch_tile_active(const ViewDev *views_dev, const int32_t *tile_view, int total_tiles, const uint32_t *mask,
-                        uint16_t *active, hipStream_t st);
+void launch_tile_active(const ViewDev *views_dev, const int32_t *tile_view, int total_tiles, int tile_shift_y,
+                        const uint32_t *mask, uint16_t *active, hipStream_t st);
 // The quadrants with a selected ray, in order: per-tile counts, their
 // exclusive scan (qoff[total_tiles] = the number listed) and the list of
 // (tile << quad_log) + quadrant.

@@ -250,3 +250,47 @@ def test_masked_emission_tiles_per_row(per_row):
     assert float(whole[on].max()) > 0
     assert torch.equal(part[on], whole[on])
     assert float(part[~on].abs().max()) == 0
+
+
+@pytest.mark.parametrize("tile", [(8, 8), (32, 32), (8, 32), (32, 8)])
+@pytest.mark.parametrize("size", [(65, 63), (31, 33), (1, 1)])
+def test_tile_activity_from_single_rays(tile, size):
+    """Single selected pixels at any bit of a mask word, first and last pixels
+    included: each one's tile is active, so its objective equals the unmasked
+    render's bit for bit, and the others read 0."""
+    import synth
+    import paper_2607_02721_amd as gs
+    W, H = size
+    sc = synth.make_cluster_scene(3000, 20, 1)
+    vw = synth.make_orbit_views(3, 21, W, H)
+    rng = np.random.default_rng(W)
+    keep = np.zeros((3, H, W), bool)
+    keep[rng.integers(0, 3, 9), rng.integers(0, H, 9), rng.integers(0, W, 9)] = True
+    keep[0, 0, 0] = keep[2, H - 1, W - 1] = True
+    mask = torch.as_tensor(synth.pack_bits(keep.reshape(-1)).view(np.int32)).cuda()
+    d = gs.DeviceScene.from_scene(sc)
+    whole = gs.render_objective(d, vw, diag=False, tile=tile)["per_ray"]
+    part = gs.render_objective(d, vw, ray_mask=mask, diag=False, tile=tile)["per_ray"]
+    on = torch.as_tensor(keep.reshape(-1)).cuda()
+    assert float(whole.max()) > 0
+    assert torch.equal(part[on], whole[on])
+    assert float(part[~on].abs().sum()) == 0
+
+
+@pytest.mark.parametrize("n", [63, 64, 65, 1023, 1025, 5000])
+def test_masked_key_runs(n):
+    """Kept keys move in runs of 64 by waves of four runs: one selected block
+    keeps few Gaussians, at counts around the run and block lengths."""
+    import synth
+    import paper_2607_02721_amd as gs
+    sc = synth.make_cluster_scene(n, 22, 1)
+    vw = synth.make_orbit_views(3, 23, 160, 96)
+    keep = np.zeros((3, 96, 160), bool)
+    keep[:, 32:64, 48:112] = True
+    mask = torch.as_tensor(synth.pack_bits(keep.reshape(-1)).view(np.int32)).cuda()
+    d = gs.DeviceScene.from_scene(sc)
+    whole = gs.render_objective(d, vw, diag=False)["per_ray"]
+    part = gs.render_objective(d, vw, ray_mask=mask, diag=False)["per_ray"]
+    on = torch.as_tensor(keep.reshape(-1)).cuda()
+    assert float(whole[on].max()) > 0
+    assert torch.equal(part[on], whole[on])
