@@ -376,7 +376,7 @@ void mlp_init(float *params, uint64_t seed, hipStream_t st);
 void mlp_forward(const float *P, const float *feat, const float *norm, int64_t n, float *y, void *scratch,
                  int64_t rows, hipStream_t st);
 // fp32: products in FP32 (v_mfma_f32_16x16x4_f32) with FP32 activations
-// instead of BF16 (a precision mode of the same kernels).
+// instead of BF16 (a precision mode, one kernel per product).
 void mlp_train_step(float *P, float *adam, int64_t step, float lr, const float *feat, const float *norm,
                     const float *y, int64_t n, float *loss, float *grad_out, void *scratch, int64_t rows,
                     hipStream_t st, bool fp32 = false);

@@ -518,7 +518,7 @@ __global__ __launch_bounds__(64, 4) void k_knn(SceneDev sc, Tree T, float *__res
 // The feature rows, 64 points per block: the attribute planes are read in
 // index order (a wave reads 64 consecutive values of a plane), transposed in
 // LDS (65 floats per row: no bank conflicts) and stored as whole rows: 0.12 ms
-// for 10^6 points, 4.1 TB/s.  (Assembled by the search itself, at scattered
+// for 10^6 points, 4.3 TB/s.  (Assembled by the search itself, at scattered
 // indices, a row takes a whole line of every plane for each 4 bytes.)
 typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 __global__ __launch_bounds__(256) void k_feature_rows(SceneDev sc, const float *__restrict__ nf,

@@ -294,3 +294,75 @@ def test_masked_key_runs(n):
     on = torch.as_tensor(keep.reshape(-1)).cuda()
     assert float(whole[on].max()) > 0
     assert torch.equal(part[on], whole[on])
+
+
+def _mlp_case(n, seed):
+    from paper_2607_02721_amd import learned
+    rng = np.random.default_rng(seed)
+    feat = torch.as_tensor(rng.normal(size=(n, 64)).astype(np.float32)).cuda()
+    target = torch.as_tensor(rng.normal(size=n).astype(np.float32)).cuda()
+    prop = learned.Proposal(seed=seed)
+    prop.set_norm(learned.feature_stats(feat) if n > 1 else torch.stack(
+        [torch.zeros(64), torch.ones(64)]).reshape(-1).cuda())
+    return learned, prop, feat, target
+
+
+def _mlp_bf16(params, x, target):
+    """Network, loss and gradient with the roundings of the BF16 step (weights,
+    activations and dZ to BF16), everything else in FP64."""
+    def r(t):
+        return t.to(torch.float32).to(torch.bfloat16).double()
+    P = params.double().cpu()
+    W, off = [], 0
+    for o, i in ((256, 64), (256, 256), (256, 256), (1, 256)):
+        W.append((r(P[off:off + o * i].reshape(o, i)), P[off + o * i:off + o * i + o]))
+        off += o * i + o
+    h, zs, hs = r(x), [], [r(x)]
+    for w, b in W[:3]:
+        z = h @ w.T + b
+        zs.append(z)
+        h = r(z * torch.sigmoid(z))
+        hs.append(h)
+    out = h @ W[3][0].T + W[3][1]
+    e = out[:, 0] - target.double().cpu()
+    n = len(e)
+    dy = 2 * e / n
+
+    def dsilu(z):
+        s = torch.sigmoid(z)
+        return s * (1 + z * (1 - s))
+    g4 = torch.cat([dy @ hs[3], dy.sum()[None]])
+    dz = r(dy[:, None] * W[3][0] * dsilu(zs[2]))
+    grads = []
+    for k in (2, 1, 0):
+        grads.insert(0, torch.cat([(dz.T @ hs[k]).reshape(-1), dz.sum(0)]))
+        if k:
+            dz = r((dz @ W[k][0]) * dsilu(zs[k - 1]))
+    return out[:, 0], (e * e).sum() / n, torch.cat(grads + [g4])
+
+
+# n: one row, the 64-row block of training and the 128-row block of inference
+# and their neighbours, two ranges of the weight gradients with a short last one,
+# more blocks than inference has in flight (33 000).
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 127, 129, 1025, 1663, 33_000])
+def test_fused_network_row_counts(n):
+    """Prediction, loss and gradient at the edges of the row blocks.  FP32
+    accumulation leaves about 1e-6; that moves a value across a rounding
+    boundary of BF16, 2^-8 apart, with a probability of 2e-6 / 2^-8 = 5e-4, and
+    the value is then 2^-8 off: 2^-8 sqrt(5e-4) = 9e-5 of a layer's norm, six
+    layers 2.2e-4.  A single row has few values to average over: 1e-3; the loss
+    goes as the square of differences of the size of the outputs: 4e-3."""
+    learned, prop, feat, target = _mlp_case(n, 3)
+    norm = prop.norm.reshape(2, 64)
+    x = ((feat - norm[0]) * norm[1]).cpu()
+    want_y, want_loss, want_g = _mlp_bf16(prop.params, x, target)
+    y = prop.predict(feat).double().cpu()
+    loss, g = prop.gradient(feat, target)
+    assert float((y - want_y).norm() / want_y.norm()) <= 1e-3
+    assert abs(float(loss) - float(want_loss)) <= 4e-3 * float(want_loss)
+    assert float((g.double().cpu() - want_g).norm() / want_g.norm()) <= 1e-3
+    # one Adam step with the gradient returned equals the gradient call's
+    p0, g2 = prop.params.clone(), torch.empty_like(g)
+    loss2 = prop.train_step(feat, target, lr=1e-3, grad=g2)
+    assert torch.equal(g2, g) and torch.equal(loss2, loss)
+    assert float((prop.params - p0).abs().max()) <= 1.01e-3
