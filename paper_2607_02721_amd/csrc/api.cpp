@@ -1086,7 +1086,11 @@ gs_status gs_render_objective(const gs_scene *scene, const gs_views *views, cons
             if (per_ray) launch_fill_u32((uint32_t *)(per_ray + S.ray_base[c.v0]), 0u, (int64_t)c.rays, st);
             a.quad_list = r.quad_list;
             a.n_listed = r.n_listed;
+        } else if (order_pays((int64_t)a.total_tiles << a.region_log)) {
+            launch_tile_order(a, r.tile_order, r.order_classes, st);
+            a.tile_order = r.tile_order;
         }
+        a.by_quads = quads_pay((int64_t)a.total_tiles << a.region_log);
         if (objective != GS_OBJ_TRUE) {
             // w_max (1 without weights) bounds every later fixed-objective term
             uint64_t *wmax = (uint64_t *)(r.view_sums + 3 * (size_t)c.vc);

@@ -366,3 +366,28 @@ def test_fused_network_row_counts(n):
     loss2 = prop.train_step(feat, target, lr=1e-3, grad=g2)
     assert torch.equal(g2, g) and torch.equal(loss2, loss)
     assert float((prop.params - p0).abs().max()) <= 1.01e-3
+
+
+@pytest.mark.parametrize("mode", ["rgbsum", "l2"])
+@pytest.mark.parametrize("tile", [(16, 16), (32, 32), (8, 8), (16, 8)])
+def test_objective_by_regions_and_by_quadrants(mode, tile):
+    """The full and fixed objectives of one call by regions (more than 32 768,
+    ragged view sizes) and of the same views in calls by quadrants: the same
+    bits per ray and per view."""
+    import synth
+    import paper_2607_02721_amd as gs
+    sc = synth.make_cluster_scene(8000, 24, 1)
+    per_view = -(-636 // max(16, tile[0])) * -(-412 // max(16, tile[1])) * max(1, 256 // (tile[0] * tile[1]))
+    n_views = 33_000 // per_view + 15
+    vw = synth.make_orbit_views(n_views, 25, 636, 412)
+    d = gs.DeviceScene.from_scene(sc)
+    rng = np.random.default_rng(0)
+    wt = torch.as_tensor(rng.exponential(size=8000) * (rng.random(8000) < 0.3)).cuda()
+    qm = {"rgbsum": gs.QUERY_RGBSUM, "l2": gs.QUERY_L2}[mode]
+    for weights, objective in ((None, gs.OBJ_FULL), (wt, gs.OBJ_FULL), (wt, gs.OBJ_FIXED)):
+        kw = dict(query_mode=qm, diag=False, tile=tile)
+        every = gs.render_objective(d, vw, weights, objective, **kw)
+        each = gs.render_objective(d, vw, weights, objective, max_views_per_chunk=1, **kw)
+        assert float(every["per_ray"].max()) > 0
+        assert torch.equal(every["per_ray"], each["per_ray"])
+        assert torch.equal(every["per_view"], each["per_view"])
