@@ -159,34 +159,56 @@ __device__ __forceinline__ bool ray_selected(const uint32_t *mask, int64_t ray) 
 // P = a' u^2 + g' dy^2 (a', g' < 0), u = dx + beta dy, with (dx, dy) the
 // centre minus the mean and centres at 0.5 ... 7.5 in quadrant coordinates.
 // The minimum of -P over the continuous square [0.5, 7.5]^2 bounds the
-// centres' values from below; it sits at the mean if the mean is inside,
-// else on an edge (a one-dimensional quadratic, clamped).  An entry is
-// dropped only when that minimum exceeds -cut by more than `err`, a bound
-// (with a wide safety factor) on the float32 rounding of this test and of
-// the per-pixel one, so a dropped entry contributes exactly nothing anyway:
-// pass 1, pass 2 and the objectives give bit-identical results either way.
-__device__ __forceinline__ bool quad_hit(float mx, float my, float beta, float ap, float gp, float cut) {
-    const float A = -ap, G = -gp, C = -cut;
-    const float x0 = 0.5f - mx, x1 = 7.5f - mx, y0 = 0.5f - my, y1 = 7.5f - my;
-    if (x0 <= 0.0f && x1 >= 0.0f && y0 <= 0.0f && y1 >= 0.0f) return true;
-    auto q = [&](float dx, float dy) {
-        const float u = fmaf(beta, dy, dx);
-        return (A * u) * u + (G * dy) * dy;
-    };
-    // edges dy = y0, y1: best dx = -beta dy, clamped to [x0, x1] (x0 < x1: a
-    // median of three is the clamp)
-    float best = fminf(q(__builtin_amdgcn_fmed3f(-beta * y0, x0, x1), y0),
-                       q(__builtin_amdgcn_fmed3f(-beta * y1, x0, x1), y1));
-    // edges dx = x0, x1: best dy = -A beta dx / (A beta^2 + G)
-    const float k = -(A * beta) * __builtin_amdgcn_rcpf(fmaf(A * beta, beta, G));
-    best = fminf(best, q(x0, __builtin_amdgcn_fmed3f(k * x0, y0, y1)));
-    best = fminf(best, q(x1, __builtin_amdgcn_fmed3f(k * x1, y0, y1)));
-    const float S = fabsf(mx) + fabsf(my) + 16.0f;
-    // (v_sqrt_f32, within about an ulp, is ample for a bound this loose)
+// centres' values from below; it sits at the mean if the mean is inside, else
+// on an edge that faces the mean (from any other point of the square the way
+// to the mean leads through the square, and -P falls along it).  So two lines
+// are enough, x = xe and y = ye for the square's nearest coordinates to the mean:
+// the minimum on a facing edge is a one-dimensional quadratic's, clamped, and a
+// coordinate that the square spans gives a point inside it, which takes nothing
+// from the bound.  (All four edges and a test for a mean inside took about
+// twice the instructions, most of pass 1's: HIT_OLD us at 1M Gaussians x 100
+// views, HIT_NEW so.)  An entry is dropped only when that minimum exceeds -cut
+// by more than `err`, a bound (with a wide safety factor) on the float32 rounding
+// of this test and of the per-pixel one, so a dropped entry contributes exactly
+// nothing anyway: pass 1, pass 2 and the objectives give bit-identical results
+// either way.
+//
+// hit_bound: -cut + err for a mean whose offsets from the quadrant origin sum
+// to at most S - 16 in magnitude (v_sqrt_f32, within about an ulp, is ample for
+// a bound this loose); hit_slope: best dy = slope dx on an edge x = const,
+// -A beta / (A beta^2 + G).
+__device__ __forceinline__ float hit_bound(float S, float beta, float A, float G, float C) {
     const float err = 3.814697265625e-6f /* 2^-18 */ * S *
                           ((1.0f + fabsf(beta)) * __builtin_amdgcn_sqrtf(A * C) + __builtin_amdgcn_sqrtf(G * C)) +
                       1e-4f * C;
-    return best <= C + err;
+    return C + err;
+}
+__device__ __forceinline__ float hit_slope(float beta, float A, float G) {
+    return -(A * beta) * __builtin_amdgcn_rcpf(fmaf(A * beta, beta, G));
+}
+
+// The square's interval [lo, hi] of offsets from the mean along one axis and
+// the offset nearest to the mean.
+struct HitSpan {
+    float lo, hi, near;
+    __device__ __forceinline__ explicit HitSpan(float m)
+        : lo(0.5f - m), hi(7.5f - m), near(__builtin_amdgcn_fmed3f(0.0f, 0.5f - m, 7.5f - m)) {}
+};
+
+// Smallest -P on the two lines (a median of three is the clamp).
+__device__ __forceinline__ float hit_min(const HitSpan &X, const HitSpan &Y, float beta, float A, float G,
+                                         float slope) {
+    const float dy = __builtin_amdgcn_fmed3f(slope * X.near, Y.lo, Y.hi);
+    const float ux = fmaf(beta, dy, X.near);
+    const float vx = -beta * Y.near;
+    const float uy = __builtin_amdgcn_fmed3f(vx, X.lo, X.hi) - vx;
+    return fminf(fmaf(A * ux, ux, (G * dy) * dy), fmaf(A * uy, uy, (G * Y.near) * Y.near));
+}
+
+__device__ __forceinline__ bool quad_hit(float mx, float my, float beta, float ap, float gp, float cut) {
+    const float A = -ap, G = -gp;
+    return hit_min(HitSpan(mx), HitSpan(my), beta, A, G, hit_slope(beta, A, G)) <=
+           hit_bound(fabsf(mx) + fabsf(my) + 16.0f, beta, A, G, -cut);
 }
 
 // The staged geometry of an entry: with u = dx + beta dy and the exponent's
@@ -443,6 +465,27 @@ __device__ __forceinline__ GlobalPtr<T> as_global(const T *p) {
 }
 typedef float GeoHalf __attribute__((ext_vector_type(4)));   // half of a GeoRec
 
+// Bits of the alive quadrants of a region that an entry (its list word raw,
+// its mean relative to the first and the second quadrant column and row) reaches,
+// as quad_hit for each; the bound is one for all four (the second column and
+// row lie kQuad further, so S grows by 2 kQuad).
+__device__ __forceinline__ uint32_t region_hits(uint32_t raw, const uint32_t (&qbit)[4], uint32_t alive, float mx0,
+                                                float my0, float mx1, float my1, float beta, float ap, float gp,
+                                                float cut) {
+    const float A = -ap, G = -gp;
+    const float slope = hit_slope(beta, A, G);
+    const float bound = hit_bound(fabsf(mx0) + fabsf(my0) + (16.0f + 2.0f * kQuad), beta, A, G, -cut);
+    const HitSpan X[2] = {HitSpan(mx0), HitSpan(mx1)}, Y[2] = {HitSpan(my0), HitSpan(my1)};
+    uint32_t h = 0u;
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+        if ((alive >> k) & 1u) {
+            const bool hit = hit_min(X[k & 1], Y[k >> 1], beta, A, G, slope) <= bound;
+            h |= hit && (raw & qbit[k]) ? 1u << k : 0u;
+        }
+    return h;
+}
+
 // An entry staged for a region: g = (mean x, y relative to the region's
 // first quadrant, beta, a'), c = (g', log2 alpha, colour sum, cut + log2
 // alpha), m1 = mean relative to the second quadrant column / row.
@@ -603,11 +646,7 @@ __global__ __launch_bounds__(kWave) void k_pass1_region(CompositeArgs a) {
             my0 = (r0.y - fy0) + r0.w;
             mx1 = (r0.x - fx1) + r0.z;
             my1 = (r0.y - fy1) + r0.w;
-#pragma unroll
-            for (int k = 0; k < 4; ++k)
-                if (((alive >> k) & 1u) && (raw & R.qbit[k]) &&
-                    quad_hit((k & 1) ? mx1 : mx0, (k >> 1) ? my1 : my0, r1.x, r1.y, r1.z, cut))
-                    h |= 1u << k;
+            h = region_hits(raw, R.qbit, alive, mx0, my0, mx1, my1, r1.x, r1.y, r1.z, cut);
         }
         const uint64_t bal = __ballot(h != 0u);
         const int n = __popcll(bal);
@@ -1795,11 +1834,7 @@ __global__ __launch_bounds__(kWave) void k_objective_region(CompositeArgs a, Obj
             my0 = (r0.y - fy0) + r0.w;
             mx1 = (r0.x - fx1) + r0.z;
             my1 = (r0.y - fy1) + r0.w;
-#pragma unroll
-            for (int k = 0; k < 4; ++k)
-                if (((alive >> k) & 1u) && (raw & R.qbit[k]) &&
-                    quad_hit((k & 1) ? mx1 : mx0, (k >> 1) ? my1 : my0, r1.x, r1.y, r1.z, cut))
-                    h |= 1u << k;
+            h = region_hits(raw, R.qbit, alive, mx0, my0, mx1, my1, r1.x, r1.y, r1.z, cut);
         }
         const uint64_t bal = __ballot(h != 0u);
         const int n = __popcll(bal);
