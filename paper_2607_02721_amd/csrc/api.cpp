@@ -567,6 +567,7 @@ gs_status run_front(const gs_scene *scene, const gs_views *views, const gs_param
         max_tx = std::max(max_tx, V.tiles_x);
         max_ty = std::max(max_ty, V.tiles_y);
     }
+    b.half_ranges = half_ranges_fit(max_tx, max_ty);
     HIP_TRY(hipMemcpyAsync(r.views_dev, hv.data(), sizeof(ViewDev) * c.vc, hipMemcpyHostToDevice, st));
     HIP_TRY(hipMemcpyAsync(r.tile_view, htv.data(), sizeof(int32_t) * c.total_tiles, hipMemcpyHostToDevice, st));
     launch_fill_u32(b.nvis, 0u, 2 * (int64_t)c.vc, st);
@@ -1664,6 +1665,7 @@ void carve_scene(PlanScene &ps, Carve &cv) {
 void enqueue_front(const gs_plan *P, PlanScene &ps, hipStream_t st) {
     const int64_t N = ps.S.N;
     ChunkBufs &b = ps.b;
+    b.half_ranges = half_ranges_fit(ps.max_tx, ps.max_ty);
     launch_fill_u32(b.nvis, 0u, 2 * (int64_t)ps.c.vc, st);
     launch_fill_u32(b.bin_count, 0u, ps.nbins, st);
     launch_fill_u64(b.counters, 0ull, CNT_WORDS, st);

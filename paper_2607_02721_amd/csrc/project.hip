@@ -26,7 +26,8 @@
 //        its own, so that the compositing passes gather 4-byte values
 //   XY = (x-range, y-range): the inclusive pixel ranges whose centres can
 //        fall inside the r-ellipse, packed as int16 (lo | hi << 16); an
-//        8-byte array of its own, gathered in depth order by k_ranges_in_order
+//        8-byte array of its own, gathered in depth order by k_ranges_in_order;
+//        or in half tiles, a 4-byte array (ChunkBufs::half_ranges)
 //   R3 = (c_R, c_G, c_B, 0), written for per-channel queries only.
 #include "gs_internal.hpp"
 
@@ -127,7 +128,7 @@ __device__ __forceinline__ uint32_t pack_range(int lo, int hi) {
 template <int kDeg, int kFmt>
 __global__ __launch_bounds__(kProjThreads) void k_project(SceneDev sc, const ViewDev *__restrict__ views, int Vc,
                                                  ProjParams pp, GeoRec *__restrict__ geo, float *__restrict__ CB,
-                                                 uint2 *__restrict__ XY,
+                                                 uint2 *__restrict__ XY, int half_ranges,
                                                  float4 *__restrict__ R3, uint32_t *__restrict__ keys,
                                                  uint4 *__restrict__ part, uint64_t *__restrict__ counters,
                                                  const uint32_t *__restrict__ tile_sat) {
@@ -270,7 +271,13 @@ __global__ __launch_bounds__(kProjThreads) void k_project(SceneDev sc, const Vie
                 else
                     cbar = (float)(c[0] + c[1] + c[2]);
                 r3 = make_float4((float)c[0], (float)c[1], (float)c[2], 0.0f);
-                xy = make_uint2(pack_range((int)xl, (int)xh), pack_range((int)yl, (int)yh));
+                if (half_ranges) {
+                    const int hx = V.tsx - 1, hy = V.tsy - 1;
+                    xy.x = (uint32_t)((int)xl >> hx) | (uint32_t)((int)xh >> hx) << 8 |
+                           (uint32_t)((int)yl >> hy) << 16 | (uint32_t)((int)yh >> hy) << 24;
+                } else {
+                    xy = make_uint2(pack_range((int)xl, (int)xh), pack_range((int)yl, (int)yh));
+                }
                 keep = true;
                 if (tile_sat) {
                     // active tiles inside the tile rectangle [x0, x1) x [y0, y1)
@@ -288,7 +295,10 @@ __global__ __launch_bounds__(kProjThreads) void k_project(SceneDev sc, const Vie
             geo[o].m = r0;
             geo[o].q = r1;
             CB[o] = cbar;
-            XY[o] = xy;
+            if (half_ranges)
+                ((uint32_t *)XY)[o] = xy.x;
+            else
+                XY[o] = xy;
             if (R3) R3[o] = r3;
         }
         if (in_range) keys[o] = keep ? __float_as_uint((float)pz) : kInvisibleKey;
@@ -410,7 +420,7 @@ static void launch_t(const SceneDev &sc, const ViewDev *views_dev, int Vc, const
     constexpr int kProjViews = 25;
     const int groups = std::max(1, (Vc + kProjViews - 1) / kProjViews);
     hipLaunchKernelGGL((k_project<kDeg, kFmt>), dim3((unsigned)blocks, (unsigned)groups), dim3(kProjThreads), 0, st, sc, views_dev, Vc, pp, b.R,
-                       b.CB, b.XY, b.R3, b.key0, (uint4 *)b.proj_part, b.counters, b.tile_sat);
+                       b.CB, b.XY, b.half_ranges, b.R3, b.key0, (uint4 *)b.proj_part, b.counters, b.tile_sat);
     hipLaunchKernelGGL(k_proj_reduce, dim3((unsigned)Vc), dim3(kReduceThreads), 0, st, (uint4 *)b.proj_part, Vc, blocks,
                        b.nvis, b.cmax, b.kmin);
 }
@@ -462,9 +472,10 @@ void launch_project(const SceneDev &sc, const ViewDev *views_dev, int Vc, const 
     table[sc.format == 1 ? 1 : 0][sc.sh_degree](sc, views_dev, Vc, pp, b, st);
 }
 
-// Depth-ordered copy of each visible Gaussian's pixel ranges, so that the
-// binning kernels read them with unit stride: xr/yr[v*N + p] for position p
-// of view v's front-to-back order.
+// Depth-ordered copy of each visible Gaussian's ranges, so that the binning
+// kernels read them with unit stride: xr/yr[v*N + p] for position p of view v's
+// front-to-back order (kHalf: ranges in half tiles, xr only).
+template <bool kHalf>
 __global__ __launch_bounds__(256) void k_ranges_in_order(const uint32_t *__restrict__ sorted_g,
                                                          const uint2 *__restrict__ XY,
                                                          const uint32_t *__restrict__ nvis, int64_t N,
@@ -479,17 +490,23 @@ __global__ __launch_bounds__(256) void k_ranges_in_order(const uint32_t *__restr
     const int64_t p = (r % nbx) * 256 + threadIdx.x;
     if (p >= (int64_t)nvis[v]) return;
     const int64_t o = (int64_t)v * N;
-    const uint2 rg = XY[o + sorted_g[o + p]];
-    xr[o + p] = rg.x;
-    yr[o + p] = rg.y;
+    if (kHalf) {
+        xr[o + p] = ((const uint32_t *)XY)[o + sorted_g[o + p]];
+    } else {
+        const uint2 rg = XY[o + sorted_g[o + p]];
+        xr[o + p] = rg.x;
+        yr[o + p] = rg.y;
+    }
 }
 
 void launch_ranges_in_order(const uint32_t *sorted_g, const ChunkBufs &b, int Vc, int64_t N, uint32_t *xr,
                             uint32_t *yr, hipStream_t st) {
     const int64_t nbx = (N + 255) / 256;
     const int64_t blocks = nbx * (((int64_t)Vc + 7) / 8) * 8;
-    hipLaunchKernelGGL(k_ranges_in_order, dim3((unsigned)blocks), dim3(256), 0, st, sorted_g, b.XY, b.nvis, N, xr,
-                       yr, Vc);
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(256), 0, st, sorted_g, b.XY, b.nvis, N, xr, yr, Vc);
+    };
+    b.half_ranges ? go(k_ranges_in_order<true>) : go(k_ranges_in_order<false>);
 }
 
 }  // namespace gs

@@ -391,3 +391,27 @@ def test_objective_by_regions_and_by_quadrants(mode, tile):
         assert float(every["per_ray"].max()) > 0
         assert torch.equal(every["per_ray"], each["per_ray"])
         assert torch.equal(every["per_view"], each["per_view"])
+
+
+@pytest.mark.parametrize("size", [(2048, 40), (2049, 40), (40, 2048), (40, 2049), (1024, 24), (1025, 24)])
+def test_ranges_in_half_tiles_and_in_pixels(size):
+    """Views of 128 and 129 tiles along an axis (ranges in half tiles, a byte
+    each, and in pixels): tiles of 8, 16 and 32 pixels give the same bits, with
+    and without a ray mask."""
+    import synth
+    import paper_2607_02721_amd as gs
+    W, H = size
+    sc = synth.make_cluster_scene(4000, 26, 1)
+    vw = synth.make_orbit_views(2, 27, W, H)
+    rng = np.random.default_rng(W + H)
+    keep = rng.random((2, H, W)) < 0.002
+    mask = torch.as_tensor(synth.pack_bits(keep.reshape(-1)).view(np.int32)).cuda()
+    d = gs.DeviceScene.from_scene(sc)
+    whole = masked = None
+    for tile in ((8, 8), (16, 16), (32, 32)):
+        s, _ = gs.sensitivity(d, vw, tile=tile)
+        m, _ = gs.sensitivity(d, vw, ray_mask=mask, tile=tile)
+        assert float(s.max()) > 0
+        assert whole is None or torch.equal(s, whole)
+        assert masked is None or torch.equal(m, masked)
+        whole, masked = s, m
