@@ -64,22 +64,35 @@ __device__ __forceinline__ uint32_t wave_incl_scan_u32(uint32_t v) {
 constexpr int kSweepExtra = 4 * 256 * 2 + 4;
 constexpr uint32_t kFlagAgg = 1u << 30, kFlagPrefix = 2u << 30, kCountMask = (1u << 30) - 1u;
 
+// Sort tiles per histogram block: its counts go to the segment's by one atomic
+// per digit and pass, so a large sort takes several tiles per block (100
+// segments of 1M keys: 1 tile 180 us, 4 tiles 147, 8 tiles 157; keys loaded one at
+// a time 217), a small one, which would leave CUs idle, one.
+constexpr int kHistTiles = 4;
+constexpr int64_t kHistManyTiles = 8192;
 __global__ __launch_bounds__(kSortThreads) void k_radix_hist_all(const uint32_t *__restrict__ keys,
                                                                   int64_t n_per_seg, int passes,
                                                                   uint32_t *__restrict__ extra,
                                                                   const uint32_t *__restrict__ kbase,
-                                                                  const uint32_t *__restrict__ seg_len) {
+                                                                  const uint32_t *__restrict__ seg_len, int tiles) {
     __shared__ uint32_t cnt[4][256];
     const int seg = blockIdx.y, b = blockIdx.x;
     for (int i = threadIdx.x; i < 4 * 256; i += kSortThreads) (&cnt[0][0])[i] = 0;
     __syncthreads();
     const int64_t base = (int64_t)seg * n_per_seg;
     const int64_t len = seg_len ? (int64_t)seg_len[seg] : n_per_seg;
-    const int64_t lo = (int64_t)b * kSortTile;
-    const int64_t hi = min(lo + (int64_t)kSortTile, len);
-    for (int64_t i = lo + threadIdx.x; i < hi; i += kSortThreads) {
-        const uint32_t k = rebase(keys[base + i], kbase, seg);
-        for (int p = 0; p < passes; ++p) atomicAdd(&cnt[p][(k >> (8 * p)) & 255u], 1u);
+    const int64_t lo = (int64_t)b * tiles * kSortTile;
+    const int64_t hi = min(lo + (int64_t)tiles * kSortTile, len);
+    for (int64_t i = lo + threadIdx.x; i < hi; i += 8 * kSortThreads) {
+        uint32_t k[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) k[u] = i + u * kSortThreads < hi ? keys[base + i + u * kSortThreads] : 0u;
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            if (i + u * kSortThreads < hi) {
+                const uint32_t x = rebase(k[u], kbase, seg);
+                for (int p = 0; p < passes; ++p) atomicAdd(&cnt[p][(x >> (8 * p)) & 255u], 1u);
+            }
     }
     __syncthreads();
     uint32_t *gc = extra + (int64_t)seg * kSweepExtra;
@@ -108,7 +121,13 @@ __global__ __launch_bounds__(256) void k_radix_digit_base(uint32_t *__restrict__
     if (d < 4) e[8 * 256 + d] = 0u;
 }
 
-__global__ __launch_bounds__(kSortThreads) void k_radix_scatter(const uint32_t *__restrict__ kin,
+// What bounds it is latency (a tile's loads, 16 rounds of ranking, the look-back,
+// then its stores), so it lives on the blocks a CU holds: the keys and then the
+// values leave through one 16 KB buffer, which with 72 registers makes seven
+// blocks (through a buffer each, four: 662 us per pass at 100 segments of 1M keys,
+// 473 so; 20 segments of 248k 42 and 31).  Looking back at four blocks at a time
+// brought nothing (731).
+__global__ __launch_bounds__(kSortThreads, 7) void k_radix_scatter(const uint32_t *__restrict__ kin,
                                                                  const uint32_t *__restrict__ vin,
                                                                  uint32_t *__restrict__ kout,
                                                                  uint32_t *__restrict__ vout, int64_t n_per_seg,
@@ -120,14 +139,13 @@ __global__ __launch_bounds__(kSortThreads) void k_radix_scatter(const uint32_t *
                                                                  int n_segs) {
     // per wave and digit: the wave's count while ranking, then (thread d
     // rewrites its own column once it has read it) the block-local start of
-    // the wave's run of digit d; one array instead of two keeps the block
-    // under 40 KB of LDS, four blocks per CU
+    // the wave's run of digit d
     __shared__ uint32_t wcnt[4][256];
     uint32_t (*wbase)[256] = wcnt;
     __shared__ uint32_t dstart[256];     // block-local start of each digit
     __shared__ uint32_t gdst[256];       // global start of the block's run of each digit
     __shared__ uint32_t wsum4[4];        // digit counts of each wave's 64 digits
-    __shared__ uint32_t lkey[kSortTile], lval[kSortTile];
+    __shared__ uint32_t stage[kSortTile];   // the keys on their way out, then the values
     __shared__ int tick;
     // blocks go to the XCDs in turn (block i to XCD i mod 8): block i works
     // on segment 8 (i / 8 / nb) + i mod 8, so each segment's scattered lines
@@ -150,17 +168,26 @@ __global__ __launch_bounds__(kSortThreads) void k_radix_scatter(const uint32_t *
     // items of the segment to sort (the whole block leaves if it holds none)
     const int64_t len = seg_len ? (int64_t)seg_len[seg] : n_per_seg;
     if ((int64_t)b * kSortTile >= len) return;
-    for (int i = threadIdx.x; i < 4 * 256; i += kSortThreads) (&wcnt[0][0])[i] = 0;
-    __syncthreads();
     const int64_t base = (int64_t)seg * n_per_seg;
     const int64_t wlo = (int64_t)b * kSortTile + (int64_t)w * (kSortRounds * 64);
     uint32_t key[kSortRounds], val[kSortRounds], rank[kSortRounds];
 #pragma unroll
     for (int k = 0; k < kSortRounds; ++k) {
         const int64_t i = wlo + k * 64 + lane;
+        key[k] = i < len ? kin[base + i] : 0u;
+    }
+#pragma unroll
+    for (int k = 0; k < kSortRounds; ++k) {
+        const int64_t i = wlo + k * 64 + lane;
+        val[k] = i < len ? (vals_are_iota ? (uint32_t)i : vin[base + i]) : 0u;
+    }
+    for (int i = threadIdx.x; i < 4 * 256; i += kSortThreads) (&wcnt[0][0])[i] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kSortRounds; ++k) {
+        const int64_t i = wlo + k * 64 + lane;
         const bool ok = i < len;
-        key[k] = ok ? rebase(kin[base + i], kbase, seg) : 0u;
-        val[k] = ok ? (vals_are_iota ? (uint32_t)i : vin[base + i]) : 0u;
+        if (ok) key[k] = rebase(key[k], kbase, seg);
         const uint32_t d = (key[k] >> shift) & 255u;
         const uint64_t active = __ballot(ok);
         const uint64_t peers = match_digit(d, active);
@@ -220,31 +247,39 @@ __global__ __launch_bounds__(kSortThreads) void k_radix_scatter(const uint32_t *
         wbase[3][d] = start + c0 + c1 + c2;
     }
     __syncthreads();
-    // the block's keys in LDS in stable digit order, then written out in that
-    // order: consecutive threads store consecutive positions of each digit's
-    // run, so the stores of a wave cover a few runs instead of 64 scattered words
-    int nvalid = 0;
+    // the block's keys, then its values, in LDS in stable digit order, written
+    // out in that order: consecutive threads store consecutive positions of each
+    // digit's run, so the stores of a wave cover a few runs instead of 64
+    // scattered words
+    const int nvalid = (int)min((int64_t)kSortTile, len - (int64_t)b * kSortTile);
 #pragma unroll
     for (int k = 0; k < kSortRounds; ++k) {
         const int64_t i = wlo + k * 64 + lane;
         if (i < len) {
-            const uint32_t d = (key[k] >> shift) & 255u;
-            const uint32_t pos = wbase[w][d] + rank[k];
-            lkey[pos] = key[k];
-            lval[pos] = val[k];
+            rank[k] += wbase[w][(key[k] >> shift) & 255u];
+            stage[rank[k]] = key[k];
         }
     }
-    {
-        const int64_t lo = (int64_t)b * kSortTile;
-        nvalid = (int)min((int64_t)kSortTile, len - lo);
+    __syncthreads();
+    uint32_t dst[kSortRounds];
+#pragma unroll
+    for (int k = 0; k < kSortRounds; ++k) {
+        const int i = k * kSortThreads + threadIdx.x;
+        if (i < nvalid) {
+            const uint32_t kk = stage[i], d = (kk >> shift) & 255u;
+            dst[k] = gdst[d] + ((uint32_t)i - dstart[d]);
+            if (kout) kout[base + dst[k]] = kk;
+        }
     }
     __syncthreads();
-    for (int i = threadIdx.x; i < nvalid; i += kSortThreads) {
-        const uint32_t kk = lkey[i];
-        const uint32_t d = (kk >> shift) & 255u;
-        const uint32_t dst = gdst[d] + ((uint32_t)i - dstart[d]);
-        if (kout) kout[base + dst] = kk;
-        vout[base + dst] = lval[i];
+#pragma unroll
+    for (int k = 0; k < kSortRounds; ++k)
+        if (wlo + k * 64 + lane < len) stage[rank[k]] = val[k];
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kSortRounds; ++k) {
+        const int i = k * kSortThreads + threadIdx.x;
+        if (i < nvalid) vout[base + dst[k]] = stage[i];
     }
 }
 
@@ -258,8 +293,10 @@ hipError_t radix_sort_segments(uint32_t *key0, uint32_t *val0, uint32_t *key1, u
     const int64_t nstatus = (int64_t)n_segs * 256 * nb;
     uint32_t *extra = hist + nstatus;
     launch_fill_u32(extra, 0u, (int64_t)n_segs * kSweepExtra, st);
-    hipLaunchKernelGGL(k_radix_hist_all, dim3(nb, n_segs), dim3(kSortThreads), 0, st, key0, n_per_seg, passes,
-                       extra, kbase, seg_len);
+    const int tiles = (int64_t)nb * n_segs >= kHistManyTiles ? kHistTiles : 1;
+    hipLaunchKernelGGL(k_radix_hist_all, dim3((nb + tiles - 1) / tiles, n_segs), dim3(kSortThreads), 0, st, key0,
+                       n_per_seg, passes,
+                       extra, kbase, seg_len, tiles);
     hipLaunchKernelGGL(k_radix_digit_base, dim3(n_segs), dim3(256), 0, st, extra, passes);
     for (int pass = 0; pass < passes; ++pass) {
         const int shift = 8 * pass;

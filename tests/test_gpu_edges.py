@@ -415,3 +415,36 @@ def test_ranges_in_half_tiles_and_in_pixels(size):
         assert whole is None or torch.equal(s, whole)
         assert masked is None or torch.equal(m, masked)
         whole, masked = s, m
+
+
+@pytest.mark.parametrize("n", [4095, 4096, 4097, 8193])
+def test_depth_sort_tile_edges(n):
+    """Sort tiles of 4096 keys with a last one full, nearly empty and nearly
+    full, at the parity bar of 1e-5 against the FP64 oracle."""
+    import synth
+    import paper_2607_02721_amd as gs
+    from oracle import oracle as ora
+    ora.build(force=False)
+    sc = synth.make_cluster_scene(n, 28, 1)
+    vw = synth.make_orbit_views(2, 29, 40, 24)
+    ref = ora.sensitivity(sc, vw)
+    mask_np = synth.pack_bits(~ref["flag"])
+    ref = ora.sensitivity(sc, vw, None, mask_np)
+    s, _ = gs.sensitivity(gs.DeviceScene.from_scene(sc), vw,
+                          ray_mask=torch.as_tensor(mask_np.view(np.int32)).cuda())
+    err = np.abs(s.cpu().numpy().astype(np.float64) - ref["s"]) - (1e-5 * ref["s"] + 1e-12)
+    assert err.max() <= 0
+
+
+def test_depth_sort_many_tiles():
+    """8200 sort tiles in one call (histograms of four tiles per block) and the
+    same views 64 to a chunk (one tile per block)."""
+    import synth
+    import paper_2607_02721_amd as gs
+    sc = synth.make_cluster_scene(4097, 30, 1)
+    vw = synth.make_orbit_views(4100, 31, 8, 8)
+    d = gs.DeviceScene.from_scene(sc)
+    every, _ = gs.sensitivity(d, vw)
+    some, _ = gs.sensitivity(d, vw, max_views_per_chunk=64)
+    assert float(every.max()) > 0
+    assert torch.equal(every, some)
