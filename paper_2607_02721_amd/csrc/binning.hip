@@ -10,7 +10,8 @@
 //             tile's total; a scan of the totals gives each tile's list start,
 //             so a tile's list is its chunks' segments in order;
 //   3. emit:  one wave per (chunk, group of tile rows) expands the chunk's
-//             positions that meet its rows, in order and 2^10 at a time, into
+//             positions that meet its rows, in order and 2^10 (2^11 with a
+//             ray mask) at a time, into
 //             (position, tile) items packed 64 to a batch; every tile's next
 //             slot comes from a wave-private LDS cursor (atomic add, executed
 //             in issue order), so each (tile, chunk) segment is written
@@ -438,7 +439,8 @@ __global__ __launch_bounds__(kEmitWave) void k_bin_emit(const ViewDev *__restric
     const int words = 1 << (chunk_bits - 6);
     const uint64_t *rbits =
         rowbits + ((int64_t)v * rows_stride + r0) * ((int64_t)nchunks * words) + (int64_t)chunk * words;
-    static_assert(kEmitBatch % 64 == 0 && kEmitBatch <= 64 * kEmitWave, "one row-bitmap word per lane");
+    static_assert(kEmitBatch % 64 == 0 && kEmitBatchMasked % 64 == 0 && kEmitBatch <= 64 * kEmitWave &&
+                      kEmitBatchMasked <= 64 * kEmitWave, "one row-bitmap word per lane");
     uint32_t tick = 0u;
     for (int b0 = 0; b0 < hi; b0 += batch) {
         const int b1 = min(b0 + batch, hi);
@@ -641,7 +643,7 @@ void launch_bin_emit(const ViewDev *views_dev, int Vc, int64_t N, int nchunks, c
     const int64_t blocks = ((int64_t)row_groups * col_groups * nchunks * Vc + run - 1) / run * run;
     const int group_tiles = kEmitRows * std::min(max_tiles_x, kEmitCols);
     const int line_log = tile_shift_x >= 5 ? 4 : 3;
-    const int batch = std::min(kEmitBatch, 1 << b.chunk_bits);
+    const int batch = std::min(b.tile_active ? kEmitBatchMasked : kEmitBatch, 1 << b.chunk_bits);
     const size_t lds = emit_lds_bytes(group_tiles, b.tile_active != nullptr, line_log, batch);
     const dim3 grid((unsigned)blocks);
     auto go = [&](auto kernel) {

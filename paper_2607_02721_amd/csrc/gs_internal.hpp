@@ -21,7 +21,10 @@ constexpr int kChunkBitsMin = 10, kChunkBitsMax = 14;
 // words: 38 912 cells (152 KiB) fit the 160 KiB a workgroup may take on CDNA4.
 constexpr int kMaxCellsPerView = 38912;
 constexpr int kSortTile = 4096;    // radix sort: keys per block (4 waves x 16 rounds x 64 lanes)
-constexpr int kEmitBatch = 1024;   // emission: positions a wave queues at a time (2048 3% slower: less LDS to spare; 512 13%)
+// Emission: positions a wave queues at a time.  2048 leave less LDS to the other
+// waves of a CU (3% slower), 512 take 13% more; with a ray mask, whose waves use
+// little else of LDS, 1024 took 1472 us where 2048 take 1317.
+constexpr int kEmitBatch = 1024, kEmitBatchMasked = 2048;
 constexpr uint32_t kInvisibleKey = 0xFFFFFFFFu;
 constexpr uint32_t kIndexMask = 0x0FFFFFFFu; // list entry = gaussian | quadrant mask << 28
 
