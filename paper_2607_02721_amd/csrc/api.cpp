@@ -469,7 +469,7 @@ struct ChunkRun {
 
 gs_status run_front(const gs_scene *scene, const gs_views *views, const gs_params *p, const Setup &S,
                     const ChunkPlan &c, hipStream_t st, int dev, std::vector<ViewDev> &hv,
-                    std::vector<int32_t> &htv, ChunkRun &r, Timer &tm, double *ms_acc, bool zero_counters,
+                    ChunkRun &r, Timer &tm, double *ms_acc, bool zero_counters,
                     uint32_t *sens_bits) {
     const int64_t N = S.N;
     const int64_t nbins = (int64_t)c.total_tiles * S.nchunks;
@@ -531,7 +531,6 @@ gs_status run_front(const gs_scene *scene, const gs_views *views, const gs_param
     if (S.agg == GS_AGG_SCENE) r.acc = cv.take<uint64_t>((size_t)N);
 
     hv.assign(c.vc, ViewDev{});
-    htv.assign(c.total_tiles, 0);
     int tb = 0, sb = 0;
     for (int k = 0; k < c.vc; ++k) {
         const int i = c.v0 + k;
@@ -556,7 +555,6 @@ gs_status run_front(const gs_scene *scene, const gs_views *views, const gs_param
         V.ray_local = S.ray_base[i] - S.ray_base[c.v0];
         V.tile_base = tb;
         V.sat_base = sb;
-        for (int t = 0; t < V.tiles_x * V.tiles_y; ++t) htv[tb + t] = k;
         tb += V.tiles_x * V.tiles_y;
         sb += (V.tiles_x + 1) * (V.tiles_y + 1);
     }
@@ -569,9 +567,7 @@ gs_status run_front(const gs_scene *scene, const gs_views *views, const gs_param
     }
     b.half_ranges = half_ranges_fit(max_tx, max_ty);
     HIP_TRY(hipMemcpyAsync(r.views_dev, hv.data(), sizeof(ViewDev) * c.vc, hipMemcpyHostToDevice, st));
-    HIP_TRY(hipMemcpyAsync(r.tile_view, htv.data(), sizeof(int32_t) * c.total_tiles, hipMemcpyHostToDevice, st));
-    launch_fill_u32(b.nvis, 0u, 2 * (int64_t)c.vc, st);
-    launch_fill_u32(b.bin_count, 0u, nbins, st);
+    launch_tile_views(r.views_dev, c.vc, max_tiles, r.tile_view, st);
     // every chunk projects every Gaussian, so the invalid count restarts per chunk
     if (zero_counters)
         launch_fill_u64(b.counters, 0ull, CNT_WORDS, st);
@@ -595,15 +591,15 @@ gs_status run_front(const gs_scene *scene, const gs_views *views, const gs_param
     // Three 8-bit passes suffice when every view's visible depth keys, less
     // the view's smallest, stay below 2^24 - 1 (depths within about a factor
     // of four: the float bits of a positive depth grow by 2^23 per octave).
-    std::vector<uint32_t> kr(2 * (size_t)c.vc), nv(c.vc);
-    HIP_TRY(hipMemcpyAsync(kr.data(), b.kmin, sizeof(uint32_t) * 2 * c.vc, hipMemcpyDeviceToHost, st));
-    HIP_TRY(hipMemcpyAsync(nv.data(), b.nvis, sizeof(uint32_t) * c.vc, hipMemcpyDeviceToHost, st));
+    std::vector<uint32_t> nv(4 * (size_t)c.vc);      // counts, colour maxima, key minima and maxima
+    HIP_TRY(hipMemcpyAsync(nv.data(), b.nvis, sizeof(uint32_t) * nv.size(), hipMemcpyDeviceToHost, st));
     uint64_t n_listed = 0;
     if (qoff)
         HIP_TRY(hipMemcpyAsync(&n_listed, qoff + c.total_tiles, sizeof(uint64_t), hipMemcpyDeviceToHost, st));
     HIP_TRY(hipStreamSynchronize(st));
     r.n_listed = (int32_t)n_listed;
     uint32_t span = 0;
+    const uint32_t *kr = nv.data() + 2 * (size_t)c.vc;
     for (int k = 0; k < c.vc; ++k)
         if (kr[c.vc + k] >= kr[k]) span = std::max(span, kr[c.vc + k] - kr[k]);
     const int passes = span < 0xFFFFFFu ? 3 : 4;
@@ -613,7 +609,7 @@ gs_status run_front(const gs_scene *scene, const gs_views *views, const gs_param
     // masks, views that see little of the scene) the kept keys are moved to
     // the front of each view's segment first and only they are sorted.
     uint64_t kept = 0;
-    for (uint32_t x : nv) kept += x;
+    for (int k = 0; k < c.vc; ++k) kept += nv[k];
     if (4 * kept <= 3 * (uint64_t)N * (uint64_t)c.vc) {
         launch_key_compact(b, c.vc, N, b.key1, b.val1, st);
         HIP_TRY(radix_sort_segments(b.key1, b.val1, b.key0, b.val0, b.hist, N, c.vc, false, passes,
@@ -702,8 +698,7 @@ gs_status run_front(const gs_scene *scene, const gs_views *views, const gs_param
     // the compositing launch sees this chunk as a single scene slot
     r.host_slot = SceneSlot{b.R, b.CB, b.lists, b.tile_off, b.cmax, b.ray_A, sens_bits, p->ray_mask,
                             N, 0, 0, b.R3, c.rays, clist};
-    HIP_TRY(hipMemcpyAsync(r.slot_dev, &r.host_slot, sizeof(SceneSlot), hipMemcpyHostToDevice, st));
-    launch_fill_u32((uint32_t *)r.tile_scene, 0u, c.total_tiles, st);
+    launch_one_scene(r.host_slot, r.slot_dev, r.tile_scene, c.total_tiles, r.order_classes, st);
     tm.mark(3, st);
     if (tm.on) {
         HIP_TRY(hipEventSynchronize(tm.ev[3]));
@@ -892,14 +887,13 @@ gs_status gs_sensitivity(const gs_scene *scene, const gs_views *views, const gs_
     double ms[6] = {0, 0, 0, 0, 0, 0};
     int64_t n_bins = 0;
     std::vector<ViewDev> hv;
-    std::vector<int32_t> htv;
     int64_t entries = 0, projected = 0;
     int32_t sort_passes = 0;
     ChunkRun r;
     const float log2e = 1.4426950408889634f;
     for (size_t ci = 0; ci < chunks.size(); ++ci) {
         const ChunkPlan &c = chunks[ci];
-        if ((s = run_front(scene, views, params, S, c, st, dev, hv, htv, r, tm, ms, ci == 0, (uint32_t *)sens)) !=
+        if ((s = run_front(scene, views, params, S, c, st, dev, hv, r, tm, ms, ci == 0, (uint32_t *)sens)) !=
             GS_OK)
             return s;
         entries += r.n_entries;
@@ -966,7 +960,7 @@ gs_status gs_sensitivity(const gs_scene *scene, const gs_views *views, const gs_
         }
         tm.mark(3, st);
         if (!a.quad_list && order_pays((int64_t)a.total_tiles << a.region_log)) {
-            launch_tile_order(a, r.tile_order, r.order_classes, st);
+            launch_tile_order(a, r.tile_order, r.order_classes, true, st);
             a.tile_order = r.tile_order;
         }
         // (counting calls keep the region form: their pair counters say what
@@ -1071,14 +1065,13 @@ gs_status gs_render_objective(const gs_scene *scene, const gs_views *views, cons
     Timer tm(false);
     double ms[6] = {0, 0, 0, 0, 0, 0};
     std::vector<ViewDev> hv;
-    std::vector<int32_t> htv;
     ChunkRun r;
     const float log2e = 1.4426950408889634f;
     uint64_t inv_total = 0;
     uint32_t gamma_bits = 0;
     for (size_t ci = 0; ci < chunks.size(); ++ci) {
         const ChunkPlan &c = chunks[ci];
-        if ((s = run_front(scene, views, params, S, c, st, dev, hv, htv, r, tm, ms, true, nullptr)) != GS_OK)
+        if ((s = run_front(scene, views, params, S, c, st, dev, hv, r, tm, ms, true, nullptr)) != GS_OK)
             return s;
         CompositeArgs a = composite_args(r, c.total_tiles, params, 0.0f, S);
         ObjectiveArgs o{weights, objective, per_ray, r.tile_sums, nullptr, 1e-9f};
@@ -1088,7 +1081,7 @@ gs_status gs_render_objective(const gs_scene *scene, const gs_views *views, cons
             a.quad_list = r.quad_list;
             a.n_listed = r.n_listed;
         } else if (order_pays((int64_t)a.total_tiles << a.region_log)) {
-            launch_tile_order(a, r.tile_order, r.order_classes, st);
+            launch_tile_order(a, r.tile_order, r.order_classes, true, st);
             a.tile_order = r.tile_order;
         }
         a.by_quads = quads_pay((int64_t)a.total_tiles << a.region_log);
@@ -1666,8 +1659,6 @@ void enqueue_front(const gs_plan *P, PlanScene &ps, hipStream_t st) {
     const int64_t N = ps.S.N;
     ChunkBufs &b = ps.b;
     b.half_ranges = half_ranges_fit(ps.max_tx, ps.max_ty);
-    launch_fill_u32(b.nvis, 0u, 2 * (int64_t)ps.c.vc, st);
-    launch_fill_u32(b.bin_count, 0u, ps.nbins, st);
     launch_fill_u64(b.counters, 0ull, CNT_WORDS, st);
     SceneDev sd{ps.sc.n, ps.sc.sh_degree, ps.sc.format, ps.sc.mean, ps.sc.log_scale,
                 ps.sc.quat, ps.sc.opacity, ps.sc.sh};
@@ -1716,7 +1707,7 @@ void enqueue_plan(gs_plan *P, hipStream_t st, float *const *sens) {
             a.ccount = cb.compact ? G.ccount + ((size_t)cb.t0 << P->quad_log) : nullptr;
             a.report_floor = P->p.share_floor > 0.0f ? std::nextafter(P->p.share_floor, 0.0f) : 0.0f;
             if (!a.work && order_pays((int64_t)a.total_tiles << a.region_log)) {
-                launch_tile_order(a, G.tile_order, G.order_classes, st);
+                launch_tile_order(a, G.tile_order, G.order_classes, false, st);
                 a.tile_order = G.tile_order;
             }
             a.by_quads = !a.work && quads_pay((int64_t)a.total_tiles << a.region_log);

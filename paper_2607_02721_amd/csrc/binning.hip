@@ -161,7 +161,9 @@ __global__ __launch_bounds__(kBinThreads) void k_bin_count(const ViewDev *__rest
 // Column pass over one view's [chunk][tile] counts: each thread owns one tile
 // and replaces its counts, chunk by chunk, with their exclusive prefix (the
 // tile's segment offsets inside its list); the tile's total goes to tile_tot.
+// (Chunks past the view's visible positions are neither written nor read.)
 __global__ __launch_bounds__(kBinThreads) void k_chunk_prefix(const ViewDev *__restrict__ views, int nchunks,
+                                                              const uint32_t *__restrict__ nvis, int chunk_bits,
                                                               uint32_t *__restrict__ bin_count,
                                                               uint32_t *__restrict__ tile_tot) {
     const ViewDev &V = views[blockIdx.y];
@@ -169,9 +171,10 @@ __global__ __launch_bounds__(kBinThreads) void k_chunk_prefix(const ViewDev *__r
     const int t = blockIdx.x * kBinThreads + threadIdx.x;
     if (t >= ntiles) return;
     uint32_t *col = bin_count + (int64_t)V.tile_base * nchunks + t;
+    const int used = (int)(((int64_t)nvis[blockIdx.y] + (1ll << chunk_bits) - 1) >> chunk_bits);
     uint32_t run = 0;
     int c = 0;
-    for (; c + 8 <= nchunks; c += 8) {
+    for (; c + 8 <= used; c += 8) {
         uint32_t x[8];
 #pragma unroll
         for (int k = 0; k < 8; ++k) x[k] = col[(int64_t)(c + k) * ntiles];
@@ -181,7 +184,7 @@ __global__ __launch_bounds__(kBinThreads) void k_chunk_prefix(const ViewDev *__r
             run += x[k];
         }
     }
-    for (; c < nchunks; ++c) {
+    for (; c < used; ++c) {
         const uint32_t x = col[(int64_t)c * ntiles];
         col[(int64_t)c * ntiles] = run;
         run += x;
@@ -631,7 +634,7 @@ void launch_bin_count(const ViewDev *views_dev, int Vc, int64_t N, int nchunks, 
 void launch_chunk_prefix(const ViewDev *views_dev, int Vc, int nchunks, const ChunkBufs &b, int max_tiles,
                          hipStream_t st) {
     hipLaunchKernelGGL(k_chunk_prefix, dim3((unsigned)((max_tiles + kBinThreads - 1) / kBinThreads), (unsigned)Vc),
-                       dim3(kBinThreads), 0, st, views_dev, nchunks, b.bin_count, b.tile_tot);
+                       dim3(kBinThreads), 0, st, views_dev, nchunks, b.nvis, b.chunk_bits, b.bin_count, b.tile_tot);
 }
 
 void launch_bin_emit(const ViewDev *views_dev, int Vc, int64_t N, int nchunks, const ChunkBufs &b,

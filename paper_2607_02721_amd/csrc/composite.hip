@@ -1340,6 +1340,33 @@ __device__ __forceinline__ int length_class(const CompositeArgs &a, int t) {
     return max(0, kOrderClasses - 2 - half);
 }
 
+__global__ __launch_bounds__(256) void k_tile_views(const ViewDev *__restrict__ views, int32_t *__restrict__ tile_view) {
+    const ViewDev &V = views[blockIdx.y];
+    const int t = (int)blockIdx.x * 256 + (int)threadIdx.x;
+    if (t < V.tiles_x * V.tiles_y) tile_view[V.tile_base + t] = (int32_t)blockIdx.y;
+}
+
+void launch_tile_views(const ViewDev *views_dev, int Vc, int max_tiles, int32_t *tile_view, hipStream_t st) {
+    hipLaunchKernelGGL(k_tile_views, dim3((unsigned)((max_tiles + 255) / 256), (unsigned)Vc), dim3(256), 0, st,
+                       views_dev, tile_view);
+}
+
+__global__ __launch_bounds__(256) void k_one_scene(SceneSlot slot, SceneSlot *__restrict__ slot_dev,
+                                                   int32_t *__restrict__ tile_scene, int tiles,
+                                                   uint32_t *__restrict__ classes) {
+    const int t = (int)blockIdx.x * 256 + (int)threadIdx.x;
+    if (t < tiles) tile_scene[t] = 0;
+    if (blockIdx.x == 0 && threadIdx.x < 2 * kOrderClasses) classes[threadIdx.x] = 0u;
+    if (t == 0) *slot_dev = slot;
+}
+
+void launch_one_scene(const SceneSlot &slot, SceneSlot *slot_dev, int32_t *tile_scene, int tiles, uint32_t *classes,
+                      hipStream_t st) {
+    static_assert(2 * kOrderClasses <= 256, "one block clears the classes");
+    hipLaunchKernelGGL(k_one_scene, dim3((unsigned)((tiles + 255) / 256)), dim3(256), 0, st, slot, slot_dev,
+                       tile_scene, tiles, classes);
+}
+
 constexpr int kOrderThreads = 256, kOrderTiles = 4;     // tiles per block: 1024
 __global__ __launch_bounds__(kOrderThreads) void k_tile_classes(CompositeArgs a, uint32_t *__restrict__ classes) {
     __shared__ uint32_t cnt[kOrderClasses];
@@ -1382,10 +1409,10 @@ __global__ __launch_bounds__(kOrderThreads) void k_tile_order(CompositeArgs a, u
     }
 }
 
-void launch_tile_order(const CompositeArgs &a, int32_t *order, uint32_t *classes, hipStream_t st) {
+void launch_tile_order(const CompositeArgs &a, int32_t *order, uint32_t *classes, bool cleared, hipStream_t st) {
     const int per = kOrderThreads * kOrderTiles;
     const unsigned blocks = (unsigned)((a.total_tiles + per - 1) / per);
-    launch_fill_u32(classes, 0u, 2 * kOrderClasses, st);
+    if (!cleared) launch_fill_u32(classes, 0u, 2 * kOrderClasses, st);
     hipLaunchKernelGGL(k_tile_classes, dim3(blocks), dim3(kOrderThreads), 0, st, a, classes);
     hipLaunchKernelGGL(k_tile_order, dim3(blocks), dim3(kOrderThreads), 0, st, a, classes, order);
 }

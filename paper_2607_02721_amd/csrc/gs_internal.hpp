@@ -332,7 +332,14 @@ constexpr double kAggScale = 1152921504606846976.0;   // 2^60
 // The launch's tiles by descending list length (in classes of half an octave)
 // into order [total_tiles]; classes: kOrderClasses x 2 words of scratch.
 constexpr int kOrderClasses = 64;
-void launch_tile_order(const CompositeArgs &a, int32_t *order, uint32_t *classes, hipStream_t st);
+// (cleared: they are 0 already).
+void launch_tile_order(const CompositeArgs &a, int32_t *order, uint32_t *classes, bool cleared, hipStream_t st);
+// What a launch over the tiles of one scene reads, set up on the device: small
+// copies from pageable host memory wait for the stream.  tile_view[t] = the
+// view of tile t; the scene's slot, tile_scene[t] = 0 and cleared order classes.
+void launch_tile_views(const ViewDev *views_dev, int Vc, int max_tiles, int32_t *tile_view, hipStream_t st);
+void launch_one_scene(const SceneSlot &slot, SceneSlot *slot_dev, int32_t *tile_scene, int tiles, uint32_t *classes,
+                      hipStream_t st);
 // Whether a launch of this many regions takes it.  The chip holds about 7 168
 // of these waves at once: fewer all start together, in any order (3 800 regions
 // lost 3%, 7 280 2%), and from 12 500 on the tail of a launch in tile order,

@@ -62,7 +62,11 @@ __device__ __forceinline__ uint32_t wave_incl_scan_u32(uint32_t v) {
 // Scratch after the status words, per segment: [4 passes][256] counts,
 // [4][256] exclusive digit bases, [4] tickets (kSweepExtra words).
 constexpr int kSweepExtra = 4 * 256 * 2 + 4;
-constexpr uint32_t kFlagAgg = 1u << 30, kFlagPrefix = 2u << 30, kCountMask = (1u << 30) - 1u;
+// A status word is flag << 30 | pass << 28 | count (segments hold fewer than 2^28
+// items): a word of an earlier pass counts as not yet written, so the words are
+// cleared once for all passes.
+constexpr uint32_t kFlagAgg = 1u << 30, kFlagPrefix = 2u << 30, kCountMask = (1u << 28) - 1u;
+constexpr int kPassShift = 28;
 
 // Sort tiles per histogram block: its counts go to the segment's by one atomic
 // per digit and pass, so a large sort takes several tiles per block (100
@@ -209,11 +213,12 @@ __global__ __launch_bounds__(kSortThreads, 7) void k_radix_scatter(const uint32_
             // publish this block's count of digit d, then add up the counts
             // of the blocks before it back to one that published its prefix
             uint32_t *st = status + (int64_t)seg * nb * 256;
+            const uint32_t tag = (uint32_t)pass << kPassShift;
             uint32_t excl = 0;
             if (b == 0) {
-                __hip_atomic_store(&st[d], kFlagPrefix | tot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_store(&st[d], kFlagPrefix | tag | tot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             } else {
-                __hip_atomic_store(&st[(int64_t)b * 256 + d], kFlagAgg | tot, __ATOMIC_RELAXED,
+                __hip_atomic_store(&st[(int64_t)b * 256 + d], kFlagAgg | tag | tot, __ATOMIC_RELAXED,
                                    __HIP_MEMORY_SCOPE_AGENT);
                 for (int j = b - 1;; --j) {
                     uint32_t v = 0;
@@ -221,13 +226,13 @@ __global__ __launch_bounds__(kSortThreads, 7) void k_radix_scatter(const uint32_
                     // keeps a broken invariant from hanging the device)
                     for (int spin = 0; spin < (1 << 24); ++spin) {
                         v = __hip_atomic_load(&st[(int64_t)j * 256 + d], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                        if (v & ~kCountMask) break;
+                        if (v >= kFlagAgg && ((v >> kPassShift) & 3u) == (uint32_t)pass) break;
                         __builtin_amdgcn_s_sleep(1);
                     }
                     excl += v & kCountMask;
                     if ((v & kFlagPrefix) || j == 0) break;
                 }
-                __hip_atomic_store(&st[(int64_t)b * 256 + d], kFlagPrefix | (excl + tot), __ATOMIC_RELAXED,
+                __hip_atomic_store(&st[(int64_t)b * 256 + d], kFlagPrefix | tag | (excl + tot), __ATOMIC_RELAXED,
                                    __HIP_MEMORY_SCOPE_AGENT);
             }
             gdst[d] = ex[4 * 256 + pass * 256 + d] + excl;
@@ -292,16 +297,14 @@ hipError_t radix_sort_segments(uint32_t *key0, uint32_t *val0, uint32_t *key1, u
     // hist: [n_segs][256][nb] status words, then kSweepExtra words per segment
     const int64_t nstatus = (int64_t)n_segs * 256 * nb;
     uint32_t *extra = hist + nstatus;
-    launch_fill_u32(extra, 0u, (int64_t)n_segs * kSweepExtra, st);
+    launch_fill_u32(hist, 0u, nstatus + (int64_t)n_segs * kSweepExtra, st);
     const int tiles = (int64_t)nb * n_segs >= kHistManyTiles ? kHistTiles : 1;
     hipLaunchKernelGGL(k_radix_hist_all, dim3((nb + tiles - 1) / tiles, n_segs), dim3(kSortThreads), 0, st, key0,
-                       n_per_seg, passes,
-                       extra, kbase, seg_len, tiles);
+                       n_per_seg, passes, extra, kbase, seg_len, tiles);
     hipLaunchKernelGGL(k_radix_digit_base, dim3(n_segs), dim3(256), 0, st, extra, passes);
     for (int pass = 0; pass < passes; ++pass) {
         const int shift = 8 * pass;
         const uint32_t *kb = pass == 0 ? kbase : nullptr;
-        launch_fill_u32(hist, 0u, nstatus, st);
         // the last pass writes the values only (nothing reads the sorted keys)
         const int64_t blocks = (int64_t)nb * n_segs;
         hipLaunchKernelGGL(k_radix_scatter, dim3((unsigned)blocks), dim3(kSortThreads), 0, st, ki, vi,
