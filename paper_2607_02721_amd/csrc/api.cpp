@@ -1122,6 +1122,23 @@ gs_status gs_render_objective(const gs_scene *scene, const gs_views *views, cons
     return GS_OK;
 }
 
+// The whole draw is enqueued and its outcome read at the end (one wait): with an
+// invalid input, or nothing to draw from, the kernels leave counts, weights and
+// support at zero.
+static gs_status sample_run(const float *sens, int64_t n, int64_t m, uint64_t seed, uint32_t *counts, double *weights,
+                            int64_t *support, uint64_t *C, uint64_t *sums, uint64_t *result, hipStream_t st) {
+    launch_sample_cdf(sens, n, C, sums, result, counts, support, st);
+    launch_draws(C, sums, result, n, m, seed, counts, st);
+    launch_weights(counts, sens, result, n, m, weights, support, st);
+    HIP_TRY(hipGetLastError());
+    uint64_t outcome[2] = {0, 0};   // Q, bad input
+    HIP_TRY(hipMemcpyAsync(outcome, result, sizeof outcome, hipMemcpyDeviceToHost, st));
+    HIP_TRY(hipStreamSynchronize(st));
+    if (outcome[1]) return fail(GS_ERR_INVALID_DATA, "a sensitivity is outside [0, 1 + 2^-10] or NaN");
+    if (outcome[0] == 0) return fail(GS_ERR_NO_POSITIVE_SENSITIVITY, "every sensitivity is 0");
+    return GS_OK;
+}
+
 gs_status gs_sample_coreset(const float *sens, int64_t n, int64_t m, uint64_t seed, uint32_t *counts,
                             double *weights, int64_t *support, void *stream) {
     g_last_error.clear();
@@ -1137,31 +1154,13 @@ gs_status gs_sample_coreset(const float *sens, int64_t n, int64_t m, uint64_t se
     hipStream_t st = (hipStream_t)stream;
     HIP_TRY(order_after_previous(dev, st));
     DoneGuard done_guard{dev, st};
-    const size_t need = 2 * sizeof(uint64_t) * (size_t)n + sizeof(uint64_t) * (scan_tmp_elems(n) + 2) + 2048;
+    const size_t need = sizeof(uint64_t) * ((size_t)n + (size_t)sample_tmp_elems(n) + 2) + 1024;
     HIP_TRY(arena_reserve(g_work[dev], need));
     Carve cv(g_work[dev].base);
-    uint64_t *q = cv.take<uint64_t>(n);
     uint64_t *C = cv.take<uint64_t>(n);
-    uint64_t *tmp = cv.take<uint64_t>(scan_tmp_elems(n) + 2);
-    uint32_t *bad = cv.take<uint32_t>(64);
-    launch_fill_u32(bad, 0u, 1, st);
-    launch_quantize(sens, n, q, bad, st);
-    scan_u64_inclusive(q, C, n, tmp, st);
-    launch_fill_u32(counts, 0u, n, st);
-    launch_fill_u64((uint64_t *)weights, 0ull, n, st);
-    launch_fill_u64((uint64_t *)support, 0ull, 1, st);
-    HIP_TRY(hipGetLastError());
-    uint64_t Q = 0;
-    uint32_t hbad = 0;
-    HIP_TRY(hipMemcpyAsync(&Q, C + n - 1, sizeof(uint64_t), hipMemcpyDeviceToHost, st));
-    HIP_TRY(hipMemcpyAsync(&hbad, bad, sizeof(uint32_t), hipMemcpyDeviceToHost, st));
-    HIP_TRY(hipStreamSynchronize(st));
-    if (hbad) return fail(GS_ERR_INVALID_DATA, "a sensitivity is outside [0, 1 + 2^-10] or NaN");
-    if (Q == 0) return fail(GS_ERR_NO_POSITIVE_SENSITIVITY, "every sensitivity is 0");
-    launch_draws(C, n, m, seed, counts, st);
-    launch_weights(counts, q, sens, C, n, m, weights, support, st);
-    HIP_TRY(hipGetLastError());
-    return GS_OK;
+    uint64_t *sums = cv.take<uint64_t>(sample_tmp_elems(n));
+    uint64_t *result = cv.take<uint64_t>(2);
+    return sample_run(sens, n, m, seed, counts, weights, support, C, sums, result, st);
 }
 
 // ---------------------------------------------------------------------------
@@ -1187,29 +1186,10 @@ gs_status gs_sample_coreset_noalloc(const float *sens, int64_t n, int64_t m, uin
     if ((s = noalloc_scratch(dev, &base)) != GS_OK) return s;
     hipStream_t st = (hipStream_t)stream;
     uint64_t *C = (uint64_t *)base;
-    uint64_t *tmp = C + kNoAllocMaxN;
-    uint32_t *bad = (uint32_t *)(tmp + kNoAllocTmp);
-    // the array keeps the previous call's contents: the flag starts at zero,
-    // and every C entry used is written (quanta, then their prefix sums)
+    uint64_t *sums = C + kNoAllocMaxN;
+    // the array keeps the previous call's contents: every word used is written
     // before it is read
-    launch_fill_u32(bad, 0u, 1, st);
-    launch_quantize(sens, n, C, bad, st);
-    scan_u64_inclusive_inplace(C, n, tmp, st);
-    launch_fill_u32(counts, 0u, n, st);
-    launch_fill_u64((uint64_t *)weights, 0ull, n, st);
-    launch_fill_u64((uint64_t *)support, 0ull, 1, st);
-    HIP_TRY(hipGetLastError());
-    uint64_t Q = 0;
-    uint32_t hbad = 0;
-    HIP_TRY(hipMemcpyAsync(&Q, C + n - 1, sizeof(uint64_t), hipMemcpyDeviceToHost, st));
-    HIP_TRY(hipMemcpyAsync(&hbad, bad, sizeof(uint32_t), hipMemcpyDeviceToHost, st));
-    HIP_TRY(hipStreamSynchronize(st));
-    if (hbad) return fail(GS_ERR_INVALID_DATA, "a sensitivity is outside [0, 1 + 2^-10] or NaN");
-    if (Q == 0) return fail(GS_ERR_NO_POSITIVE_SENSITIVITY, "every sensitivity is 0");
-    launch_draws(C, n, m, seed, counts, st);
-    launch_weights(counts, nullptr, sens, C, n, m, weights, support, st);
-    HIP_TRY(hipGetLastError());
-    return GS_OK;
+    return sample_run(sens, n, m, seed, counts, weights, support, C, sums, sums + kNoAllocTmp, st);
 }
 
 int64_t gs_mlp_param_count(void) { return kMlpParams; }

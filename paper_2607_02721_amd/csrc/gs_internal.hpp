@@ -255,8 +255,6 @@ void launch_list_guard(uint64_t *tile_off, int64_t ntiles, uint64_t cap, uint32_
                        hipStream_t st);
 void scan_u32_to_u64_exclusive(const uint32_t *in, uint64_t *out, int64_t n, uint64_t *block_tmp,
                                hipStream_t st);
-void scan_u64_inclusive(const uint64_t *in, uint64_t *out, int64_t n, uint64_t *block_tmp, hipStream_t st);
-void scan_u64_inclusive_inplace(uint64_t *data, int64_t n, uint64_t *block_tmp, hipStream_t st);
 int64_t scan_tmp_elems(int64_t n);
 
 // One scene of a compositing launch (a launch may cover several scenes).
@@ -391,14 +389,18 @@ void launch_view_sums(const double *tile_sums, const ViewDev *views_dev, int Vc,
 void launch_coreset_error(const double *per_view, int n_views, double *out, hipStream_t st);
 
 // Sampler
-// q_i = ceil(s_i 2^40); *bad |= 1 if some s_i is outside [0, 1 + 2^-10] or
-// NaN (*bad must be zeroed first).
+// C = inclusive prefix sum of q_i = ceil(s_i 2^40), sums = where its blocks start
+// (sample_tmp_elems(n) words), result = (Q, 1 if some s_i is outside [0, 1 + 2^-10]
+// or NaN); counts and *support are zeroed.  Draws leave the counts at zero where Q
+// is 0 or an s_i is bad.  kSampleMaxN = 2^24 - 2^16: Q < 2^64 for up to that many.
 constexpr int64_t kSampleMaxN = ((int64_t)1 << 24) - ((int64_t)1 << 16);
-void launch_quantize(const float *sens, int64_t n, uint64_t *q, uint32_t *bad, hipStream_t st);
-void launch_draws(const uint64_t *C, int64_t n, int64_t m, uint64_t seed, uint32_t *counts, hipStream_t st);
-// q: the quanta of k_quantize, or null to recompute them from sens.
-void launch_weights(const uint32_t *counts, const uint64_t *q, const float *sens, const uint64_t *C, int64_t n,
-                    int64_t m, double *weights, int64_t *support, hipStream_t st);
+int64_t sample_tmp_elems(int64_t n);
+void launch_sample_cdf(const float *sens, int64_t n, uint64_t *C, uint64_t *sums, uint64_t *result, uint32_t *counts,
+                       int64_t *support, hipStream_t st);
+void launch_draws(const uint64_t *C, const uint64_t *sums, const uint64_t *result, int64_t n, int64_t m,
+                  uint64_t seed, uint32_t *counts, hipStream_t st);
+void launch_weights(const uint32_t *counts, const float *sens, const uint64_t *result, int64_t n, int64_t m,
+                    double *weights, int64_t *support, hipStream_t st);
 
 // MLP proposal and features
 size_t mlp_scratch_bytes(int64_t rows);
@@ -437,7 +439,6 @@ void launch_fill_u32(uint32_t *p, uint32_t v, int64_t n, hipStream_t st);
 void launch_fill_u64(uint64_t *p, uint64_t v, int64_t n, hipStream_t st);
 // dst[k] = src[min(k stride, n)] for k = 0 .. ceil(n / stride) (dst holds that many + 1).
 void launch_gather_u64(uint64_t *dst, const uint64_t *src, int64_t n, int64_t stride, hipStream_t st);
-void launch_copy_u64(uint64_t *dst, const uint64_t *src, int64_t n, hipStream_t st);
 void launch_sum_f32_to_f64(const float *x, int64_t n, double *out, double *block_tmp, hipStream_t st);
 
 }  // namespace gs

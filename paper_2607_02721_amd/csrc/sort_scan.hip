@@ -1,5 +1,5 @@
-// Segmented LSD radix sort of (u32 key, u32 value) pairs, exclusive/inclusive
-// prefix sums, fills and a fixed-order float sum.
+// Segmented LSD radix sort of (u32 key, u32 value) pairs, exclusive prefix
+// sums, fills and a fixed-order float sum.
 //
 // Radix sort: each of n_segs segments of n_per_seg items (one segment per
 // view) is sorted independently and stably by key, 8 bits per pass, 3 or 4
@@ -324,14 +324,13 @@ int64_t radix_sort_scratch_words(int64_t n_per_seg, int n_segs) {
 }
 
 // ---------------------------------------------------------------------------
-// Prefix sums over u64 (inputs u32 or u64), three phases with 2048-item blocks.
+// Exclusive prefix sums of u32 in u64, three phases with 2048-item blocks.
 constexpr int kScanThreads = 256;
 constexpr int kScanItems = 8;
 constexpr int kScanBlock = kScanThreads * kScanItems;
 
 int64_t scan_tmp_elems(int64_t n) { return (n + kScanBlock - 1) / kScanBlock + 1; }
 
-template <typename T>
 __device__ __forceinline__ uint64_t block_exclusive_scan(uint64_t v, uint64_t *sh, uint64_t *total) {
     // sh: kScanThreads entries
     const int t = threadIdx.x;
@@ -349,9 +348,8 @@ __device__ __forceinline__ uint64_t block_exclusive_scan(uint64_t v, uint64_t *s
     return incl - v;
 }
 
-template <typename T>
-__global__ __launch_bounds__(kScanThreads) void k_scan_reduce(const T *__restrict__ in, int64_t n,
-                                                               uint64_t *__restrict__ partial) {
+__global__ __launch_bounds__(kScanThreads) void k_scan_reduce(const uint32_t *__restrict__ in, int64_t n,
+                                                              uint64_t *__restrict__ partial) {
     __shared__ uint64_t sh[kScanThreads];
     const int64_t lo = (int64_t)blockIdx.x * kScanBlock;
     uint64_t s = 0;
@@ -392,9 +390,8 @@ __global__ __launch_bounds__(1024) void k_scan_partials(uint64_t *__restrict__ p
     if (threadIdx.x == 1023) partial[nblk] = sh[1023];
 }
 
-template <typename T, bool kInclusive>
-__global__ __launch_bounds__(kScanThreads) void k_scan_apply(const T *__restrict__ in, int64_t n,
-                                                              const uint64_t *__restrict__ partial,
+__global__ __launch_bounds__(kScanThreads) void k_scan_apply(const uint32_t *__restrict__ in, int64_t n,
+                                                              const uint64_t *__restrict__ partial, int64_t nblk,
                                                               uint64_t *__restrict__ out) {
     __shared__ uint64_t sh[kScanThreads];
     const int64_t lo = (int64_t)blockIdx.x * kScanBlock + (int64_t)threadIdx.x * kScanItems;
@@ -406,64 +403,56 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_apply(const T *__restrict
         s += v[k];
     }
     uint64_t total;
-    uint64_t run = block_exclusive_scan<T>(s, sh, &total) + partial[blockIdx.x];
+    uint64_t run = block_exclusive_scan(s, sh, &total) + partial[blockIdx.x];
     for (int k = 0; k < kScanItems; ++k) {
         const int64_t i = lo + k;
-        if (kInclusive) run += v[k];
         if (i < n) out[i] = run;
-        if (!kInclusive) run += v[k];
-    }
-}
-
-// The inclusive apply phase over one array in place: each thread reads its
-// own items before the block scan and writes the same items after it, so no
-// item is read after another thread has written it (no __restrict__ here:
-// input and output are the same memory).
-__global__ __launch_bounds__(kScanThreads) void k_scan_apply_inplace(uint64_t *data, int64_t n,
-                                                                      const uint64_t *__restrict__ partial) {
-    __shared__ uint64_t sh[kScanThreads];
-    const int64_t lo = (int64_t)blockIdx.x * kScanBlock + (int64_t)threadIdx.x * kScanItems;
-    uint64_t v[kScanItems];
-    uint64_t s = 0;
-    for (int k = 0; k < kScanItems; ++k) {
-        const int64_t i = lo + k;
-        v[k] = i < n ? data[i] : 0ull;
-        s += v[k];
-    }
-    uint64_t total;
-    uint64_t run = block_exclusive_scan<uint64_t>(s, sh, &total) + partial[blockIdx.x];
-    for (int k = 0; k < kScanItems; ++k) {
-        const int64_t i = lo + k;
         run += v[k];
-        if (i < n) data[i] = run;
     }
+    if (blockIdx.x == 0 && threadIdx.x == 0) out[n] = partial[nblk];
 }
 
-void scan_u64_inclusive_inplace(uint64_t *data, int64_t n, uint64_t *tmp, hipStream_t st) {
-    const int64_t nblk = (n + kScanBlock - 1) / kScanBlock;
-    hipLaunchKernelGGL(k_scan_reduce<uint64_t>, dim3((unsigned)nblk), dim3(kScanThreads), 0, st, data, n, tmp);
-    hipLaunchKernelGGL(k_scan_partials, dim3(1), dim3(1024), 0, st, tmp, nblk);
-    hipLaunchKernelGGL(k_scan_apply_inplace, dim3((unsigned)nblk), dim3(kScanThreads), 0, st, data, n, tmp);
+// The whole scan in one block, for up to kScanSmall items: 16 per thread.  Three
+// launches take about 15 us however few the items are; one about 5.
+constexpr int kScanSmallItems = 16, kScanSmall = 1024 * kScanSmallItems;
+__global__ __launch_bounds__(1024) void k_scan_small(const uint32_t *__restrict__ in, int n,
+                                                     uint64_t *__restrict__ out) {
+    __shared__ uint64_t wsum[16];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, lo = (int)threadIdx.x * kScanSmallItems;
+    uint32_t v[kScanSmallItems];
+    uint64_t s = 0;
+#pragma unroll
+    for (int k = 0; k < kScanSmallItems; ++k) v[k] = lo + k < n ? in[lo + k] : 0u;
+#pragma unroll
+    for (int k = 0; k < kScanSmallItems; ++k) s += v[k];
+    uint64_t incl = s;
+    for (int off = 1; off < 64; off <<= 1) {
+        const uint64_t x = (uint64_t)__shfl_up((unsigned long long)incl, off);
+        if (lane >= off) incl += x;
+    }
+    if (lane == 63) wsum[w] = incl;
+    __syncthreads();
+    uint64_t run = incl - s;
+    for (int k = 0; k < w; ++k) run += wsum[k];
+#pragma unroll
+    for (int k = 0; k < kScanSmallItems; ++k) {
+        if (lo + k < n) out[lo + k] = run;
+        run += v[k];
+    }
+    if (threadIdx.x == 1023) out[n] = run;
 }
 
-// out[i] = sum_{j<i} in[j] for i in [0, n]; out has n+1 entries.
+// out[i] = sum_{j<i} in[j] for i in [0, n]; out has n+1 entries.  (Kernels only,
+// so that the sequence can be captured into a graph.)
 void scan_u32_to_u64_exclusive(const uint32_t *in, uint64_t *out, int64_t n, uint64_t *tmp, hipStream_t st) {
+    if (n <= kScanSmall) {
+        hipLaunchKernelGGL(k_scan_small, dim3(1), dim3(1024), 0, st, in, (int)n, out);
+        return;
+    }
     const int64_t nblk = (n + kScanBlock - 1) / kScanBlock;
-    hipLaunchKernelGGL(k_scan_reduce<uint32_t>, dim3((unsigned)nblk), dim3(kScanThreads), 0, st, in, n, tmp);
+    hipLaunchKernelGGL(k_scan_reduce, dim3((unsigned)nblk), dim3(kScanThreads), 0, st, in, n, tmp);
     hipLaunchKernelGGL(k_scan_partials, dim3(1), dim3(1024), 0, st, tmp, nblk);
-    hipLaunchKernelGGL((k_scan_apply<uint32_t, false>), dim3((unsigned)nblk), dim3(kScanThreads), 0, st, in, n,
-                       tmp, out);
-    // trailing total (a kernel rather than a copy, so that the sequence can be
-    // captured into a graph)
-    launch_copy_u64(out + n, tmp + nblk, 1, st);
-}
-
-void scan_u64_inclusive(const uint64_t *in, uint64_t *out, int64_t n, uint64_t *tmp, hipStream_t st) {
-    const int64_t nblk = (n + kScanBlock - 1) / kScanBlock;
-    hipLaunchKernelGGL(k_scan_reduce<uint64_t>, dim3((unsigned)nblk), dim3(kScanThreads), 0, st, in, n, tmp);
-    hipLaunchKernelGGL(k_scan_partials, dim3(1), dim3(1024), 0, st, tmp, nblk);
-    hipLaunchKernelGGL((k_scan_apply<uint64_t, true>), dim3((unsigned)nblk), dim3(kScanThreads), 0, st, in, n,
-                       tmp, out);
+    hipLaunchKernelGGL(k_scan_apply, dim3((unsigned)nblk), dim3(kScanThreads), 0, st, in, n, tmp, nblk, out);
 }
 
 // ---------------------------------------------------------------------------
@@ -474,14 +463,6 @@ __global__ void k_fill_u32(uint32_t *p, uint32_t v, int64_t n) {
 __global__ void k_fill_u64(uint64_t *p, uint64_t v, int64_t n) {
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
         p[i] = v;
-}
-__global__ void k_copy_u64(uint64_t *dst, const uint64_t *src, int64_t n) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) dst[i] = src[i];
-}
-void launch_copy_u64(uint64_t *dst, const uint64_t *src, int64_t n, hipStream_t st) {
-    if (n <= 0) return;
-    hipLaunchKernelGGL(k_copy_u64, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, dst, src, n);
 }
 // dst[k] = src[min(k stride, n)] for k = 0 .. ceil(n / stride).
 __global__ void k_gather_u64(uint64_t *dst, const uint64_t *src, int64_t n, int64_t stride, int64_t count) {

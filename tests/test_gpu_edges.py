@@ -448,3 +448,48 @@ def test_depth_sort_many_tiles():
     some, _ = gs.sensitivity(d, vw, max_views_per_chunk=64)
     assert float(every.max()) > 0
     assert torch.equal(every, some)
+
+
+# blocks of 2048 quanta and their neighbours, a block of zeros in the middle, more
+# than 1024 blocks (a thread then takes several of their sums), one Gaussian
+@pytest.mark.parametrize("n", [1, 2, 2047, 2048, 2049, 6144, 2_100_000])
+@pytest.mark.parametrize("noalloc", [False, True])
+def test_sampler_block_edges(n, noalloc):
+    """Counts, weights and support equal the oracle's bit for bit; an invalid
+    value in any block leaves them all at zero."""
+    import paper_2607_02721_amd as gs
+    from oracle import oracle as ora
+    ora.build(force=False)
+    rng = np.random.default_rng(n)
+    s = rng.uniform(0, 1, n).astype(np.float32)
+    s[rng.uniform(size=n) < 0.3] = 0
+    s[2048:4096] = 0
+    s[-1] = np.float32(0.5)
+    ref = ora.sample(s, 5000, 7)
+    out = (torch.full((n,), 3, dtype=torch.int32).cuda(), torch.full((n,), 3.0, dtype=torch.float64).cuda(),
+           torch.full((1,), 3, dtype=torch.int64).cuda())
+    counts, w, sup = gs.sample_coreset(torch.as_tensor(s).cuda(), 5000, 7, out=out, noalloc=noalloc)
+    assert np.array_equal(counts.cpu().numpy().view(np.uint32), ref["counts"])
+    assert np.array_equal(w.cpu().numpy().view(np.uint64), ref["weights"].view(np.uint64))
+    assert int(sup.item()) == ref["support"]
+    for where in (0, n // 2, n - 1):
+        x = s.copy()
+        x[where] = -1
+        with pytest.raises(gs.GsError):
+            gs.sample_coreset(torch.as_tensor(x).cuda(), 5000, 7, out=out, noalloc=noalloc)
+        assert not out[0].any() and not out[1].any() and int(out[2]) == 0
+
+
+@pytest.mark.parametrize("tiles", [(16_384, 1), (16_385, 1), (1, 1)])
+def test_list_offsets_of_few_and_many_tiles(tiles):
+    """Tile counts at the edge of the one-block scan (as views of one tile):
+    a call equals its views 4096 to a chunk, which take that form."""
+    import synth
+    import paper_2607_02721_amd as gs
+    sc = synth.make_cluster_scene(300, 32, 1)
+    vw = synth.make_orbit_views(tiles[0], 33, 16, 16)
+    d = gs.DeviceScene.from_scene(sc)
+    every, _ = gs.sensitivity(d, vw)
+    some, _ = gs.sensitivity(d, vw, max_views_per_chunk=4096)
+    assert float(every.max()) > 0
+    assert torch.equal(every, some)
