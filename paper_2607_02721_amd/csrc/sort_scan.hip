@@ -288,10 +288,102 @@ __global__ __launch_bounds__(kSortThreads, 7) void k_radix_scatter(const uint32_
     }
 }
 
+// Segments of one tile or less: every pass in one block, keys and values in LDS
+// between the passes.  (The general form is a chain of launches, each a chain of
+// latencies: 4 segments of 2000 keys took 48 us in six launches, 10 so.)
+// Wave w holds `rounds` runs of 64 neighbouring items, so that its ranks by
+// ballots follow the order of the items, as in k_radix_scatter.
+constexpr int kSmallThreads = 1024, kSmallWaves = kSmallThreads / 64, kSmallRounds = kSortTile / kSmallThreads;
+__global__ __launch_bounds__(kSmallThreads) void k_sort_small(const uint32_t *__restrict__ kin,
+                                                              const uint32_t *__restrict__ vin,
+                                                              uint32_t *__restrict__ vout, int64_t n_per_seg,
+                                                              int passes, const uint32_t *__restrict__ kbase,
+                                                              const uint32_t *__restrict__ seg_len) {
+    __shared__ uint32_t wcnt[kSmallWaves][256], dstart[256], wsum4[4];
+    __shared__ uint32_t skey[kSortTile], sval[kSortTile];
+    const int seg = blockIdx.x, w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int len = (int)(seg_len ? (int64_t)seg_len[seg] : n_per_seg);
+    const int64_t base = (int64_t)seg * n_per_seg;
+    const int rounds = (len + kSmallThreads - 1) / kSmallThreads, wlo = w * rounds * 64;
+    uint32_t key[kSmallRounds], val[kSmallRounds], rank[kSmallRounds];
+#pragma unroll
+    for (int k = 0; k < kSmallRounds; ++k) {
+        const int i = wlo + k * 64 + lane;
+        const bool ok = k < rounds && i < len;
+        key[k] = ok ? rebase(kin[base + i], kbase, seg) : 0u;
+        val[k] = ok ? (vin ? vin[base + i] : (uint32_t)i) : 0u;
+    }
+    for (int pass = 0; pass < passes; ++pass) {
+        const int shift = 8 * pass;
+        for (int i = threadIdx.x; i < kSmallWaves * 256; i += kSmallThreads) (&wcnt[0][0])[i] = 0u;
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < kSmallRounds; ++k) {
+            if (k >= rounds) break;
+            const bool ok = wlo + k * 64 + lane < len;
+            const uint32_t d = (key[k] >> shift) & 255u;
+            const uint64_t peers = match_digit(d, __ballot(ok));
+            const uint32_t before = (uint32_t)__popcll(peers & lanemask_lt());
+            const uint32_t run = ok ? wcnt[w][d] : 0u;
+            rank[k] = run + before;
+            if (ok && (peers >> lane) == 1ull) wcnt[w][d] = run + before + 1u;
+            __builtin_amdgcn_wave_barrier();
+        }
+        __syncthreads();
+        // digit starts: over the waves, then over the digits
+        uint32_t tot = 0u, incl = 0u;
+        if (threadIdx.x < 256) {
+            for (int q = 0; q < kSmallWaves; ++q) {
+                const uint32_t c = wcnt[q][threadIdx.x];
+                wcnt[q][threadIdx.x] = tot;
+                tot += c;
+            }
+            incl = wave_incl_scan_u32(tot);
+            if (lane == 63) wsum4[w] = incl;
+        }
+        __syncthreads();
+        if (threadIdx.x < 256) {
+            uint32_t start = incl - tot;
+            for (int q = 0; q < w; ++q) start += wsum4[q];
+            dstart[threadIdx.x] = start;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < kSmallRounds; ++k)
+            if (k < rounds && wlo + k * 64 + lane < len) {
+                const uint32_t d = (key[k] >> shift) & 255u;
+                const uint32_t pos = dstart[d] + wcnt[w][d] + rank[k];
+                skey[pos] = key[k];
+                sval[pos] = val[k];
+            }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < kSmallRounds; ++k) {
+            const int i = wlo + k * 64 + lane;
+            if (k < rounds && i < len) {
+                key[k] = skey[i];
+                val[k] = sval[i];
+            }
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < kSmallRounds; ++k) {
+        const int i = wlo + k * 64 + lane;
+        if (k < rounds && i < len) vout[base + i] = val[k];
+    }
+}
+
 hipError_t radix_sort_segments(uint32_t *key0, uint32_t *val0, uint32_t *key1, uint32_t *val1, uint32_t *hist,
                                int64_t n_per_seg, int n_segs, bool vals_are_iota, int passes,
                                const uint32_t *kbase, const uint32_t *seg_len, uint32_t **key_out,
                                uint32_t **val_out, hipStream_t st) {
+    if (n_per_seg <= kSortTile) {
+        hipLaunchKernelGGL(k_sort_small, dim3((unsigned)n_segs), dim3(kSmallThreads), 0, st, key0,
+                           vals_are_iota ? nullptr : val0, val1, n_per_seg, passes, kbase, seg_len);
+        *key_out = nullptr;
+        *val_out = val1;
+        return hipGetLastError();
+    }
     const int nb = (int)((n_per_seg + kSortTile - 1) / kSortTile);
     uint32_t *ki = key0, *vi = val0, *ko = key1, *vo = val1;
     // hist: [n_segs][256][nb] status words, then kSweepExtra words per segment

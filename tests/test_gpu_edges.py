@@ -493,3 +493,30 @@ def test_list_offsets_of_few_and_many_tiles(tiles):
     some, _ = gs.sensitivity(d, vw, max_views_per_chunk=4096)
     assert float(every.max()) > 0
     assert torch.equal(every, some)
+
+
+@pytest.mark.parametrize("n", [1, 64, 1023, 1024, 1025, 3000, 4096])
+@pytest.mark.parametrize("far", [False, True])
+def test_one_block_sort(n, far):
+    """Segments of up to 4096 keys, over three passes and (depths over more than
+    two octaves) four, of all Gaussians and of the kept ones of a ray mask, at the
+    parity bar of 1e-5 against the FP64 oracle."""
+    import synth
+    import paper_2607_02721_amd as gs
+    from oracle import oracle as ora
+    ora.build(force=False)
+    sc = synth.make_cluster_scene(n, 34, 1)
+    if far:
+        sc.mean *= np.float32(1) + np.float32(40) * (np.arange(n) % 3 == 0).astype(np.float32)
+    vw = synth.make_orbit_views(3, 35, 96, 40)
+    ref = ora.sensitivity(sc, vw)
+    keep = ~ref["flag"]
+    few = keep.reshape(3, 40, 96).copy()
+    few[:, :, 24:] = False
+    for sel in (keep, few.reshape(-1)):
+        bits = synth.pack_bits(sel)
+        want = ora.sensitivity(sc, vw, None, bits)["s"]
+        s, _ = gs.sensitivity(gs.DeviceScene.from_scene(sc), vw,
+                              ray_mask=torch.as_tensor(bits.view(np.int32)).cuda())
+        err = np.abs(s.cpu().numpy().astype(np.float64) - want) - (1e-5 * want + 1e-12)
+        assert err.max() <= 0
