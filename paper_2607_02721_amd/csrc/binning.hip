@@ -4,7 +4,7 @@
 // radix-sorted (depth key, index) sequence; ties by index because the sort is
 // stable and starts from index order).  A list entry is keyed by (tile, p)
 // and the lists are built by a counting sort on that key:
-//   1. count: one block per chunk of 2^10 to 2^14 consecutive positions counts its
+//   1. count: one block per chunk of 2^8 to 2^14 consecutive positions counts its
 //             entries per tile in LDS and stores them, one row per chunk;
 //   2. scan:  per tile, the exclusive prefix over chunks (in place) and the
 //             tile's total; a scan of the totals gives each tile's list start,

@@ -14,8 +14,8 @@ namespace gs {
 constexpr int kTileShiftDefault = 4;
 constexpr int kQuad = 8;           // compositing quadrant edge: one wave per 8x8 quadrant
 // Depth positions are binned in chunks of 2^bits (one list segment per tile
-// and chunk), 10 <= bits <= 14: see chunk_bits_for.
-constexpr int kChunkBitsMin = 10, kChunkBitsMax = 14;
+// and chunk), 8 <= bits <= 14: see chunk_bits_for.
+constexpr int kChunkBitsMin = 8, kChunkBitsMax = 14;
 // The counting kernel keeps a view's 2D difference array of
 // (tiles_x + 1)(tiles_y + 1) int32 cells in LDS beside its 4 KiB of row
 // words: 38 912 cells (152 KiB) fit the 160 KiB a workgroup may take on CDNA4.
@@ -223,10 +223,15 @@ inline int chunk_count(int64_t n, int chunk_bits) { return (int)((n + (1ll << ch
 // views at 1280x720 has 142 600 waves at 2^14 and keeps it.  With 16 384 as the
 // bound the second took 3250 us where 65 536 gave 2860, and twice as many or
 // more measured the same within 3%.
-constexpr int64_t kEmitWaves = 65536;
+// Below 2^10 positions the per-chunk work weighs (50k x 24 views with 2^8: 3%
+// slower), unless the emission then still leaves most of the chip's 4096 places
+// for its waves empty: 2k Gaussians x 4 views of 64x64 238 us with 2^10, 215 with
+// 2^8; 30k x 6 of 400x300 460 with 2^10, 438 with 2^9.
+constexpr int64_t kEmitWaves = 65536, kEmitPlaces = 4096;
 inline int chunk_bits_for(int64_t n, int64_t rows) {
     int bits = kChunkBitsMax;
-    while (bits > kChunkBitsMin && rows * chunk_count(n, bits) < kEmitWaves) --bits;
+    while (bits > 10 && rows * chunk_count(n, bits) < kEmitWaves) --bits;
+    while (bits > kChunkBitsMin && rows * chunk_count(n, bits) < kEmitPlaces) --bits;
     return bits;
 }
 // u64 words of the row bitmaps of Vc views with at most max_ty tile rows.

@@ -122,11 +122,11 @@ def test_depth_sort_segment_counts(views):
     assert torch.equal(one, two)
 
 
-@pytest.mark.parametrize("n", [1023, 1025, 30_000, 60_000])
+@pytest.mark.parametrize("n", [255, 257, 1023, 1025, 30_000, 60_000])
 @pytest.mark.parametrize("tile", [(16, 16), (32, 32), (8, 8)])
 def test_binning_chunk_lengths(n, tile):
     """The binning chunk follows the waves a call has: 200 views in one call
-    take longer chunks than single views (2^11 against 2^10 positions at
+    take longer chunks than single views (2^11 against 2^8 positions at
     60 000 Gaussians and 8-pixel rows).  The lists, and so the sensitivities,
     do not depend on it: one call of all views is the maximum of their own."""
     import synth
