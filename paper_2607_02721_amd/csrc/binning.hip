@@ -207,12 +207,15 @@ __global__ __launch_bounds__(kBinThreads) void k_chunk_prefix(const ViewDev *__r
 // execute in issue order, so later positions always receive later slots and every
 // (tile, chunk) segment is filled in increasing p.
 //
-// What bounds it is the chain of LDS accesses of a batch, some eight, at the 16
-// to 22 waves per CU that the lines in LDS leave room for (2.1 of its 3.0 ms are
-// vector instructions at 1M Gaussians x 100 views, 486 million entries of 32-pixel
-// tiles; writing them takes 0.5).  Scans for owners, an atomic add and a shuffle
-// for each run's slots and three reads per owner took 545 us at 300k x 20 views of
-// 1280x720 with 16-pixel tiles, 480 so.
+// Positions left over from full rounds of 64 wait for the next batch.
+//
+// What bounds it is the chain of LDS accesses of an item batch, some eight, at the
+// 20 or so waves per CU that the lines in LDS leave room for, and about 115 vector
+// instructions per item batch (2 of 2.8 ms at 1M Gaussians x 100 views, 486
+// million entries of 32-pixel tiles; writing them takes 0.5).  Scans for owners, an
+// atomic add and a shuffle for each run's slots, three reads per owner and partly
+// filled rounds at the end of every 2048 positions took 3.02 ms there and 545 us
+// at 300k x 20 views of 1280x720 with 16-pixel tiles (461 so).
 //
 // Entries are not stored one by one: each tile keeps the block ("line") of
 // its list that it is filling in LDS (slot = absolute entry index mod the
@@ -294,12 +297,14 @@ struct __align__(16) EmitTile {
     uint32_t cur, seg0;
 };
 
-// A position expanded by the wave: its index, its range in half tiles from
-// column c0 on, clipped to the wave's columns (first | last << 16), the halves of
-// the tile row it meets (1 top, 4 bottom), and its first item of the round.
-struct __align__(16) EmitPos {
-    uint32_t g, x, rows, first;
+// A position expanded by the wave: its index; and in one word its range in half
+// tiles from column c0 on, clipped to the wave's columns (first and last, a byte
+// each), the halves of the tile row it meets (3 bits: 1 top, 4 bottom) and its
+// first item of the round (13 bits: 64 positions of up to kEmitCols tiles).
+struct __align__(8) EmitPos {
+    uint32_t g, at;
 };
+static_assert(2 * 128 <= 256 && 64 * 128 <= 8192, "the fields of EmitPos::at");
 
 // LDS layout of one emission wave.
 struct EmitLds {
@@ -309,13 +314,13 @@ struct EmitLds {
     uint32_t *line;     // [tiles][2^kLineLog] the line each tile is filling
     uint32_t *mark;     // [64] the batch in which an item last started a position
     uint32_t *act;      // [tiles / 32] active tiles (masked form only)
-    uint16_t *queue;    // [batch] chunk-local positions meeting the rows
+    uint16_t *queue;    // [batch + 63] chunk-local positions meeting the rows
 };
 
 __host__ __device__ constexpr size_t emit_lds_bytes(int tiles, bool masked, int line_log, int batch) {
     return (size_t)tiles * (sizeof(EmitTile) + (sizeof(uint32_t) << line_log)) +
            (sizeof(EmitPos) + sizeof(uint2) + sizeof(uint32_t)) * kEmitWave +
-           (masked ? sizeof(uint32_t) * (((size_t)tiles + 31) / 32) : 0) + sizeof(uint16_t) * batch;
+           (masked ? sizeof(uint32_t) * (((size_t)tiles + 31) / 32) : 0) + sizeof(uint16_t) * ((size_t)batch + kEmitWave);
 }
 
 template <int kLine>
@@ -445,37 +450,43 @@ __global__ __launch_bounds__(kEmitWave) void k_bin_emit(const ViewDev *__restric
     static_assert(kEmitBatch % 64 == 0 && kEmitBatchMasked % 64 == 0 && kEmitBatch <= 64 * kEmitWave &&
                       kEmitBatchMasked <= 64 * kEmitWave, "one row-bitmap word per lane");
     uint32_t tick = 0u;
+    auto bitmap_word = [&](int b0) {    // of positions b0 + 64 lane ... + 63 of a batch
+        return lane < ((min(b0 + batch, hi) - b0 + 63) >> 6) ? __builtin_nontemporal_load(&rbits[(b0 >> 6) + lane]) : 0ull;
+    };
+    uint64_t ahead = bitmap_word(0);
+    int left = 0;                       // queued positions of the batches before
     for (int b0 = 0; b0 < hi; b0 += batch) {
-        const int b1 = min(b0 + batch, hi);
-        // 1. positions of the batch that meet row r0, in order: lane l < 16
-        // takes the bitmap word of positions b0 + 64 l ... + 63 (bits past the
-        // chunk's visible positions are clear), a wave prefix sum of the
-        // popcounts places each lane's positions in the queue
-        const int nw = (b1 - b0 + 63) >> 6;
-        uint64_t word = lane < nw ? __builtin_nontemporal_load(&rbits[(b0 >> 6) + lane]) : 0ull;
+        // 1. positions of the batch that meet row r0, in order: lane l takes
+        // the bitmap word of positions b0 + 64 l ... + 63 (bits past the chunk's
+        // visible positions are clear), a wave prefix sum of the popcounts
+        // places each lane's positions in the queue
+        uint64_t word = ahead;
+        if (b0 + batch < hi) ahead = bitmap_word(b0 + batch);
         const int cnt = __popcll(word);
         const int incl = wave_scan_add(cnt);
-        const int nq = __builtin_amdgcn_readlane(incl, kEmitWave - 1);
-        int slot = incl - cnt;
+        const int nq = left + __builtin_amdgcn_readlane(incl, kEmitWave - 1);
+        int slot = left + incl - cnt;
         while (word) {
             const int bit = __ffsll((long long)word) - 1;
             L.queue[slot++] = (uint16_t)(b0 + 64 * lane + bit);
             word &= word - 1ull;
         }
         wave_sync();
-        // 2. expansion of the queued positions against this wave's tiles; the
-        // next round's ranges and indices are loaded while this one expands
+        // 2. expansion of the queued positions against this wave's tiles, 64 at
+        // a time (what is left over waits for the next batch); the next round's
+        // ranges and indices are loaded while this one expands
+        const int rounds = b0 + batch < hi ? nq & ~(kEmitWave - 1) : nq;
         uint32_t nx_ = 0, ny_ = 0, ng_ = 0;
-        if (lane < nq) {
+        if (lane < rounds) {
             const int p = L.queue[lane];
             nx_ = xr_in[o + p];
             if (!half_ranges) ny_ = yr_in[o + p];
             ng_ = sorted_g[o + p];
         }
-        for (int base = 0; base < nq; base += kEmitWave) {
+        for (int base = 0; base < rounds; base += kEmitWave) {
             const int qi = base + lane;
             const uint32_t ux = nx_, uy = ny_, ug = ng_;
-            if (qi + kEmitWave < nq) {
+            if (qi + kEmitWave < rounds) {
                 const int p = L.queue[qi + kEmitWave];
                 nx_ = xr_in[o + p];
                 if (!half_ranges) ny_ = yr_in[o + p];
@@ -506,13 +517,11 @@ __global__ __launch_bounds__(kEmitWave) void k_bin_emit(const ViewDev *__restric
             // the tiles of its rectangle inside this wave's row and columns
             // (masked form: the active ones among them)
             int k = 0;
-            EmitPos mine;
-            mine.g = ug;
+            EmitPos mine{ug, 0u};
             if (qi < nq) {
                 const HalfRange h = half_range(half_ranges, ux, uy, sx, sy);
                 const int xa = max(h.xa - 2 * c0, 0), xb = min(h.xb - 2 * c0, 2 * ncols - 1);
-                mine.x = (uint32_t)xa | (uint32_t)xb << 16;
-                mine.rows = row_halves(h, r0);
+                mine.at = (uint32_t)(xa & 255) | (uint32_t)(xb & 255) << 8 | row_halves(h, r0) << 16;
                 if (kMasked) {
                     if (xa <= xb) {
                         uint64_t lo64 = act_lo, hi64 = act_hi;
@@ -526,7 +535,7 @@ __global__ __launch_bounds__(kEmitWave) void k_bin_emit(const ViewDev *__restric
             const int incl = wave_scan_add(k);
             const int K = __builtin_amdgcn_readlane(incl, kEmitWave - 1);
             const int excl = incl - k;   // first item of this lane's position
-            mine.first = (uint32_t)excl;
+            mine.at |= (uint32_t)excl << 19;
             const uint64_t with = __ballot(k > 0);
             if (k > 0) L.pos[__popcll(with & lanemask_lt64_bin())] = mine;
             for (int i0 = 0; i0 < K; i0 += kEmitWave) {
@@ -544,7 +553,7 @@ __global__ __launch_bounds__(kEmitWave) void k_bin_emit(const ViewDev *__restric
                 const int own = (int)__builtin_amdgcn_mbcnt_hi(
                     (uint32_t)(starts >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)starts, (uint32_t)carry));
                 const EmitPos P = L.pos[on ? own : 0];
-                const int j = i - (int)P.first, xa = (int)(P.x & 0xFFFFu), xb = (int)(P.x >> 16);
+                const int j = i - (int)(P.at >> 19), xa = (int)(P.at & 255u), xb = (int)((P.at >> 8) & 255u);
                 int t = (xa >> 1) + j;                 // tile within the wave
                 if (kMasked) {
                     uint64_t lo64 = act_lo, hi64 = act_hi;
@@ -552,7 +561,7 @@ __global__ __launch_bounds__(kEmitWave) void k_bin_emit(const ViewDev *__restric
                     if (on) t = nth_bit(lo64, hi64, j);
                 }
                 t = on ? t : 0;
-                const uint32_t val = P.g | (column_halves(xa, xb, t) * P.rows) << 28;
+                const uint32_t val = P.g | (column_halves(xa, xb, t) * ((P.at >> 16) & 7u)) << 28;
                 // Lanes on the same tile: each lane ORs its bit into its tile's
                 // 64-bit mask and reads the mask and the cursor back.  A lane's
                 // rank among them (lanes are in position order) is its offset from
@@ -588,7 +597,13 @@ __global__ __launch_bounds__(kEmitWave) void k_bin_emit(const ViewDev *__restric
                 wave_sync();
             }
         }
-        wave_sync();   // the queue is refilled by the next batch
+        wave_sync();
+        left = nq - rounds;
+        if (left > 0) {
+            const uint16_t p = lane < left ? L.queue[rounds + lane] : (uint16_t)0;
+            wave_sync();
+            if (lane < left) L.queue[lane] = p;
+        }
     }
     if (direct) return;
     // 3. the last, partly filled line of every tile whose segment ends inside one

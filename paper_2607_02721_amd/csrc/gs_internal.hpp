@@ -21,9 +21,9 @@ constexpr int kChunkBitsMin = 8, kChunkBitsMax = 14;
 // words: 38 912 cells (152 KiB) fit the 160 KiB a workgroup may take on CDNA4.
 constexpr int kMaxCellsPerView = 38912;
 constexpr int kSortTile = 4096;    // radix sort: keys per block (4 waves x 16 rounds x 64 lanes)
-// Emission: positions a wave queues at a time.  2048 leave less LDS to the other
-// waves of a CU (3% slower), 512 take 13% more; with a ray mask, whose waves use
-// little else of LDS, 1024 took 1472 us where 2048 take 1317.
+// Emission: positions a wave queues at a time.  2048 leave a CU room for fewer
+// waves, 512 make more batches (both 3 to 7% slower); with a ray mask, whose waves
+// use little else of LDS, 1024 took 17% more.
 constexpr int kEmitBatch = 1024, kEmitBatchMasked = 2048;
 constexpr uint32_t kInvisibleKey = 0xFFFFFFFFu;
 constexpr uint32_t kIndexMask = 0x0FFFFFFFu; // list entry = gaussian | quadrant mask << 28

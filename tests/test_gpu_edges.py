@@ -520,3 +520,28 @@ def test_one_block_sort(n, far):
                               ray_mask=torch.as_tensor(bits.view(np.int32)).cuda())
         err = np.abs(s.cpu().numpy().astype(np.float64) - want) - (1e-5 * want + 1e-12)
         assert err.max() <= 0
+
+
+@pytest.mark.parametrize("n", [1500, 2100, 9000])
+@pytest.mark.parametrize("masked", [False, True])
+def test_emission_carries_positions_between_batches(n, masked):
+    """Chunks of several batches (200 views in one call take chunks of up to
+    2^14 positions, queued 1024 or, with a ray mask, 2048 at a time) whose rows
+    meet few positions each, so that batches leave positions over: one call of
+    all views is the maximum of calls of one view, whose chunks are one batch."""
+    import synth
+    import paper_2607_02721_amd as gs
+    sc = synth.make_cluster_scene(n, 36, 0)
+    sc.log_scale[:] -= np.float32(1.5)
+    vw = synth.make_orbit_views(400, 37, 48, 1600)
+    d = gs.DeviceScene.from_scene(sc)
+    keep = np.ones((400, 1600, 48), bool)
+    if masked:
+        keep[:, ::2, :] = False
+    mask = lambda k: torch.as_tensor(synth.pack_bits(k.reshape(-1)).view(np.int32)).cuda() if masked else None
+    every, _ = gs.sensitivity(d, vw, ray_mask=mask(keep))
+    each = torch.zeros_like(every)
+    for v in range(400):
+        each = torch.maximum(each, gs.sensitivity(d, vw.subset([v]), ray_mask=mask(keep[v]))[0])
+    assert float(every.max()) > 0
+    assert torch.equal(every, each)
