@@ -431,7 +431,7 @@ __global__ __launch_bounds__(kEmitWave) void k_bin_emit(const ViewDev *__restric
     // the tile's cursor (lane a holds that of the a-th active tile).  The general
     // form's owner search, ranks and lines in LDS are a chain of some twenty LDS
     // accesses per round, which the 16 waves a CU has room for do not hide: 2.43
-    // -> 1.32 ms at 1M Gaussians x 100 views, 1% of the 8x8 blocks (three active
+    // -> 1.16 ms at 1M Gaussians x 100 views, 1% of the 8x8 blocks (three active
     // tiles of 80 per row; bounds of 16 and of 64 tiles measured alike).
     const int n_act = kMasked ? __popcll(act_lo) + __popcll(act_hi) : 0;
     const bool direct = kMasked && n_act <= kDirectTiles;

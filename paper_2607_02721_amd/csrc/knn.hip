@@ -1,7 +1,6 @@
 // Per-Gaussian features of the learned proposal: 59 attributes plus five
-// features of the k = 16 nearest neighbours of each mean (exact kNN on a
-// uniform grid; neighbours ordered by (squared distance, index), self
-// excluded).
+// features of the k = 16 nearest neighbours of each mean (exact kNN;
+// neighbours ordered by (squared distance, index), self excluded).
 //
 // Feature vector (64 float32 per Gaussian):
 //   0-2 mean, 3-5 log-scale, 6-9 normalised quaternion with w >= 0,

@@ -14,6 +14,7 @@
 //            before them, which keeps the sort stable; the block's start in
 //            each digit's run is the digit base plus the counts of the
 //            segment's earlier blocks, found by decoupled look-back.
+// Segments of one block (4096 items) or less: every pass in one launch.
 #include "gs_internal.hpp"
 
 namespace gs {
