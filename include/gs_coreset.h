@@ -319,9 +319,9 @@ typedef struct gs_plan gs_plan;
  * 4096 one-wave workgroups takes 8x8 quadrants from an atomic counter;
  * persistent = 0: one workgroup per quadrant, and xcd_remap = 1 renumbers
  * workgroups so that consecutive quadrants of a tile row land on one XCD
- * (shared L2); launches over more than 8192 regions of 16x16 pixels take the
- * tiles with the longest lists first instead, whatever xcd_remap says.  Default
- * {0, 1}. */
+ * (shared L2); launches over more than 8192 regions of 16x16 pixels (in a plan
+ * of one scene, up to 131072) take the tiles with the longest lists first
+ * instead, whatever xcd_remap says.  Default {0, 1}. */
 typedef struct {
     int32_t persistent;
     int32_t xcd_remap;

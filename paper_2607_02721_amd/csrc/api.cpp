@@ -959,7 +959,7 @@ gs_status gs_sensitivity(const gs_scene *scene, const gs_views *views, const gs_
             continue;
         }
         tm.mark(3, st);
-        if (!a.quad_list && order_pays((int64_t)a.total_tiles << a.region_log)) {
+        if (!a.quad_list && order_pays((int64_t)a.total_tiles << a.region_log, true)) {
             launch_tile_order(a, r.tile_order, r.order_classes, true, st);
             a.tile_order = r.tile_order;
         }
@@ -1080,7 +1080,7 @@ gs_status gs_render_objective(const gs_scene *scene, const gs_views *views, cons
             if (per_ray) launch_fill_u32((uint32_t *)(per_ray + S.ray_base[c.v0]), 0u, (int64_t)c.rays, st);
             a.quad_list = r.quad_list;
             a.n_listed = r.n_listed;
-        } else if (order_pays((int64_t)a.total_tiles << a.region_log)) {
+        } else if (order_pays((int64_t)a.total_tiles << a.region_log, true)) {
             launch_tile_order(a, r.tile_order, r.order_classes, true, st);
             a.tile_order = r.tile_order;
         }
@@ -1686,7 +1686,7 @@ void enqueue_plan(gs_plan *P, hipStream_t st, float *const *sens) {
             a.region_log = P->region_log;
             a.ccount = cb.compact ? G.ccount + ((size_t)cb.t0 << P->quad_log) : nullptr;
             a.report_floor = P->p.share_floor > 0.0f ? std::nextafter(P->p.share_floor, 0.0f) : 0.0f;
-            if (!a.work && order_pays((int64_t)a.total_tiles << a.region_log)) {
+            if (!a.work && order_pays((int64_t)a.total_tiles << a.region_log, G.scenes.size() == 1)) {
                 launch_tile_order(a, G.tile_order, G.order_classes, false, st);
                 a.tile_order = G.tile_order;
             }

@@ -346,8 +346,16 @@ void launch_one_scene(const SceneSlot &slot, SceneSlot *slot_dev, int32_t *tile_
 // Whether a launch of this many regions takes it.  The chip holds about 7 168
 // of these waves at once: fewer all start together, in any order (3 800 regions
 // lost 3%, 7 280 2%), and from 12 500 on the tail of a launch in tile order,
-// with the dense tiles anywhere, is worth more than the ordering's 20 us.
-inline bool order_pays(int64_t regions) { return regions > 8192; }
+// with the dense tiles anywhere, is worth more than the ordering's 20 us.  With
+// many rounds of waves the tail of one scene's views is short and neighbouring
+// tiles, whose records an XCD's L2 then still holds, weigh more (600k Gaussians x
+// 50 views, 180 000 regions: 9.48 ms ordered, 9.26 in tile order; 2M x 60, 348 000:
+// 21.2 and 20.7; 1M x 100, 368 000: alike, with 26 GB read by pass 1 instead of 11);
+// several scenes in one launch end in the densest one's tail instead (a plan of
+// four, 230 400 regions: 5.8 ms ordered, 6.7 in tile order).
+inline bool order_pays(int64_t regions, bool one_scene) {
+    return regions > 8192 && (!one_scene || regions <= 131072);
+}
 // Whether a launch of this many regions runs one wave per quadrant instead.  A
 // region's wave takes its entries one after the other through up to four
 // quadrants behind branches, some 400 cycles each when nothing else shares its

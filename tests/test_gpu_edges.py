@@ -545,3 +545,19 @@ def test_emission_carries_positions_between_batches(n, masked):
         each = torch.maximum(each, gs.sensitivity(d, vw.subset([v]), ray_mask=mask(keep[v]))[0])
     assert float(every.max()) > 0
     assert torch.equal(every, each)
+
+
+@pytest.mark.parametrize("aggregate", ["ray", "image"])
+def test_many_regions_in_tile_order(aggregate):
+    """132 600 regions of one scene composite in tile order, 52 000 at a time by
+    descending list length (or by quadrants): the same sensitivities."""
+    import synth
+    import paper_2607_02721_amd as gs
+    sc = synth.make_cluster_scene(3000, 38, 1)
+    vw = synth.make_orbit_views(510, 39, 320, 208)
+    d = gs.DeviceScene.from_scene(sc)
+    agg = {"ray": gs.AGG_RAY, "image": gs.AGG_IMAGE}[aggregate]
+    every, _ = gs.sensitivity(d, vw, aggregate=agg)
+    some, _ = gs.sensitivity(d, vw, aggregate=agg, max_views_per_chunk=200)
+    assert float(every.max()) > 0
+    assert torch.equal(every, some)
