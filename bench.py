@@ -45,10 +45,10 @@ PEAK_MFMA_BF16 = 2.5e15
 # multiply-add of its four layers.
 MLP_FLOP_PER_ROW = 2 * (64 * 256 + 256 * 256 + 256 * 256 + 256 * 1)
 # Algorithmic bytes of the tile-list emission kernel: per visible (view,
-# Gaussian) position its two packed pixel ranges and its index are read once
-# (12 B); per (tile, chunk) segment its start offset is read once (8 B); per
+# Gaussian) position its range in half tiles and its index are read once
+# (8 B); per (tile, chunk) segment its start offset is read once (8 B); per
 # list entry one 4-byte word is written.
-EMIT_BYTES_POSITION, EMIT_BYTES_BIN, EMIT_BYTES_ENTRY = 12, 8, 4
+EMIT_BYTES_POSITION, EMIT_BYTES_BIN, EMIT_BYTES_ENTRY = 8, 8, 4
 # Measured HBM traffic of the dominant kernels (rocprofv3 --pmc FETCH_SIZE /
 # WRITE_SIZE, scaled by a plain copy of known size), with the hash of the
 # kernel source the counters were taken on.
