@@ -1644,6 +1644,7 @@ void enqueue_front(const gs_plan *P, PlanScene &ps, hipStream_t st) {
                 ps.sc.quat, ps.sc.opacity, ps.sc.sh};
     ProjParams pp{P->p.footprint_sigma, P->p.dilation, P->p.z_near, P->p.query_mode};
     launch_project(sd, ps.views_dev, ps.c.vc, pp, b, st);
+    if (ps.passes == 3) launch_span_check(b, ps.c.vc, ps.over, P->flag, st);
     uint32_t *skeys = nullptr;
     radix_sort_segments(b.key0, b.val0, b.key1, b.val1, b.hist, N, ps.c.vc, true, ps.passes,
                         ps.passes == 3 ? b.kmin : nullptr, nullptr, &skeys, &ps.sorted_g, st);
@@ -1663,7 +1664,6 @@ void enqueue_plan(gs_plan *P, hipStream_t st, float *const *sens) {
         for (int si : G.scenes) {
             PlanScene &ps = P->scenes[si];
             enqueue_front(P, ps, st);
-            if (ps.passes == 3) launch_span_check(ps.b.kmin, ps.c.vc, ps.over, P->flag, st);
             launch_list_guard(ps.b.tile_off, ps.c.total_tiles, ps.cap, ps.over, P->flag, ps.passes == 3, st);
             launch_bin_emit(ps.views_dev, ps.c.vc, ps.S.N, ps.S.nchunks, ps.b, ps.xr, ps.yr, ps.sorted_g,
                             ps.max_tx, ps.max_ty, ps.cap, ps.S.tsx, st);

@@ -675,18 +675,21 @@ void launch_bin_emit(const ViewDev *views_dev, int Vc, int64_t N, int nchunks, c
         line_log == 4 ? go(k_bin_emit<false, 4>) : go(k_bin_emit<false, 3>);
 }
 
-// Capacity guard for lists sized in advance (plans): if the counted entries
-// exceed the capacity, flag it and empty every list of the scene so that no
-// later kernel reads past the buffer.
-// Plan guards.  A scene whose lists outgrow their capacity, or (with the
-// three-pass depth sort) whose view's depth keys span 2^24 or more, gets
-// empty lists this run (its output is zero) and raises the sticky flag.
-__global__ void k_span_check(const uint32_t *__restrict__ kmin, int Vc, uint32_t *__restrict__ over,
-                             uint32_t *__restrict__ flag) {
+// Plan guards.  Lists sized in advance: if the counted entries exceed the
+// capacity, every list of the scene is emptied, so that no later kernel reads
+// past the buffer.  Three-pass depth sorts: a view's depth keys that span 2^24 - 1
+// or more no longer sort before the invisible ones, which have no ranges, so the
+// scene's views then hold no position at all; this runs before the sort, and
+// nothing after it reads a position.  Either way the scene's output is zero this
+// run and the sticky flag is raised.
+__global__ void k_span_check(const uint32_t *__restrict__ kmin, int Vc, uint32_t *__restrict__ nvis,
+                             uint32_t *__restrict__ over, uint32_t *__restrict__ flag) {
     bool bad = false;
     for (int v = threadIdx.x; v < Vc; v += blockDim.x)
         bad = bad || (kmin[Vc + v] >= kmin[v] && kmin[Vc + v] - kmin[v] >= 0xFFFFFFu);
     bad = __any(bad);
+    if (bad)
+        for (int v = threadIdx.x; v < Vc; v += blockDim.x) nvis[v] = 0u;
     if (threadIdx.x == 0) {
         *over = bad ? 1u : 0u;
         if (bad) atomicOr(flag, kGuardSpan);
@@ -702,8 +705,8 @@ __global__ void k_guard_apply(uint64_t *__restrict__ tile_off, int64_t ntiles, c
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (*over && i <= ntiles) tile_off[i] = 0;
 }
-void launch_span_check(const uint32_t *kmin, int Vc, uint32_t *over, uint32_t *flag, hipStream_t st) {
-    hipLaunchKernelGGL(k_span_check, dim3(1), dim3(64), 0, st, kmin, Vc, over, flag);
+void launch_span_check(const ChunkBufs &b, int Vc, uint32_t *over, uint32_t *flag, hipStream_t st) {
+    hipLaunchKernelGGL(k_span_check, dim3(1), dim3(64), 0, st, b.kmin, Vc, b.nvis, over, flag);
 }
 void launch_list_guard(uint64_t *tile_off, int64_t ntiles, uint64_t cap, uint32_t *over, uint32_t *flag, bool keep,
                        hipStream_t st) {

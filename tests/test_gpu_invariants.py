@@ -1,0 +1,63 @@
+"""What calls answer at the limits of a rule: depth spans past a plan's sort,
+degenerate and very large Gaussians, equal results however a call is cut up."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+pytestmark = pytest.mark.gpu
+
+
+def _front_view(width, height, focal, n_views=1, turn=0.0):
+    """Cameras at the origin that look along +z, rolled by `turn`."""
+    import synth
+    c, s = np.cos(turn), np.sin(turn)
+    P = np.array([[c, -s, 0, 0], [s, c, 0, 0], [0, 0, 1, 0]], float).reshape(1, 12)
+    K = np.array([[focal, focal, width / 2, height / 2]], float)
+    return synth.Views(np.repeat(P, n_views, 0), np.repeat(K, n_views, 0),
+                       np.array([[width, height]] * n_views, dtype=np.int32))
+
+
+# both forms of the sort (one block for up to 4096 keys), ranges in half tiles and
+# (from 129 tiles across) in pixels
+@pytest.mark.parametrize("n", [700, 9000])
+@pytest.mark.parametrize("width", [96, 2080])
+def test_plan_depth_span_with_invisible_gaussians(n, width):
+    """A plan sorts a scene's depth keys by their low 24 bits when they span
+    less at creation.  Attributes that change in place so that a key lies exactly
+    2^24 - 1 past the nearest one tie with the Gaussians off screen, which come
+    first by index and have no ranges: the scene's output is 0, the other scene's
+    stands, and with the old attributes the first one's is what it was."""
+    import synth
+    import paper_2607_02721_amd as gs
+    rng = np.random.default_rng(n)
+    vw = _front_view(width, 48, 60.0, 3)
+    mean = np.stack([rng.uniform(-0.5, 0.5, n), rng.uniform(-0.3, 0.3, n), rng.uniform(2.5, 7.0, n)], 1)
+    mean[: n // 2, 0] += 1000.0                      # off screen
+    mean[-1] = (0.0, 0.0, 2.0)
+    d = gs.DeviceScene.from_scene(synth.make_explicit_scene(mean, -3.0, (1.0, 0, 0, 0), 0.5, 1.0))
+    other = gs.DeviceScene.from_scene(synth.make_cluster_scene(3000, 41, 1))
+    other_views = synth.make_orbit_views(3, 42, 80, 48)
+    plan = gs.Plan([d, other], [vw, other_views])
+    assert plan.info()["n_sort3_scenes"] == 2
+    first, second = [o.clone() for o in plan.run()]
+    torch.cuda.synchronize()
+    plan.status()
+    assert float(first.max()) > 0 and float(second.max()) > 0
+    old = float(d.mean[2, -2])
+    near = np.float32(2.0).view(np.uint32)
+    d.mean[2, -2] = float((near + np.uint32(0xFFFFFF)).view(np.float32))
+    out = [o.clone() for o in plan.run()]
+    torch.cuda.synchronize()
+    with pytest.raises(gs.GsError) as e:
+        plan.status()
+    assert e.value.status == 5 and "depth keys spanned" in str(e.value)
+    assert float(out[0].abs().max()) == 0
+    assert torch.equal(out[1], second)
+    d.mean[2, -2] = old
+    out = plan.run()
+    torch.cuda.synchronize()
+    assert torch.equal(out[0], first) and torch.equal(out[1], second)
+    plan.close()
