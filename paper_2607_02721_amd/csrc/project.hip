@@ -215,7 +215,10 @@ __global__ __launch_bounds__(kProjThreads) void k_project(SceneDev sc, const Vie
             const double sxx = fma(T0[0], u0[0], fma(T0[1], u0[1], fma(T0[2], u0[2], (double)pp.dilation)));
             const double sxy = fma(T0[0], u1[0], fma(T0[1], u1[1], T0[2] * u1[2]));
             const double syy = fma(T1[0], u1[0], fma(T1[1], u1[1], fma(T1[2], u1[2], (double)pp.dilation)));
-            const double det = fma(sxx, syy, -(sxy * sxy));
+            // (two rounded products: a needle seen along a diagonal has three equal
+            // entries and exactly no area; fused, the difference would be the
+            // rounding error of one product, and half of them visible)
+            const double det = sxx * syy - sxy * sxy;
             const double mx = fma(V.fx, ax, V.cx);
             const double my = fma(V.fy, ay, V.cy);
             // (square roots to 2^-45, far inside cut_pad; NaN where det > 0 fails)

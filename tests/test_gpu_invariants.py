@@ -61,3 +61,29 @@ def test_plan_depth_span_with_invisible_gaussians(n, width):
     torch.cuda.synchronize()
     assert torch.equal(out[0], first) and torch.equal(out[1], second)
     plan.close()
+
+
+def test_needles_without_area_are_absent():
+    """Gaussians of one dimension, without dilation, seen by a camera rolled by
+    45 degrees: the entries of the 2D covariance are equal, so it has no inverse
+    and the Gaussian is absent, as in the FP64 oracle; with the default dilation
+    every one is there."""
+    import synth
+    import paper_2607_02721_amd as gs
+    from oracle import oracle as ora
+    ora.build(force=False)
+    n = 200
+    rng = np.random.default_rng(1)
+    mean = np.zeros((n, 3))
+    mean[:, 2] = rng.uniform(1.5, 4.0, n)
+    scale = np.full((n, 3), -400.0)                 # exp(2 x -400) is 0 in FP64
+    scale[:, 0] = rng.uniform(-4.0, 0.0, n)
+    sc = synth.make_explicit_scene(mean, scale, (1.0, 0, 0, 0), 0.5, 1.0)
+    vw = _front_view(64, 64, 60.0)
+    vw.world_to_cam[0, [0, 1, 4, 5]] = np.sqrt(0.5) * np.array([1, -1, 1, 1])
+    d = gs.DeviceScene.from_scene(sc)
+    s, st = gs.sensitivity(d, vw, stats=True)
+    assert st["n_projected"] == n and float(s.max()) > 0
+    assert float(np.max(ora.sensitivity(sc, vw, ora.default_params(dilation=0.0))["s"])) == 0
+    s, st = gs.sensitivity(d, vw, dilation=0.0, stats=True)
+    assert st["n_projected"] == 0 and float(s.max()) == 0
