@@ -7,10 +7,11 @@
 // record, the colour factor, the packed pixel ranges and a depth key.
 // Set-up runs in FP64 (the vector FP64 rate equals the non-packed FP32 rate
 // on CDNA4), so the float32 record fields carry only their own rounding.  FP64
-// issue and the record stores bound it: with fused multiply-adds, one reciprocal
-// instead of three divisions and Newton steps instead of IEEE divisions and
-// square roots it takes 1.65 ms at 1M Gaussians x 100 views (4.8 GB written)
-// where it took 1.95.
+// issue and the record stores bound it: with fused multiply-adds, kept pairs'
+// records only, one reciprocal for three quotients and Newton steps in place of
+// the IEEE sequences it takes 1.62 ms at 1M Gaussians x 100 views (4.8 GB written)
+// where it took 1.95 (1.58 without the corrections that make the quotients and
+// roots as accurate as IEEE operations).
 //
 // Records (all float32 unless noted):
 //   geo.m = mean2d as float hi + float lo (x_hi, y_hi, x_lo, y_lo)
@@ -71,23 +72,36 @@ __device__ __forceinline__ uint32_t wave_min_u32(uint32_t v) {
     return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
 }
 
-// 1 / x and 1 / sqrt(x) in FP64 from the hardware's estimates (v_rcp_f64,
-// v_rsq_f64: about 2^-23) by two Newton steps: five and seven instructions where
-// an IEEE division takes eleven and a square root and a division 25.  Within 2
-// ulp for normal arguments well inside the range, which the callers see to.
+// Quotients and roots in FP64 from the hardware's estimates (v_rcp_f64, v_rsq_f64:
+// about 2^-24) by Newton steps, the last of which takes its residual from a fused
+// product, so that what is left is the rounding of the result: five instructions
+// for 1/x and ten for 1/sqrt(x), where an IEEE division takes eleven and a square
+// root and a division 25.  Over 2 x 10^8 arguments from 2^-900 to 2^900, rcp64 and
+// sqrt64 gave the IEEE results bit for bit, and so did div64 with rcp64 for r;
+// rsq64 is off by at most 1.0 x 2^-53 of its value, where 1.0 / sqrt(x) with IEEE
+// operations is off by up to 1.5.  The callers see to arguments inside that range.
 __device__ __forceinline__ double rcp64(double x) {
     double r = __builtin_amdgcn_rcp(x);
     r = fma(fma(-x, r, 1.0), r, r);
     return fma(fma(-x, r, 1.0), r, r);
 }
+// n / x from the rounded quotient q and r = 1 / x, both within a few ulp.
+__device__ __forceinline__ double div64(double n, double x, double q, double r) { return fma(fma(-x, q, n), r, q); }
 __device__ __forceinline__ double rsq64_once(double x) {
     const double r = __builtin_amdgcn_rsq(x);
     return r * fma(-(0.5 * x * r), r, 1.5);
 }
 __device__ __forceinline__ double rsq64(double x) {
-    const double r = rsq64_once(x);
-    return r * fma(-(0.5 * x * r), r, 1.5);
+    const double r = rsq64_once(x), h = x * r;
+    return fma(0.5 * r, fma(-fma(x, r, -h), r, fma(-h, r, 1.0)), r);
 }
+__device__ __forceinline__ double sqrt64(double x) {
+    const double r = rsq64_once(x), s = x * r;
+    return fma(fma(-s, s, x), 0.5 * r, s);
+}
+// Arguments whose reciprocals, products and quotients stay inside that range.
+constexpr double kOrdinary = 1e140;
+__device__ __forceinline__ bool ordinary(double x) { return x > 1.0 / kOrdinary && x < kOrdinary; }
 
 // Real spherical harmonics (orthonormal, degree <= 3) at unit direction d.
 __device__ __forceinline__ void sh_basis(double x, double y, double z, double *Y) {
@@ -195,7 +209,7 @@ __global__ __launch_bounds__(kProjThreads) void k_project(SceneDev sc, const Vie
         float4 r3 = make_float4(0, 0, 0, 0);
         float cbar = 0.0f;
         if (vis) {
-            const double iz = rcp64(pz);
+            const double iz = pz < kOrdinary ? rcp64(pz) : 1.0 / pz;
             // T = J R (2x3), J = [[fx/z, 0, -fx x/z^2], [0, fy/z, -fy y/z^2]]:
             // row 0 is fx/z (R_0 - x/z R_2), row 1 fy/z (R_1 - y/z R_2)
             const double ax = px * iz, ay = py * iz;
@@ -221,8 +235,14 @@ __global__ __launch_bounds__(kProjThreads) void k_project(SceneDev sc, const Vie
             const double det = sxx * syy - sxy * sxy;
             const double mx = fma(V.fx, ax, V.cx);
             const double my = fma(V.fy, ay, V.cy);
-            // (square roots to 2^-45, far inside cut_pad; NaN where det > 0 fails)
-            const double rx = r * (sxx * rsq64_once(sxx)), ry = r * (syy * rsq64_once(syy));
+            double rx, ry;
+            if (ordinary(sxx) && ordinary(syy)) {
+                rx = r * sqrt64(sxx);
+                ry = r * sqrt64(syy);
+            } else {
+                rx = r * sqrt(sxx);
+                ry = r * sqrt(syy);
+            }
             double xl = ceil(mx - rx - 0.5 - cut_pad), xh = floor(mx + rx - 0.5 + cut_pad);
             double yl = ceil(my - ry - 0.5 - cut_pad), yh = floor(my + ry - 0.5 + cut_pad);
             xl = fmax(xl, 0.0); yl = fmax(yl, 0.0);
@@ -230,25 +250,26 @@ __global__ __launch_bounds__(kProjThreads) void k_project(SceneDev sc, const Vie
             vis = det > 0.0 && syy > 0.0 && xl <= xh && yl <= yh;
             if (vis) {
                 const double log2e = 1.4426950408889634;
-                // 1/syy and syy/det from one reciprocal (by divisions outside
-                // its range)
-                const double w = syy * det;
-                double a, gm;
-                if (w > 1e-280 && w < 1e280) {
-                    const double inv = rcp64(w);
-                    gm = det * inv;
-                    a = (syy * inv) * syy;
+                // 1/syy, syy/det and -sxy/syy from one reciprocal (by divisions
+                // outside its range)
+                double a, gm, beta;
+                if (ordinary(det) && ordinary(syy)) {
+                    const double inv = rcp64(syy * det), g0 = det * inv, id = syy * inv;
+                    gm = div64(1.0, syy, g0, g0);
+                    a = div64(syy, det, syy * id, id);
+                    beta = div64(-sxy, syy, -sxy * gm, gm);
                 } else {
                     gm = 1.0 / syy;
                     a = syy / det;
+                    beta = -sxy / syy;
                 }
-                const double beta = -sxy * gm;
                 const float hx = (float)mx, hy = (float)my;
                 r0 = make_float4(hx, hy, (float)(mx - (double)hx), (float)(my - (double)hy));
                 r1 = make_float4((float)beta, (float)(-0.5 * log2e * a), (float)(-0.5 * log2e * gm), alpha);
                 // colour at the direction camera centre -> mean
                 double d0 = mu[0] - V.cam[0], d1 = mu[1] - V.cam[1], d2 = mu[2] - V.cam[2];
-                const double dn = rsq64(fma(d0, d0, fma(d1, d1, d2 * d2)));
+                const double dd = fma(d0, d0, fma(d1, d1, d2 * d2));
+                const double dn = ordinary(dd) ? rsq64(dd) : 1.0 / sqrt(dd);
                 double Y[16];
                 sh_basis(d0 * dn, d1 * dn, d2 * dn, Y);
                 // the coefficients stay float32 in registers and are widened

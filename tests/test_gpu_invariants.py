@@ -87,3 +87,24 @@ def test_needles_without_area_are_absent():
     assert float(np.max(ora.sensitivity(sc, vw, ora.default_params(dilation=0.0))["s"])) == 0
     s, st = gs.sensitivity(d, vw, dilation=0.0, stats=True)
     assert st["n_projected"] == 0 and float(s.max()) == 0
+
+
+def test_ranges_of_very_large_footprints():
+    """Footprints of 4.5 to 9 x 10^15 pixels in radius, where FP64 numbers are 1
+    pixel apart, whose edge crosses the view: the tiles they list are those right of
+    the edge (at most a pixel or two off by rounding; the edges stand 4 pixels from
+    a tile's border)."""
+    import synth
+    import paper_2607_02721_amd as gs
+    rng = np.random.default_rng(2)
+    sc = synth.make_explicit_scene([[0.0, 0.0, 2.0]], 0.0, (1.0, 0, 0, 0), 0.5, 1.0)
+    d = gs.DeviceScene.from_scene(sc)
+    vw = _front_view(1024, 16, 60.0)
+    for k in range(48):
+        fx = float(rng.uniform(3.0e15, 5.9e15))
+        radius = 3.0 * np.sqrt((0.5 * fx) ** 2 + np.float64(np.float32(0.3)))
+        tile = int(rng.integers(1, 63))
+        vw.intrinsics[0, 0] = fx
+        vw.intrinsics[0, 2] = radius + 16 * tile + (4 if k % 2 else 12)
+        _, st = gs.sensitivity(d, vw, stats=True)
+        assert st["n_entries"] == 64 - tile, (k, fx, tile)
