@@ -871,6 +871,8 @@ gs_status gs_sensitivity(const gs_scene *scene, const gs_views *views, const gs_
     // every granularity composites on compacted lists
     S.compact = true;
     const auto chunks = plan_chunks(views, S, params, scratch_budget());
+    int64_t call_regions = 0;
+    for (const ChunkPlan &c : chunks) call_regions += (int64_t)c.total_tiles << region_log_of(S.tsx, S.tsy);
     launch_fill_u32((uint32_t *)sens, 0u, S.N, st);
     // per-scene queries: the absolute contributions and A summed over chunks
     double *agg_num = nullptr, *agg_den = nullptr;
@@ -966,7 +968,7 @@ gs_status gs_sensitivity(const gs_scene *scene, const gs_views *views, const gs_
         // (counting calls keep the region form: their pair counters say what
         // its 64-entry slices walk)
         a.by_quads = !a.quad_list && S.agg != GS_AGG_TILE && !(params->flags & GS_FLAG_COUNT_PAIRS) &&
-                     quads_pay((int64_t)a.total_tiles << a.region_log);
+                     quads_pay(S.agg == GS_AGG_RAY ? (int64_t)a.total_tiles << a.region_log : call_regions);
         launch_composite_pass1(a, st);
         HIP_TRY(hipGetLastError());
         tm.mark(4, st);

@@ -367,6 +367,11 @@ inline bool order_pays(int64_t regions, bool one_scene) {
 // Gaussians x 2 views at 400x300, 950 regions, 1590 and 660 us; 20k x 24, 11 400
 // regions, per image 990 and 590; 50k x 24 at 640x360, 22 080 regions, 1135 and
 // 1109; 250k x 20 at 960x540, 40 800 regions, 2460 and 2990.)
+// Past the slice in which the last ray of a quadrant stopped, the two forms leave
+// out different entries (each below the share floor).  Per-ray shares there are not
+// reported, so they are the same either way; per-image and per-scene sums differ
+// in their last bits, so those calls decide once, by the regions of all of their
+// views, and their results do not depend on how many views a chunk holds.
 constexpr int64_t kByQuads = 32768;
 inline bool quads_pay(int64_t regions) { return regions <= kByQuads; }
 void launch_composite_pass1(const CompositeArgs &a, hipStream_t st);

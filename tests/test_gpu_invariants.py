@@ -108,3 +108,27 @@ def test_ranges_of_very_large_footprints():
         vw.intrinsics[0, 2] = radius + 16 * tile + (4 if k % 2 else 12)
         _, st = gs.sensitivity(d, vw, stats=True)
         assert st["n_entries"] == 64 - tile, (k, fx, tile)
+
+
+@pytest.mark.parametrize("mode", ["rgbsum", "l2"])
+@pytest.mark.parametrize("floor", [1e-12, 1e-2])
+@pytest.mark.parametrize("aggregate", ["ray", "image"])
+def test_results_do_not_depend_on_the_chunks(mode, floor, aggregate):
+    """36 864 regions in one call and 3 072 at a time: per-ray results are maxima
+    of shares, per-image ones maxima over the views of exact integer sums, so how
+    many views a chunk holds (which the free memory decides) changes no bit, also
+    where rays stop early."""
+    import synth
+    import paper_2607_02721_amd as gs
+    sc = synth.make_cluster_scene(20_000, 43, 1)
+    sc.log_scale[:] += np.float32(1.0)
+    sc.opacity[:] = np.float32(0.9)
+    vw = synth.make_orbit_views(12, 44, 1024, 768)
+    d = gs.DeviceScene.from_scene(sc)
+    qm = {"rgbsum": gs.QUERY_RGBSUM, "l2": gs.QUERY_L2}[mode]
+    kw = dict(query_mode=qm, aggregate={"ray": gs.AGG_RAY, "image": gs.AGG_IMAGE}[aggregate], share_floor=floor)
+    every, _ = gs.sensitivity(d, vw, **kw)
+    assert float(every.max()) > 0
+    for k in (1, 5):
+        some, _ = gs.sensitivity(d, vw, max_views_per_chunk=k, **kw)
+        assert torch.equal(every, some), k
