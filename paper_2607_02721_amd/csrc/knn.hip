@@ -265,22 +265,24 @@ __device__ __forceinline__ uint32_t wave_min_bits(uint32_t v) {
 // Inserting word w into the ascending list b: b[k] = min(b[k], max(b[k-1], w))
 // from the last to the first, in place (31 instructions, two temporaries; as
 // separate statements the compiler holds all sixteen maxima at once, and the
-// kernel spills).
+// kernel spills).  The list's registers are written before the last input is read,
+// so none of them may be an input's, which the compiler would share where it knows
+// the values to be equal, as at the start: hence the early clobbers.
 __device__ __forceinline__ void insert_word(double (&b)[16], double w) {
     double t0, t1;
     asm("v_max_f64 %8, %6, %11\n v_max_f64 %9, %5, %11\n v_min_f64 %7, %7, %8\n v_min_f64 %6, %6, %9\n"
         "v_max_f64 %8, %4, %11\n v_max_f64 %9, %3, %11\n v_min_f64 %5, %5, %8\n v_min_f64 %4, %4, %9\n"
         "v_max_f64 %8, %2, %11\n v_max_f64 %9, %1, %11\n v_min_f64 %3, %3, %8\n v_min_f64 %2, %2, %9\n"
         "v_max_f64 %8, %0, %11\n v_max_f64 %9, %10, %11\n v_min_f64 %1, %1, %8\n v_min_f64 %0, %0, %9\n"
-        : "+v"(b[8]), "+v"(b[9]), "+v"(b[10]), "+v"(b[11]), "+v"(b[12]), "+v"(b[13]), "+v"(b[14]), "+v"(b[15]),
-          "=&v"(t0), "=&v"(t1)
+        : "+&v"(b[8]), "+&v"(b[9]), "+&v"(b[10]), "+&v"(b[11]), "+&v"(b[12]), "+&v"(b[13]), "+&v"(b[14]),
+          "+&v"(b[15]), "=&v"(t0), "=&v"(t1)
         : "v"(b[7]), "v"(w));
     asm("v_max_f64 %8, %6, %10\n v_max_f64 %9, %5, %10\n v_min_f64 %7, %7, %8\n v_min_f64 %6, %6, %9\n"
         "v_max_f64 %8, %4, %10\n v_max_f64 %9, %3, %10\n v_min_f64 %5, %5, %8\n v_min_f64 %4, %4, %9\n"
         "v_max_f64 %8, %2, %10\n v_max_f64 %9, %1, %10\n v_min_f64 %3, %3, %8\n v_min_f64 %2, %2, %9\n"
         "v_max_f64 %8, %0, %10\n v_min_f64 %0, %0, %10\n v_min_f64 %1, %1, %8\n"
-        : "+v"(b[0]), "+v"(b[1]), "+v"(b[2]), "+v"(b[3]), "+v"(b[4]), "+v"(b[5]), "+v"(b[6]), "+v"(b[7]), "=&v"(t0),
-          "=&v"(t1)
+        : "+&v"(b[0]), "+&v"(b[1]), "+&v"(b[2]), "+&v"(b[3]), "+&v"(b[4]), "+&v"(b[5]), "+&v"(b[6]), "+&v"(b[7]),
+          "=&v"(t0), "=&v"(t1)
         : "v"(w));
 }
 __device__ __forceinline__ double word_of(float d2, uint32_t i) {
