@@ -132,3 +132,31 @@ def test_results_do_not_depend_on_the_chunks(mode, floor, aggregate):
     for k in (1, 5):
         some, _ = gs.sensitivity(d, vw, max_views_per_chunk=k, **kw)
         assert torch.equal(every, some), k
+
+
+@pytest.mark.parametrize("kind,n", [("point", 33), ("point", 2049), ("point", 10_000), ("pairs", 6000),
+                                    ("lattice", 8000), ("lattice", 27_000)])
+def test_knn_of_ties(kind, n):
+    """Clouds in which most distances are equal (all means in one place, in two,
+    on a shuffled lattice): ties go to the smaller index, bit for bit as by
+    comparing every pair."""
+    import paper_2607_02721_amd as gs
+    from paper_2607_02721_amd import learned
+    g = torch.Generator(device="cuda").manual_seed(n)
+    if kind == "lattice":
+        side = round(n ** (1 / 3))
+        m = torch.stack(torch.meshgrid(*[torch.arange(float(side), device="cuda")] * 3, indexing="ij")).reshape(3, -1)
+        m = m[:, torch.randperm(n, generator=g, device="cuda")]
+    else:
+        m = torch.full((3, n), 0.25, device="cuda")
+        if kind == "pairs":
+            m[0] += torch.randint(0, 2, (n,), generator=g, device="cuda")
+    one = lambda *s: torch.ones(*s, device="cuda")  # noqa: E731
+    idx, d2 = learned.knn(gs.DeviceScene(m.contiguous(), -one(3, n), one(4, n), one(n), one(1, 3, n), 0))
+    rows = torch.randperm(n, generator=g, device="cuda")[:700]
+    d = ((m[:, None] - m[:, rows, None]) ** 2).sum(0)       # exact: multiples of 1/16
+    key = (d.view(torch.int32).long() << 32) | torch.arange(n, device="cuda")[None]
+    key[torch.arange(len(rows), device="cuda"), rows] = torch.iinfo(torch.int64).max
+    best = torch.topk(key, 16, dim=1, largest=False).values.sort(1).values
+    assert torch.equal(idx[rows], (best & 0xFFFFFFFF).int())
+    assert torch.equal(d2[rows], (best >> 32).int().view(torch.float32))
