@@ -1688,7 +1688,7 @@ void enqueue_plan(gs_plan *P, hipStream_t st, float *const *sens) {
             a.region_log = P->region_log;
             a.ccount = cb.compact ? G.ccount + ((size_t)cb.t0 << P->quad_log) : nullptr;
             a.report_floor = P->p.share_floor > 0.0f ? std::nextafter(P->p.share_floor, 0.0f) : 0.0f;
-            if (!a.work && order_pays((int64_t)a.total_tiles << a.region_log, G.scenes.size() == 1)) {
+            if (!a.work && a.xcd_remap && order_pays((int64_t)a.total_tiles << a.region_log, G.scenes.size() == 1)) {
                 launch_tile_order(a, G.tile_order, G.order_classes, false, st);
                 a.tile_order = G.tile_order;
             }

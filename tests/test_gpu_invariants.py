@@ -160,3 +160,31 @@ def test_knn_of_ties(kind, n):
     best = torch.topk(key, 16, dim=1, largest=False).values.sort(1).values
     assert torch.equal(idx[rows], (best & 0xFFFFFFFF).int())
     assert torch.equal(d2[rows], (best >> 32).int().view(torch.float32))
+
+
+@pytest.mark.parametrize("xcd_remap", [0, 1])
+def test_plan_launch_orders_agree(xcd_remap, monkeypatch):
+    """A plan of two scenes, 133 200 and 9 360 regions, each a launch of its own
+    (no room for compacted lists) and both in one: in tile order (xcd_remap 0) and
+    with the longest lists first, the scenes' sensitivities are those of their
+    own calls."""
+    import synth
+    import paper_2607_02721_amd as gs
+    batch = [(gs.DeviceScene.from_scene(synth.make_cluster_scene(3000, 47 + k, 1)),
+              synth.make_orbit_views(v, 49 + k, 1280, 720)) for k, v in enumerate((37, 3))]
+    ref = [gs.sensitivity(d, vw)[0] for d, vw in batch]
+    for room in ("0", None):
+        if room is None:
+            monkeypatch.delenv("GS_COMPACT_POOL_GB")
+        else:
+            monkeypatch.setenv("GS_COMPACT_POOL_GB", room)
+        plan = gs.Plan([d for d, _ in batch], [v for _, v in batch])
+        assert plan.info()["n_launches"] == (1 if room is None else 2)
+        plan.set_config(0, xcd_remap)
+        for _ in range(2):
+            outs = plan.run()
+        torch.cuda.synchronize()
+        for o, r in zip(outs, ref):
+            assert float(r.max()) > 0
+            assert torch.equal(o, r)
+        plan.close()
