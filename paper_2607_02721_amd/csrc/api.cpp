@@ -1543,6 +1543,7 @@ struct PlanScene {
 // its region (the list guard empties lists that outgrow the capacity).
 struct CompositeBatch {
     int t0 = 0, t1 = 0;
+    int scenes = 0;
     bool compact = false;
 };
 
@@ -1688,7 +1689,7 @@ void enqueue_plan(gs_plan *P, hipStream_t st, float *const *sens) {
             a.region_log = P->region_log;
             a.ccount = cb.compact ? G.ccount + ((size_t)cb.t0 << P->quad_log) : nullptr;
             a.report_floor = P->p.share_floor > 0.0f ? std::nextafter(P->p.share_floor, 0.0f) : 0.0f;
-            if (!a.work && a.xcd_remap && order_pays((int64_t)a.total_tiles << a.region_log, G.scenes.size() == 1)) {
+            if (!a.work && a.xcd_remap && order_pays((int64_t)a.total_tiles << a.region_log, cb.scenes == 1)) {
                 launch_tile_order(a, G.tile_order, G.order_classes, false, st);
                 a.tile_order = G.tile_order;
             }
@@ -1735,15 +1736,16 @@ void plan_batches(gs_plan *P) {
             const int t0 = ps.tile0, t1 = ps.tile0 + ps.c.total_tiles;
             const size_t need = region(ps);
             if (need > pool_budget) {
-                G.batches.push_back(CompositeBatch{t0, t1, false});
+                G.batches.push_back(CompositeBatch{t0, t1, 1, false});
                 used = 0;
                 continue;
             }
             if (G.batches.empty() || !G.batches.back().compact || used + need > pool_budget) {
-                G.batches.push_back(CompositeBatch{t0, t1, true});
+                G.batches.push_back(CompositeBatch{t0, t1, 0, true});
                 used = 0;
             }
             G.batches.back().t1 = t1;
+            ++G.batches.back().scenes;
             off[si] = used;
             used += need;
             pool = std::max(pool, used);
@@ -1754,7 +1756,7 @@ void plan_batches(gs_plan *P) {
         P->pool = nullptr;
         for (PlanGroup &G : P->groups) {
             G.batches.clear();
-            if (G.total_tiles > 0) G.batches.push_back(CompositeBatch{0, G.total_tiles, false});
+            if (G.total_tiles > 0) G.batches.push_back(CompositeBatch{0, G.total_tiles, (int)G.scenes.size(), false});
         }
         return;
     }
