@@ -160,7 +160,8 @@ typedef struct {
     double total_sensitivity; /* S = sum_i s_i, fixed-order reduction */
     double ms_project, ms_sort, ms_bin, ms_pass1, ms_pass2; /* device time per stage, summed over chunks */
     double ms_emit;           /* the tile-list emission kernel (not part of ms_bin) */
-    int64_t n_bins;           /* (tile, chunk) segments: tiles x chunks of 16384 depth positions */
+    int64_t n_bins;           /* (tile, chunk) segments: tiles x chunks of the call's 2^8 to 2^14 depth
+                                 positions (short chunks in calls whose long ones would leave the chip idle) */
     int32_t sort_passes;      /* most 8-bit passes a view chunk's depth sort took: 3 when every view's
                                  depth keys span under 2^24 - 1, else 4 */
     int32_t pad0;

@@ -899,7 +899,7 @@ gs_status gs_sensitivity(const gs_scene *scene, const gs_views *views, const gs_
             GS_OK)
             return s;
         entries += r.n_entries;
-        n_bins += (int64_t)c.total_tiles * chunk_count(S.N, kChunkBitsMax);
+        n_bins += (int64_t)c.total_tiles * S.nchunks;
         sort_passes = std::max(sort_passes, r.passes);
         CompositeArgs a = composite_args(r, c.total_tiles, params, params->share_floor, S);
         a.ccount = r.host_slot.clist ? r.ccount : nullptr;

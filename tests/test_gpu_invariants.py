@@ -188,3 +188,15 @@ def test_plan_launch_orders_agree(xcd_remap, monkeypatch):
             assert float(r.max()) > 0
             assert torch.equal(o, r)
         plan.close()
+
+
+@pytest.mark.parametrize("n,views,height,chunks", [(60_000, 1, 136, 235), (60_000, 200, 136, 59), (20_000, 4096, 272, 2)])
+def test_segment_count(n, views, height, chunks):
+    """gs_stats.n_bins: the (tile, chunk) segments of the call, whose chunks hold
+    2^8, 2^10 and 2^14 depth positions here."""
+    import synth
+    import paper_2607_02721_amd as gs
+    d = gs.DeviceScene.from_scene(synth.make_cluster_scene(n, 45, 0))
+    vw = synth.make_orbit_views(views, 46, 16, height)
+    _, st = gs.sensitivity(d, vw, stats=True)
+    assert st["n_bins"] == views * (height // 16 + (height % 16 > 0)) * chunks
