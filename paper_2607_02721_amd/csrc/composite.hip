@@ -613,34 +613,23 @@ __global__ __launch_bounds__(kWave) void k_pass1_region(CompositeArgs a) {
                            : nullptr;
     uint32_t ccnt = 0u;
     const uint64_t lt = lanemask_lt64();
-    // Two slices ahead their list words and one slice ahead their records are
-    // on the way while a slice composites: a launch of few waves, or its last
-    // long lists, would otherwise wait for memory four times per 64 entries.
+    // List words are loaded two slices ahead, a slice's records at its top.  (Records
+    // a slice ahead as well: 1107 us against 1055 at 50k Gaussians x 24 views.)
     const GlobalPtr<GeoHalf> Rv = as_global((const GeoHalf *)(S.R + vbase));
     const GlobalPtr<float> CBv = as_global(S.CB + vbase);
     const GlobalPtr<uint32_t> lists = as_global(S.lists + start);
     const uint64_t len = end - start;
-    uint32_t want = 0u;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) want |= ((alive >> k) & 1u) ? R.qbit[k] : 0u;
     uint32_t raw = lane < len ? lists[lane] : 0u, raw1 = lane + kWave < len ? lists[lane + kWave] : 0u;
     for (uint64_t e0 = 0; e0 < len && alive; e0 += kWave) {
-        uint32_t h = 0u;
+        uint32_t h = 0u, want = 0u;
         const uint32_t g = raw & kIndexMask;
-        want = 0u;
 #pragma unroll
         for (int k = 0; k < 4; ++k) want |= ((alive >> k) & 1u) ? R.qbit[k] : 0u;
-        GeoHalf pm = {0.0f, 0.0f, 0.0f, 0.0f}, pq = {0.0f, 0.0f, 0.0f, 0.0f};
-        if (raw & want) {
-            pm = Rv[2 * (uint64_t)(raw & kIndexMask)];
-            pq = Rv[2 * (uint64_t)(raw & kIndexMask) + 1];
-        }
-        const float4 r0 = make_float4(pm.x, pm.y, pm.z, pm.w), r1 = make_float4(pq.x, pq.y, pq.z, pq.w);
+        GeoHalf r0 = {0.0f, 0.0f, 0.0f, 0.0f}, r1 = {0.0f, 0.0f, 0.0f, 0.0f};
         float mx0 = 0.0f, my0 = 0.0f, mx1 = 0.0f, my1 = 0.0f, cb = 0.0f;
-        want = 0u;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) want |= ((alive >> k) & 1u) ? R.qbit[k] : 0u;
         if (raw & want) {
+            r0 = Rv[2 * (uint64_t)g];
+            r1 = Rv[2 * (uint64_t)g + 1];
             if (!kCh) cb = CBv[g];
             mx0 = (r0.x - fx0) + r0.z;
             my0 = (r0.y - fy0) + r0.w;
@@ -1081,34 +1070,23 @@ __global__ __launch_bounds__(kWave, kStats ? 5 : (kMode == kModeChannel ? 6 : 7)
     uint32_t n_in = 0, n_live = 0, n_amb = 0, amb = 0u;   // amb: quadrants whose ray saw an ambiguous pair
     uint64_t n_eval = 0;
     const uint64_t lt = lanemask_lt64();
-    // (list words two slices ahead, records and sensitivities one slice ahead,
-    // as in k_pass1_region; a sensitivity read early is only lower, and one that
-    // a share beats is raised by an atomic maximum anyway)
+    // (list words are loaded two slices ahead, a slice's records and sensitivities
+    // at its top, as in k_pass1_region)
     const GlobalPtr<GeoHalf> Rv = as_global((const GeoHalf *)(S.R + vbase));
     const GlobalPtr<float> CBv = as_global(S.CB + vbase);
     const GlobalPtr<uint32_t> sens = as_global((const uint32_t *)sens_bits);
     uint32_t raw = lane < count ? cl[lane] : 0u, raw1 = lane + kWave < count ? cl[lane + kWave] : 0u;
-    GeoHalf pm = {0.0f, 0.0f, 0.0f, 0.0f}, pq = {0.0f, 0.0f, 0.0f, 0.0f};
-    float pcb = 0.0f;
-    uint32_t psens = 0u;
-    auto fetch = [&]() {
-        if ((raw >> 28) & alive) {
-            const uint64_t g = raw & kIndexMask;
-            pm = Rv[2 * g];
-            pq = Rv[2 * g + 1];
-            if (!kCh) pcb = CBv[g];
-            if (kAgg == 0) psens = sens[g];
-        }
-    };
     for (uint32_t e0 = 0; e0 < count && alive; e0 += kWave) {
         const uint32_t h = (raw >> 28) & alive;
         const uint64_t bal = __ballot(h != 0u);
         const int n = __popcll(bal);
-        fetch();
         if (h) {
             const uint32_t g = raw & kIndexMask;
-            const float4 r0 = make_float4(pm.x, pm.y, pm.z, pm.w), r1 = make_float4(pq.x, pq.y, pq.z, pq.w);
-            float cb;
+            const GeoHalf r0 = Rv[2 * (uint64_t)g], r1 = Rv[2 * (uint64_t)g + 1];
+            float cb = 0.0f;
+            if (!kCh) cb = CBv[g];
+            uint32_t old = 0u;
+            if (kAgg == 0) old = sens[g];
             RegionRec &q = rec[__popcll(bal & lt)];
             const float4 sg = scaled_geo((r0.x - fx0) + r0.z, (r0.y - fy0) + r0.w, r1.x, r1.y);
             q.g = sg;
@@ -1118,7 +1096,6 @@ __global__ __launch_bounds__(kWave, kStats ? 5 : (kMode == kModeChannel ? 6 : 7)
                 q.c = make_float4(r1.z, r1.w, c3.x, c3.y);
                 q.cblue = c3.z;
             } else {
-                cb = pcb;
                 const float la = __builtin_amdgcn_logf(r1.w);
                 q.c = make_float4(r1.z, la, cb, cut + la);
             }
@@ -1126,7 +1103,7 @@ __global__ __launch_bounds__(kWave, kStats ? 5 : (kMode == kModeChannel ? 6 : 7)
             q.sid = g;
             q.hq = h;
             if (kAgg == 0) {
-                const float sold = fmaxf(__uint_as_float(psens), a.report_floor);
+                const float sold = fmaxf(__uint_as_float(old), a.report_floor);
                 q.sold = sold;
                 // c x > sold implies x > sold / (c (1 + 2^-24)); the bar sits
                 // below that by more than the rounding of v_rcp_f32 and the
