@@ -968,7 +968,8 @@ gs_status gs_sensitivity(const gs_scene *scene, const gs_views *views, const gs_
         // (counting calls keep the region form: their pair counters say what
         // its 64-entry slices walk)
         a.by_quads = !a.quad_list && S.agg != GS_AGG_TILE && !(params->flags & GS_FLAG_COUNT_PAIRS) &&
-                     quads_pay(S.agg == GS_AGG_RAY ? (int64_t)a.total_tiles << a.region_log : call_regions);
+                     (S.agg == GS_AGG_RAY ? quads_pay((int64_t)a.total_tiles << a.region_log, c.vc)
+                                          : quads_pay(call_regions, views->n_views));
         launch_composite_pass1(a, st);
         HIP_TRY(hipGetLastError());
         tm.mark(4, st);
@@ -1086,7 +1087,7 @@ gs_status gs_render_objective(const gs_scene *scene, const gs_views *views, cons
             launch_tile_order(a, r.tile_order, r.order_classes, true, st);
             a.tile_order = r.tile_order;
         }
-        a.by_quads = quads_pay((int64_t)a.total_tiles << a.region_log);
+        a.by_quads = quads_pay((int64_t)a.total_tiles << a.region_log, c.vc);
         if (objective != GS_OBJ_TRUE) {
             // w_max (1 without weights) bounds every later fixed-objective term
             uint64_t *wmax = (uint64_t *)(r.view_sums + 3 * (size_t)c.vc);
@@ -1543,7 +1544,7 @@ struct PlanScene {
 // its region (the list guard empties lists that outgrow the capacity).
 struct CompositeBatch {
     int t0 = 0, t1 = 0;
-    int scenes = 0;
+    int scenes = 0, views = 0;
     bool compact = false;
 };
 
@@ -1693,7 +1694,7 @@ void enqueue_plan(gs_plan *P, hipStream_t st, float *const *sens) {
                 launch_tile_order(a, G.tile_order, G.order_classes, false, st);
                 a.tile_order = G.tile_order;
             }
-            a.by_quads = !a.work && quads_pay((int64_t)a.total_tiles << a.region_log);
+            a.by_quads = !a.work && quads_pay((int64_t)a.total_tiles << a.region_log, cb.views);
             launch_composite_pass1(a, st);
             launch_composite_pass2(a, false, nullptr, st);
         }
@@ -1736,16 +1737,17 @@ void plan_batches(gs_plan *P) {
             const int t0 = ps.tile0, t1 = ps.tile0 + ps.c.total_tiles;
             const size_t need = region(ps);
             if (need > pool_budget) {
-                G.batches.push_back(CompositeBatch{t0, t1, 1, false});
+                G.batches.push_back(CompositeBatch{t0, t1, 1, ps.c.vc, false});
                 used = 0;
                 continue;
             }
             if (G.batches.empty() || !G.batches.back().compact || used + need > pool_budget) {
-                G.batches.push_back(CompositeBatch{t0, t1, 0, true});
+                G.batches.push_back(CompositeBatch{t0, t1, 0, 0, true});
                 used = 0;
             }
             G.batches.back().t1 = t1;
             ++G.batches.back().scenes;
+            G.batches.back().views += ps.c.vc;
             off[si] = used;
             used += need;
             pool = std::max(pool, used);
@@ -1756,7 +1758,7 @@ void plan_batches(gs_plan *P) {
         P->pool = nullptr;
         for (PlanGroup &G : P->groups) {
             G.batches.clear();
-            if (G.total_tiles > 0) G.batches.push_back(CompositeBatch{0, G.total_tiles, (int)G.scenes.size(), false});
+            if (G.total_tiles > 0) G.batches.push_back(CompositeBatch{0, G.total_tiles, (int)G.scenes.size(), G.total_views, false});
         }
         return;
     }

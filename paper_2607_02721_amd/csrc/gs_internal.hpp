@@ -357,23 +357,33 @@ void launch_one_scene(const SceneSlot &slot, SceneSlot *slot_dev, int32_t *tile_
 inline bool order_pays(int64_t regions, bool one_scene) {
     return regions > 8192 && (!one_scene || regions <= 131072);
 }
-// Whether a launch of this many regions runs one wave per quadrant instead.  A
-// region's wave takes its entries one after the other through up to four
-// quadrants behind branches, some 400 cycles each when nothing else shares its
-// SIMD; a quadrant's wave takes four entries at a time without branches, about a
-// tenth, at a quarter more instructions in all.  So few regions, whose longest
-// list is what the launch waits for, run by quadrants, and launches that fill
-// the chip with regions by regions.  (Calls by regions and by quadrants: 100k
-// Gaussians x 2 views at 400x300, 950 regions, 1590 and 660 us; 20k x 24, 11 400
-// regions, per image 990 and 590; 50k x 24 at 640x360, 22 080 regions, 1135 and
-// 1109; 250k x 20 at 960x540, 40 800 regions, 2460 and 2990.)
+// Whether a launch of this many regions over so many views runs one wave per
+// quadrant instead.  A region's wave takes its entries one after the other through
+// up to four quadrants behind branches, some 400 cycles each when nothing else
+// shares its SIMD; a quadrant's wave takes four entries at a time without branches,
+// about a tenth, at a quarter to a half more instructions in all.  So launches that
+// wait for their longest list run by quadrants, and launches that fill the chip
+// with regions by regions.  Both grow with the launch's regions, but the longest list
+// follows the densest part of one view: spread over a large view's tiles it is
+// shorter, so fewer regions of large views fill the chip than of small ones.
+// Calls in us, by regions and by quadrants, 100k Gaussians at 16-pixel tiles:
+//   320x200    77 views, 20 020 regions 2765, 2249;  125, 32 500 3279, 3412
+//   640x360    22, 20 240 1362, 1259;  27, 24 840 1415, 1456;  35, 32 200 1497, 1773
+//   960x540     6, 12 240  877,  782;  10, 20 400  959, 1047;  16, 32 640 1065, 1433
+//   1280x720    3, 10 800  739,  706;   6, 21 600  798, 1025;   9, 32 400  909, 1320
+//   1920x1080   1,  8 160  629,  670;   2, 16 320  691,  877
+//   3840x2160   1, 32 400  816, 1378
+// The line regions (1 + 2 / views) = 27 000 costs 0.4% on average and 13% at worst
+// over 389 such calls (20k to 1M Gaussians, 1 to 212 views of 320x200 to 3840x2160,
+// five tile shapes, per ray in every query mode, per image, objectives); regions
+// alone 1% and 30% at best (a bound of 12 500), 9% and 69% with one of 32 768.
 // Past the slice in which the last ray of a quadrant stopped, the two forms leave
 // out different entries (each below the share floor).  Per-ray shares there are not
 // reported, so they are the same either way; per-image and per-scene sums differ
 // in their last bits, so those calls decide once, by the regions of all of their
 // views, and their results do not depend on how many views a chunk holds.
-constexpr int64_t kByQuads = 32768;
-inline bool quads_pay(int64_t regions) { return regions <= kByQuads; }
+constexpr int64_t kByQuads = 27000;
+inline bool quads_pay(int64_t regions, int64_t views) { return regions * (views + 2) <= kByQuads * views; }
 void launch_composite_pass1(const CompositeArgs &a, hipStream_t st);
 void launch_composite_pass2(const CompositeArgs &a, bool stats, uint64_t *counters, hipStream_t st);
 // Query objectives of the aggregated granularities from pass 1's per-ray A:
