@@ -321,7 +321,7 @@ typedef struct gs_plan gs_plan;
  * persistent = 0: one workgroup per quadrant or, in large launches, per region of
  * 16x16 pixels, in tile order with xcd_remap = 0; xcd_remap = 1 renumbers
  * workgroups so that consecutive quadrants of a tile row land on one XCD (shared
- * L2), and launches over more than 8192 regions (of a single scene, up to 131072)
+ * L2), and launches over more than 6144 regions (of a single scene, up to 131072)
  * take the tiles with the longest lists first, in runs per XCD.  Default {0, 1}. */
 typedef struct {
     int32_t persistent;

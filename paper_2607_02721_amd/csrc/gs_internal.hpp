@@ -344,18 +344,20 @@ void launch_tile_order(const CompositeArgs &a, int32_t *order, uint32_t *classes
 void launch_tile_views(const ViewDev *views_dev, int Vc, int max_tiles, int32_t *tile_view, hipStream_t st);
 void launch_one_scene(const SceneSlot &slot, SceneSlot *slot_dev, int32_t *tile_scene, int tiles, uint32_t *classes,
                       hipStream_t st);
-// Whether a launch of this many regions takes it.  The chip holds about 7 168
-// of these waves at once: fewer all start together, in any order (3 800 regions
-// lost 3%, 7 280 2%), and from 12 500 on the tail of a launch in tile order,
-// with the dense tiles anywhere, is worth more than the ordering's 20 us.  With
-// many rounds of waves the tail of one scene's views is short and neighbouring
-// tiles, whose records an XCD's L2 then still holds, weigh more (600k Gaussians x
-// 50 views, 180 000 regions: 9.48 ms ordered, 9.26 in tile order; 2M x 60, 348 000:
-// 21.2 and 20.7; 1M x 100, 368 000: alike, with 26 GB read by pass 1 instead of 11);
-// several scenes in one launch end in the densest one's tail instead (a plan of
-// four, 230 400 regions: 5.8 ms ordered, 6.7 in tile order).
+// Whether a launch of this many regions takes it.  Few waves all start together, in
+// any order: 2 800 to 6 000 regions (four waves each by quadrants) measured within
+// 4% of each other either way, save for the ordering's 20 us.  From there the tail
+// of a launch in tile order, with the dense tiles anywhere, is worth more: calls
+// gain 1 to 17% at 6 400 to 8 200 regions, up to 32% at 9 000 to 65 000.  With many
+// rounds of waves the tail of one scene's views is short and neighbouring tiles,
+// whose records an XCD's L2 then still holds, weigh more: ordered calls gain 1 to
+// 11% at 130 000 regions, -2 to 6% at 160 000, -5 to 3% at 200 000, -4 to 1% at
+// 300 000 (30k to 600k Gaussians, views of 320x200 to 1920x1080; at 1M x 100 views,
+// 368 000, alike with 26 GB read by pass 1 instead of 11).  Several scenes in one
+// launch end in the densest one's tail instead: plans of two and four gain 12 to 32%
+// at 14 000 to 115 000 regions and 13% at 230 400.
 inline bool order_pays(int64_t regions, bool one_scene) {
-    return regions > 8192 && (!one_scene || regions <= 131072);
+    return regions > 6144 && (!one_scene || regions <= 131072);
 }
 // Whether a launch of this many regions over so many views runs one wave per
 // quadrant instead.  A region's wave takes its entries one after the other through
