@@ -200,3 +200,71 @@ def test_segment_count(n, views, height, chunks):
     vw = synth.make_orbit_views(views, 46, 16, height)
     _, st = gs.sensitivity(d, vw, stats=True)
     assert st["n_bins"] == views * (height // 16 + (height % 16 > 0)) * chunks
+
+
+# 40 000 tile rows: chunks of 2^13 and 2^14 positions, eight and sixteen batches of
+# 1024 (half as many of 2048 with a mask), the last chunk of 808 and 616 positions
+@pytest.mark.parametrize("n", [9000, 17_000])
+@pytest.mark.parametrize("width", [48, 288])
+def test_emission_of_long_chunks(n, width):
+    """Rows that meet few positions of a batch leave some over for the next, with
+    and without a ray mask, with 3 active tiles per row (taken one by one) and 18
+    (the general form): the selected rays' objectives equal the unmasked call's, and
+    a view's equal those of a call of its own, whose chunks are one batch."""
+    import synth
+    import paper_2607_02721_amd as gs
+    sc = synth.make_cluster_scene(n, 51, 0)
+    sc.log_scale[:] -= np.float32(1.5)
+    vw = synth.make_orbit_views(400, 52, width, 800)
+    d = gs.DeviceScene.from_scene(sc)
+    kw = dict(diag=False, tile=(16, 8))
+    whole = gs.render_objective(d, vw, **kw)["per_ray"]
+    assert float(whole.max()) > 0
+    rays = width * 800
+    mask = torch.full(((400 * rays + 31) // 32,), 0x11111111, dtype=torch.int32, device="cuda")   # every fourth ray
+    part = gs.render_objective(d, vw, ray_mask=mask, **kw)["per_ray"]
+    assert torch.equal(part[::4], whole[::4])
+    assert float(part.view(-1, 4)[:, 1:].abs().max()) == 0
+    for v in (0, 133, 399):
+        one = gs.render_objective(d, vw.subset([v]), **kw)["per_ray"]
+        assert torch.equal(one, whole[v * rays:(v + 1) * rays])
+
+
+@pytest.mark.parametrize("noalloc", [False, True])
+def test_sampler_beyond_the_prefixes_in_lds(noalloc):
+    """More than 2048 blocks of quanta (4.2 million Gaussians), whose prefixes a
+    draw searches in memory: counts, weights and support equal the oracle's."""
+    import paper_2607_02721_amd as gs
+    from oracle import oracle as ora
+    ora.build(force=False)
+    n = 4_300_001
+    rng = np.random.default_rng(53)
+    s = rng.uniform(0, 1, n).astype(np.float32)
+    s[rng.uniform(size=n) < 0.3] = 0
+    s[100_000:110_000] = 0
+    ref = ora.sample(s, 50_000, 9)
+    counts, w, sup = gs.sample_coreset(torch.as_tensor(s).cuda(), 50_000, 9, noalloc=noalloc)
+    assert np.array_equal(counts.cpu().numpy().view(np.uint32), ref["counts"])
+    assert np.array_equal(w.cpu().numpy().view(np.uint64), ref["weights"].view(np.uint64))
+    assert int(sup.item()) == ref["support"]
+
+
+def test_knn_four_levels():
+    """More than 32 x 64^3 means: four levels of nodes."""
+    import paper_2607_02721_amd as gs
+    from paper_2607_02721_amd import learned
+    n = 8_400_001
+    g = torch.Generator(device="cuda").manual_seed(54)
+    m = torch.rand(3, n, generator=g, device="cuda")
+    m[:, ::3] *= 0.1
+    one = lambda *s: torch.ones(*s, device="cuda")  # noqa: E731
+    idx, d2 = learned.knn(gs.DeviceScene(m, -one(3, n), one(4, n), one(n), one(1, 3, n), 0))
+    rows = torch.cat([torch.randint(0, n, (118,), generator=g, device="cuda"), torch.tensor([0, n - 1], device="cuda")])
+    for r in rows.split(20):
+        e = [m[c][None, :] - m[c][r][:, None] for c in range(3)]
+        d = (e[0] * e[0] + e[1] * e[1]) + e[2] * e[2]
+        key = (d.view(torch.int32).long() << 32) | torch.arange(n, device="cuda")[None]
+        key[torch.arange(len(r), device="cuda"), r] = torch.iinfo(torch.int64).max
+        best = torch.topk(key, 16, dim=1, largest=False).values.sort(1).values
+        assert torch.equal(idx[r], (best & 0xFFFFFFFF).int())
+        assert torch.equal(d2[r], (best >> 32).int().view(torch.float32))
