@@ -13,14 +13,15 @@
 //             positions that meet its rows, in order and 2^10 (2^11 with a
 //             ray mask) at a time, into
 //             (position, tile) items packed 64 to a batch; every tile's next
-//             slot comes from a wave-private LDS cursor (atomic add, executed
-//             in issue order), so each (tile, chunk) segment is written
-//             already sorted by p, as g | quadrant mask << 28.
+//             slot comes from a wave-private LDS cursor, taken in the
+//             positions' order, so each (tile, chunk) segment is written
+//             already sorted by p, as g | sub-rectangle mask << 28.
 // Chunks are long so that a tile's segment in a chunk spans whole cache
 // lines: list entries are 4 bytes, and segments of a few entries each end in
 // partial lines that cost a full write each.
-// Bit q of the mask says whether the Gaussian's pixel range touches 8x8
-// quadrant q of the 16x16 tile.
+// The mask's bits name the tile's sub-rectangles (halves in x and y, whatever the
+// tile's size) that the Gaussian's pixel range meets; quad_subrect_bits says which
+// 8x8 quadrants they hold.
 #include "gs_internal.hpp"
 
 #include <algorithm>

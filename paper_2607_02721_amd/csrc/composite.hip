@@ -3,18 +3,19 @@
 // a = c rho T, A = sum a) and the per-Gaussian maximum share
 // (Section 3.2, Eq. sen: s_i = max_q a_i(q) / A(q), rays with A = 0 skipped).
 //
-// Work decomposition: one wave (64 lanes) per 8x8 quadrant of a 16x16 bin
-// tile, one lane per pixel.  Waves are independent: each walks its tile's
-// front-to-back list in slices of 64 entries, keeps the entries whose pixel
-// range touches its quadrant (bit 28+q of the entry), stages their records
-// in wave-private LDS and then composites them from LDS broadcasts.  A ray
+// Work decomposition: one wave (64 lanes) per 8x8 quadrant of a bin tile, one lane
+// per pixel, or (larger launches) one per region of up to 2x2 quadrants, four pixels
+// per lane.  Waves are independent: each walks its tile's front-to-back list in
+// slices of 64 entries, keeps the entries whose pixel range touches its quadrants
+// (the entry's sub-rectangle bits, then an exact test), stages their records in
+// wave-private LDS and then composites them from LDS broadcasts.  A ray
 // stops once T * c_max < floor * A (no later Gaussian can reach a share of
 // `floor`); a wave stops when all of its rays have stopped.
 //
 // Pass 1 writes A per ray.  Pass 2 repeats the walk with the same arithmetic,
 // forms shares a / A, reduces each entry's share over the wave's 64 pixels
-// with a transposed butterfly (32 entries at a time; lane L ends with the
-// maximum of entry L/2), and raises s with an atomic maximum on the float
+// with a transposed butterfly (16 entries at a time; lane L ends with the
+// maximum of entry L / 4), and raises s with an atomic maximum on the float
 // bits (order-free, so the result is deterministic).
 //
 // A launch may cover several scenes (batched plans): each tile of the launch

@@ -26,7 +26,7 @@ constexpr int kSortTile = 4096;    // radix sort: keys per block (4 waves x 16 r
 // use little else of LDS, 1024 took 17% more.
 constexpr int kEmitBatch = 1024, kEmitBatchMasked = 2048;
 constexpr uint32_t kInvisibleKey = 0xFFFFFFFFu;
-constexpr uint32_t kIndexMask = 0x0FFFFFFFu; // list entry = gaussian | quadrant mask << 28
+constexpr uint32_t kIndexMask = 0x0FFFFFFFu; // list entry = gaussian | sub-rectangle mask << 28
 
 // MLP proposal: 64 -> 256 -> 256 -> 256 -> 1; offsets into the FP32 parameter vector.
 constexpr int kMlpIn = 64, kMlpH = 256;
@@ -244,7 +244,7 @@ void launch_bin_count(const ViewDev *views_dev, int Vc, int64_t N, int nchunks, 
 // bin_count -> per-tile prefix over chunks (in place) and tile_tot.
 void launch_chunk_prefix(const ViewDev *views_dev, int Vc, int nchunks, const ChunkBufs &b, int max_tiles,
                          hipStream_t st);
-// Writes every list entry (g | quadrant mask << 28) in its final, sorted
+// Writes every list entry (g | sub-rectangle mask << 28) in its final, sorted
 // place; entries at list index >= cap are dropped.
 void launch_bin_emit(const ViewDev *views_dev, int Vc, int64_t N, int nchunks, const ChunkBufs &b,
                      const uint32_t *xr, const uint32_t *yr, const uint32_t *sorted_g, int max_tiles_x,

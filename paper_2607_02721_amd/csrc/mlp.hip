@@ -518,11 +518,11 @@ __device__ __forceinline__ void fused_store(__bf16 (*Out)[kFusePitch], int w, in
 }
 
 // Inference.  A million rows take at least 0.20 ms of matrix instructions and
-// about 0.25 ms of vector instructions (SiLU's exponential and reciprocal run
-// at a quarter of the rate), so the two have to overlap: a wave holds a layer's
-// weights for its 32 columns in registers (the next layer's are on their way)
-// and goes through the 128 rows 16 at a time, with the SiLU of one 16-row tile
-// beside the products of the next.  Layers alternate between two LDS buffers,
+// about 0.25 ms of vector instructions (SiLU's exponential alone takes 1.9 issue
+// slots, measured), so the two have to overlap: a wave holds a layer's weights for
+// its 32 columns in registers (the next layer's are on their way) and goes through
+// the 128 rows 16 at a time, with the SiLU of one 16-row tile beside the products of
+// the next.  Layers alternate between two LDS buffers,
 // so one barrier per layer is enough; 136 KB make one block per CU, which goes
 // through row blocks in turn with the next block's features already loading.
 // With the products of all rows first, one buffer and 2 blocks of 4 waves per
